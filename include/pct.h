@@ -190,7 +190,8 @@ typedef struct {
     int64_t block_begin; /* first block of every sweep (>= 0)                       */
     int64_t block_end;   /* one past the last block; < 0 means ceil(n/B)            */
     int32_t lanes;       /* lanes per proton in the block kernel: 0 automatic, or
-                            1, 8, 16, 32, 64                                         */
+                            1, 8, 16, 32, 64.  1 gives every proton one lane (and
+                            the separate schedule), any other value a wave of 64   */
     int32_t reserved;    /* must be 0                                              */
 } pct_drop_opts;
 
@@ -199,21 +200,23 @@ typedef struct {
 #define PCT_DROP_NO_GRAPH 0x2u     /* launch per block on the stream, no HIP graph   */
 #define PCT_DROP_PROFILE 0x4u      /* bracket a sample of the per-block kernels with
                                       HIP events on `stream` (see pct_profile_read) */
-/* Block schedules of the FP32 value type with lanes > 1 (DROP's block step,
- * Section IV-B: all rows of block t against the same iterate, then the
+/* Block schedules of the FP32 value type with lanes other than 1 (DROP's block
+ * step, Section IV-B: all rows of block t against the same iterate, then the
  * D-weighted back-projection committed before block t+1).
  *
  * Default, when the workspace holds the slab bins of B rows (pct_workspace_size
  * with n >= B) and max(nx, ny) <= 8192: the binned schedule.  Per block, one
- * launch walks the rows and stores each lane's packed contributions (row count
- * bit + fixed-point rho_i a_ij) into per-(slab, row) bins of the block's
- * dominant in-plane axis; a second launch sums each slab's bins in LDS, one
- * workgroup per slab, and commits x_j += acc_j / s_j over exactly the touched
- * voxels.  The per-voxel integer sums equal those of the atomic schedules.
- * By default the commit carries the FP32 iterate's rounding error in a second
- * FP32 word per voxel (workspace, zeroed at the start of each call), so x is
- * rounded once per call rather than once per commit; the gathers read the
- * FP32 x.  Without a workspace large enough, the fused schedules below run. */
+ * launch walks the rows, stores every piece's chord in per-(slab, row) bins of
+ * the block's dominant in-plane axis and at the end each row's rho_i; a second
+ * launch sums rho_i a_ij (row count bit + fixed point) of each slab's bins in
+ * LDS, one workgroup per slab, and commits x_j += acc_j / s_j over exactly the
+ * touched voxels.  The per-voxel integer sums equal those of the atomic
+ * schedules.  By default the commit carries the FP32 iterate's rounding error in
+ * a second FP32 word per voxel (workspace, zeroed at the start of each call), so
+ * x is rounded once per call rather than once per commit; the gathers read the
+ * FP32 x.  Calls of several block steps keep the iterate in the workspace and
+ * write x when the last one has ended.  Without a workspace large enough, the
+ * fused schedule below runs. */
 #define PCT_DROP_NO_COMPENSATION 0x40u /* binned schedule: round x at every commit
                                           (bitwise the atomic schedules' result) */
 /* The atomic schedules: every piece is one 64-bit atomic into a packed
@@ -224,18 +227,14 @@ typedef struct {
 /* The separate schedule: one block kernel and one commit kernel per block
  * (also the FP64 value type's schedule). */
 #define PCT_DROP_SEPARATE_COMMIT 0x8u
-/* Fused schedule, 64 lanes per proton, blocks of at most 4096 protons,
- * workspace sized for the block: by default the rows of block t+1 are traced
- * in the launch that runs the DROP step of block t (the rows do not depend on
- * x), so each block step no longer waits for its own walk; results are
- * bitwise those of the other atomic schedules.  This flag asks for the plain
- * fused schedule. */
+/* Accepted and without effect: it asked for the fused schedule without rows
+ * traced one launch ahead, which is the only one there is. */
 #define PCT_DROP_NO_TRACE_AHEAD 0x10u
 /* Cancellable call: the block steps stop at the first block boundary after a
  * pct_drop_cancel request on this workspace (see there).  The call runs the
  * binned schedule when it would otherwise (FP32), else the separate schedule
- * (FP64, or FP32 without the bins' workspace); the fused and traced-ahead
- * atomic schedules, whose launches commit the previous block, are not used. */
+ * (FP64, or FP32 without the bins' workspace); the fused schedule, whose
+ * launches commit the previous block, is not used. */
 #define PCT_DROP_CANCELLABLE 0x80u
 /* Deterministic FP64 block sums: each contribution rho_i a_ij is split into
  * its bits above 2^-28 and the rest rounded at 2^-72, and both parts are
@@ -246,11 +245,9 @@ typedef struct {
  * FP32 block sums are integers already: the flag changes nothing there. */
 #define PCT_DROP_DETERMINISTIC 0x100u
 
-/* Workspace bytes for this plan and x of type dtype.  n > 0 adds, for DROP
- * blocks of up to n protons, two row slots (the traced-ahead schedule,
- * 2 * n * 6.4 KB) and the slab bins of the binned schedule
- * (max(nx, ny) * n * 64 B + 2 * max(nx, ny) * n B); with n = 0 pct_drop_iterate
- * uses the atomic schedules. */
+/* Workspace bytes for this plan and x of type dtype.  n > 0 adds the slab bins
+ * of the binned schedule for DROP blocks of up to n protons (max(nx, ny) * n *
+ * 32 B + 12 n B); with n = 0 pct_drop_iterate uses the atomic schedules. */
 int pct_workspace_size(const pct_plan *plan, int64_t n, int32_t dtype, size_t *bytes);
 
 /* Writes the coefficient table into the workspace and clears its counters and

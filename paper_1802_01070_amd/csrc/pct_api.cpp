@@ -62,6 +62,13 @@ GridDev grid_dev(const pct_grid &g)
         d.hi[a] = g.origin[a] + n[a] * g.pitch[a];
     }
     d.inv_nxy = 1.0 / (double(n[0]) * double(n[1]));
+    // signed fields that hold -2 .. n
+    auto bits = [](int32_t v) {
+        int b = 1;
+        for (; v > 0; v >>= 1) ++b;
+        return b;
+    };
+    d.xy_shift = bits(n[0]) + bits(n[1]) <= 32 ? bits(n[0]) : 0;
     return d;
 }
 
@@ -78,6 +85,7 @@ PathSrc path_src(const pct_plan &pl, const void *table_dev)
     p.u_in = pl.mlp.u_in;
     p.u_out = pl.mlp.u_out;
     p.step = pl.mlp.step;
+    p.inv_step = 1.0 / pl.mlp.step;
     for (int k = 0; k < 6; ++k) p.poly[k] = pl.mlp.poly[k];
     p.E0 = pl.mlp.E0;
     p.X0 = pl.mlp.X0;
@@ -354,7 +362,7 @@ int pct_workspace_size(const pct_plan *plan, int64_t n, int32_t dtype, size_t *b
 {
     if (!plan || !bytes || n < 0 || !valid_dtype(dtype)) return PCT_ERR_INVALID_ARG;
     const int nslab = std::max(plan->grid.nx, plan->grid.ny);
-    *bytes = layout_for(plan->nvox, plan->K, dtype).total + (n > 0 ? 2 * slot_bytes(n) + bin_bytes(n, nslab) : 0);
+    *bytes = layout_for(plan->nvox, plan->K, dtype).total + (n > 0 ? bin_bytes(n, nslab) : 0);
     return PCT_OK;
 }
 

@@ -22,6 +22,7 @@ struct GridDev {
     double inv_pitch[3];
     double inv_n[3];   // 1 / n and 1 / (nx ny): exact integer quotients by the extents
     double inv_nxy;
+    int32_t xy_shift;  // bits of ix in a packed (ix, iy) pair, 0: the pair does not fit 32 bits
     double lo[3];  // origin
     double hi[3];  // origin + n*pitch
 };
@@ -38,7 +39,7 @@ struct PathSrc {
     int nvmax;          // most vertices a proton's polyline can have
     int hull;           // 0 or 1
     double hx, hy, hr;  // hull centre and radius (mm)
-    double u_in, u_out, step;
+    double u_in, u_out, step, inv_step;
     double poly[6], E0, X0;
     int log_term;
 };
@@ -61,21 +62,14 @@ struct Layout {
     size_t x1;       // second copy of the iterate, nvox doubles
     size_t partial;  // kMaxPartials doubles
     size_t lo;       // compensation word of the FP32 iterate, nvox floats
-    size_t total;    // end of the fixed part; the traced-ahead row slots and the bins follow
-
+    size_t total;    // end of the fixed part; the bins follow
 };
 constexpr int kMaxPartials = 4096;
-// One traced-ahead row record: 12 stash entries x 64 lanes of (voxel, chord),
-// 64 lane counts and ||a_i||^2 (two slots of B records follow Layout::total).
-constexpr size_t kSlotRecordBytes = size_t(12) * 64 * 8 + 64 * 4 + 8;
-inline size_t slot_bytes(int64_t records) { return (size_t(records) * kSlotRecordBytes + 255) & ~size_t(255); }
-// Slab bins of the binned schedule (after the two row slots): per slab of the
-// block's dominant axis and row of the block, kBinCap entries (a packed
-// 64-bit word each, the voxel index of entries 1.. in a second array) and, per
-// block parity, the voxel index of entry 0 with the entry count in its top
-// bits: 52 bytes per (slab, row); then the largest contribution of every row
-// (one float per row).  Rows are rounded up to a multiple of 16;
-// blocks of the binned schedule hold at most kBinMaxRows rows.
+// Slab bins of the binned schedule (after Layout::total): per slab of the
+// block's dominant axis and row of the block, kBinCap entries of 8 bytes (cell
+// of the voxel in the slab, chord), 32 bytes; then rho_i (a double) and the largest contribution (a
+// float) of every row.  Rows are rounded up to a multiple of 16; blocks of the
+// binned schedule hold at most kBinMaxRows rows.
 constexpr int kBinCap = 4;
 constexpr int kBinMaxRows = 8192;
 constexpr int kWinWords = 16384;  // LDS window of a slab commit: 128 KB of packed words
@@ -83,21 +77,16 @@ inline int64_t bin_rows(int64_t records) { return (records + 15) & ~int64_t(15);
 inline size_t bin_bytes(int64_t records, int nslab)
 {
     const size_t nrow = size_t(nslab) * size_t(bin_rows(records));
-    return (nrow * (kBinCap * 8 + (kBinCap - 1) * 4 + 2 * 4) + size_t(bin_rows(records)) * 4 + 255) & ~size_t(255);
+    return (nrow * kBinCap * 8 + size_t(bin_rows(records)) * 12 + 255) & ~size_t(255);
 }
 
-// header words (int32 index): status word, then the [jmin, jmax] voxel range
-// touched by a block, double-buffered by block parity (FP64 path), four
-// rotating range slots of the fused FP32 path, the two overflow flags of the
+// header words (int32 index): status word, the two overflow flags of the
 // binned schedule (by block parity), and the block-boundary gate of
 // cancellable calls: the host's cancel request, the gate word, the count of
 // ended workgroups of the running commit launch and (int64) the block steps
 // applied
 enum : int {
     kHdrStatus = 0,
-    kHdrRange0 = 2,
-    kHdrRange1 = 4,
-    kHdrSlots = 8,
     kHdrOvf = 16,
     kHdrCancel = 20,
     kHdrHalt = 21,

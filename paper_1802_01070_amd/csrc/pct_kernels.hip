@@ -3,12 +3,13 @@
 //   k_trace        ordered emission list of each proton's path (debug/parity)
 //   k_forward      y = A x, ||a_i||^2   (one lane per proton, gathers)
 //   k_backproject  g += A^T r           (one lane per proton, LDS-summed, atomics)
-//   k_drop_block   DROP block, LPP lanes per proton: walk -> a_i.x, ||a_i||^2 ->
-//                  rho_i -> re-walk and scatter rho_i a_ij into the block
-//                  accumulator and the per-voxel row count; records the
-//                  block's touched voxel index range
-//   k_drop_rows    the same with one lane per proton (very long paths)
-//   k_drop_commit  x_j += acc_j / s_j over the touched range, reset
+//   k_drop_bin     DROP block, a wave per row: records -> a_i.x, ||a_i||^2 ->
+//                  rho_i, chords into slab bins (FP32)
+//   k_slab_commit  x_j += acc_j / s_j slab by slab from the bins
+//   k_drop_block   DROP block, a wave per row, one atomic per piece (separate
+//                  schedule); k_drop_fused: with the commit of the block before
+//   k_drop_rows    the same with one lane per row
+//   k_drop_commit  x_j += acc_j / s_j, reset
 //   k_tv           smoothed total variation value and gradient
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
@@ -23,6 +24,7 @@
 
 #include "pct_internal.h"
 #include "pct_path.hpp"
+#include "pct_walk.hpp"
 
 namespace pct {
 
@@ -157,11 +159,15 @@ __global__ void __launch_bounds__(kWG) k_trace(ProtonsDev p, int64_t first, int6
 // ---------------------------------------------------------------------------
 // forward projection
 // ---------------------------------------------------------------------------
-// Value of the iterate at voxel j seen by a block.
+// Value of the iterate at voxel j seen by a block.  load() issues the read,
+// value() consumes it.
 template <typename T>
 struct PlainX {
+    using Raw = T;
     const T *__restrict__ x;
-    __device__ __forceinline__ double operator()(int j) const { return double(x[j]); }
+    __device__ __forceinline__ Raw load(int j) const { return x[j]; }
+    __device__ __forceinline__ static double value(Raw v) { return double(v); }
+    __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
 };
 
 template <typename T, class XA = PlainX<T>>
@@ -188,8 +194,7 @@ __global__ void __launch_bounds__(kWG) k_forward(ProtonsDev p, int64_t first, in
     Rec r = load_rec(p, i);
     DotSink<T> s;
     s.x = PlainX<T>{x};
-    s.dot = 0.0;
-    s.n2 = 0.0;
+    s.dot = s.n2 = 0.0;
     s.re.init(r);
     if (rec_finite(r)) {
         Merge<DotSink<T>, PCT_CHORD_F64> m(s, g);
@@ -320,7 +325,10 @@ __device__ __forceinline__ unsigned long long pack_contribution(double v, bool f
         if (v != v) v = 0.0;
         else v = fmin(fmax(v, -kFixMax), kFixMax);
     }
-    const long long q = llrint(v * kFixScale);
+    // adding 1.5 2^52 rounds to a whole number (to nearest, ties to even) and
+    // leaves it in the low bits: |v| 2^28 stays below 2^41
+    constexpr double kShift = 6755399441055744.0;
+    const long long q = __double_as_longlong(fma(v, kFixScale, kShift)) - __double_as_longlong(kShift);
     return static_cast<unsigned long long>(q) + (first ? (1ull << kCntShift) : 0ull);
 }
 
@@ -389,53 +397,20 @@ struct DropScatterSink {
     unsigned *status;
     Reentry re;
     double rho;
-    int jmin, jmax;
     __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
     __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
     {
         bool first;
         re.visit(j, ix, iy, iz, c, first);
         scatter_one<T>(acc, acc_lo, cnt, j, rho * c, first, status);
-        jmin = min(jmin, j);
-        jmax = max(jmax, j);
     }
 };
 
-// Workgroup-wide min/max of the touched voxel range, then one atomic pair per
-// workgroup into the block's range words.  Every thread of the workgroup must
-// call it.
-__device__ __forceinline__ void publish_range(int jmin, int jmax, int *range)
-{
-    __shared__ int smin[kWG / 64], smax[kWG / 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        jmin = min(jmin, __shfl_xor(jmin, off, 64));
-        jmax = max(jmax, __shfl_xor(jmax, off, 64));
-    }
-    const int w = threadIdx.x / 64;
-    if ((threadIdx.x & 63) == 0) {
-        smin[w] = jmin;
-        smax[w] = jmax;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int a = smin[0], b = smax[0];
-        for (int q = 1; q < int(blockDim.x / 64); ++q) {
-            a = min(a, smin[q]);
-            b = max(b, smax[q]);
-        }
-        // same-address atomics serialise across the chip: only issue the ones
-        // that can still move the extremes (they only ever tighten)
-        if (b >= a) {
-            if (a < __hip_atomic_load(range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(range, a);
-            if (b > __hip_atomic_load(range + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(range + 1, b);
-        }
-    }
-}
-
+// One lane per row, two walks (lanes = 1, and grids whose in-plane index does not
+// fit the wave kernels' packed pair).
 template <typename T, int CHORD, bool HULL>
 __global__ void __launch_bounds__(kWG) k_drop_rows(ProtonsDev p, const float *__restrict__ b,
-                                                   const T *__restrict__ x, void *acc, int32_t *cnt, int *range,
+                                                   const T *__restrict__ x, void *acc, int32_t *cnt,
                                                    const PathSrc src,  GridDev g, int64_t lo,
                                                    int64_t hi, double lambda, unsigned *status, long long *acc_lo,
                                                    const int *halt)
@@ -454,13 +429,10 @@ __global__ void __launch_bounds__(kWG) k_drop_rows(ProtonsDev p, const float *__
         }
     }
     DropScatterSink<T> sc;
-    sc.jmin = INT_MAX;
-    sc.jmax = -1;
     if (active) {
         DotSink<T> s;
         s.x = PlainX<T>{x};
-        s.dot = 0.0;
-        s.n2 = 0.0;
+        s.dot = s.n2 = 0.0;
         s.re.init(r);
         {
             Merge<DotSink<T>, CHORD> m(s, g);
@@ -480,24 +452,13 @@ __global__ void __launch_bounds__(kWG) k_drop_rows(ProtonsDev p, const float *__
             m.finish();
         }
     }
-    publish_range(sc.jmin, sc.jmax, range);
 }
 
 // ---------------------------------------------------------------------------
-// DROP block kernel, LPP lanes per proton.
-//
-// The path is monotone along its dominant in-plane axis (the lab axis closest
-// to the beam direction), so a voxel can only be visited again while the path
-// stays inside one slab of that axis.  The slabs the path crosses are split
-// into LPP contiguous ranges, one per lane; each lane walks the pieces of the
-// path inside its range.  Lanes therefore never share a voxel: merging,
-// re-entry tracking, ||a_i||^2 and the once-per-row count stay lane-local, and
-// the only cross-lane step is the sum of a_i.x and ||a_i||^2.
-//
-// Per proton: the dominant coordinate of every vertex is staged in LDS (one
-// value per vertex, computed by the group's lanes in parallel); it gives the
-// monotonicity check and, by binary search, each lane's first segment.  A path
-// that is not monotone falls back to a single-lane walk of the whole row.
+// DROP block kernels, one wave (and workgroup) per row: the row's records in
+// LDS (pct_walk.hpp), a pass over its pieces for a_i.x and ||a_i||^2, and the
+// scatter, a second pass over the same records (fused and separate schedule)
+// or stored by the first one (binned schedule).
 // ---------------------------------------------------------------------------
 template <int LPP>
 __device__ __forceinline__ double group_sum(double v)
@@ -507,380 +468,77 @@ __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
-template <int LPP>
-__device__ __forceinline__ double group_max(double v)
+// Record of the block that workgroup w takes (hi: none).  XCD-aware: workgroup
+// w runs on XCD w mod 8, so the rows are dealt to the eight XCDs in contiguous
+// runs of the block (a multiple of eight is launched, the padding workgroups
+// idle), and each XCD walks a band of neighbouring paths of an ordered block
+// and finds their voxels in its own L2.
+__device__ __forceinline__ int64_t row_of_workgroup(int w, int64_t lo, int64_t hi)
 {
-#pragma unroll
-    for (int off = LPP / 2; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+    const int64_t per_xcd = (hi - lo + 7) / 8;
+    const int64_t q = int64_t(w % 8) * per_xcd + w / 8;
+    return q < hi - lo ? lo + q : hi;
 }
 
-template <int LPP>
-__device__ __forceinline__ bool group_any(bool p)
+// a_i.x and ||a_i||^2 of a row.  Chords enter a_i.x as CT values.
+template <typename CT, int CHORD, bool HULL, class XA>
+__device__ __forceinline__ void row_dot(const RowPath<HULL> &p, RecWindow &win, int dom, const XA &xa, bool &have,
+                                        bool &onward, double &dot, double &n2)
 {
-    int v = p ? 1 : 0;
-#pragma unroll
-    for (int off = LPP / 2; off > 0; off >>= 1) v |= __shfl_xor(v, off, 64);
-    return v != 0;
+    double d = 0.0, s = 0.0;
+    const int sy = p.g.n[0], sz = p.g.n[0] * p.g.n[1];
+    row_pieces<HULL, CHORD>(p, win, dom, have, onward, [&](const RowPiece &q) {
+        if (!q.real) return;
+        d = fma(double(CT(q.c)), xa(q.ix + sy * q.iy + sz * q.iz), d);
+        s = fma(q.c, fma(2.0, q.before, q.c), s);
+    });
+    dot = wave_sum(d);
+    n2 = wave_sum(s);
 }
 
-// Per-proton path state shared by the LPP lanes of its group.  The lab
-// coordinates of every vertex live in LDS (P, 3 doubles per vertex); the
-// signed coordinate along the dominant axis, A(k) = sgn * P[k][dom], increases
-// along a monotone path.
-struct GroupPath {
-    int K;           // segments of this proton's polyline
-    int dom;         // dominant in-plane axis (0: x, 1: y)
-    double sgn;      // direction of travel along it
-    int s_lo, s_hi;  // dominant-axis index range crossed by the path (s_lo > s_hi: none)
-    bool full;       // not monotone: lane 0 walks the whole row over the whole grid
-};
-
-__device__ __forceinline__ double path_A(const GroupPath &gp, const double *__restrict__ P, int k)
+// Both passes of the atomic schedules over row i.
+template <typename T, int CHORD, bool HULL, class XA>
+__device__ __forceinline__ void drop_row(const ProtonsDev &p, const float *__restrict__ b, const XA &xa, void *acc,
+                                         long long *acc_lo, int32_t *cnt, const PathSrc &src, const GridDev &g,
+                                         int64_t i, int span, double lambda, unsigned *status)
 {
-    return gp.sgn * P[3 * k + gp.dom];
-}
-
-template <int LPP, bool HULL>
-__device__ __forceinline__ GroupPath stage_path(const Rec &r, const PathSrc &src, const GridDev &g,
-                                                double *__restrict__ P, int l, bool active)
-{
-    GroupPath gp;
-    gp.dom = fabs(r.cs) >= fabs(r.sn) ? 0 : 1;
-    const double e = gp.dom == 0 ? r.cs : r.sn;
-    gp.sgn = e > 0.0 ? 1.0 : -1.0;
-    const PathState ps = path_prepare<HULL>(r, src);
-    const int K = ps.nv - 1;
-    gp.K = K;
-    for (int k = l; k <= K; k += LPP) {
-        double v[3] = {0.0, 0.0, 0.0};
-        if (active) path_vertex<HULL>(r, src, ps, k, v);
-        P[3 * k] = v[0];
-        P[3 * k + 1] = v[1];
-        P[3 * k + 2] = v[2];
-    }
-    __syncthreads();
-    bool bad = !active;
-    for (int k = l; k < K; k += LPP) bad |= !(path_A(gp, P, k + 1) > path_A(gp, P, k));
-    gp.full = group_any<LPP>(bad);
-    gp.s_lo = 0;
-    gp.s_hi = -1;
-    if (gp.full) {
-        if (active) gp.s_hi = g.n[gp.dom] - 1;
-        return gp;
-    }
-    const int a = gp.dom;
-    const double c0 = P[a], c1 = P[3 * K + a];
-    const double f0 = floor((fmin(c0, c1) - g.lo[a]) * g.inv_pitch[a]);
-    const double f1 = floor((fmax(c0, c1) - g.lo[a]) * g.inv_pitch[a]);
-    if (f1 < 0.0 || f0 > double(g.n[a] - 1)) return gp;
-    gp.s_lo = int(fmax(f0, 0.0));
-    gp.s_hi = int(fmin(f1, double(g.n[a] - 1)));
-    return gp;
-}
-
-// The lane's share of the path: a contiguous range of dominant-axis slabs
-// (lanes take consecutive ranges in the direction of travel), walked as one
-// run of segments clipped to the range.  A non-monotone path is walked whole
-// by lane 0.
-template <int LPP, class M>
-__device__ __forceinline__ void walk_lane(const GroupPath &gp, int l, const GridDev &g,
-                                          const double *__restrict__ P, M &m)
-{
-    const int K = gp.K;
-    const int a = gp.dom;
-    if (gp.full) {
-        if (l != 0 || gp.s_hi < gp.s_lo) return;
-        for (int k = 0; k < K; ++k) {
-            const double *p0 = P + 3 * k, *p1 = P + 3 * k + 3;
-            m.segment(p1[0] - p0[0], p1[1] - p0[1]);
-            walk_segment_range(p0, p1, g, a, 0, g.n[a] - 1, m);
-        }
-        return;
-    }
-    const int ns = gp.s_hi - gp.s_lo + 1;
-    if (ns <= 0) return;
-    const int q = ns / LPP, rem = ns % LPP;
-    const int off = l * q + min(l, rem);
-    const int cntl = q + (l < rem ? 1 : 0);
-    if (cntl <= 0) return;
-    int s0, s1;
-    if (gp.sgn > 0.0) {
-        s0 = gp.s_lo + off;
-        s1 = s0 + cntl - 1;
-    } else {
-        s1 = gp.s_hi - off;
-        s0 = s1 - cntl + 1;
-    }
-    // entry and exit planes of the range in signed coordinate
-    const double entry = gp.sgn > 0.0 ? g.lo[a] + s0 * g.pitch[a] : -(g.lo[a] + (s1 + 1) * g.pitch[a]);
-    const double exitc = gp.sgn > 0.0 ? g.lo[a] + (s1 + 1) * g.pitch[a] : -(g.lo[a] + s0 * g.pitch[a]);
-    // last vertex k in [0, K-1] with A(k) <= entry
-    int lo = 0, hi = K - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (path_A(gp, P, mid) <= entry) lo = mid;
-        else hi = mid - 1;
-    }
-    for (int k = lo; k < K; ++k) {
-        const double *p0 = P + 3 * k, *p1 = P + 3 * k + 3;
-        walk_segment_range(p0, p1, g, a, s0, s1, m);
-        if (path_A(gp, P, k + 1) >= exitc) break;
-    }
-}
-
-// Table-path form of the group staging: LDS holds only the signed dominant
-// coordinate A(k) of every vertex (one double per vertex instead of three),
-// which is all the monotonicity check and the lanes' binary searches read; a
-// lane recomputes the full vertices of the segments it walks from the shared
-// table, with the same arithmetic, so the walk sees the same values.
-template <int LPP>
-__device__ __forceinline__ GroupPath stage_path_dom(const Rec &r, const PathSrc &src, const GridDev &g,
-                                                    double *__restrict__ A, int l, bool active)
-{
-    GroupPath gp;
-    gp.dom = fabs(r.cs) >= fabs(r.sn) ? 0 : 1;
-    const double e = gp.dom == 0 ? r.cs : r.sn;
-    gp.sgn = e > 0.0 ? 1.0 : -1.0;
-    const int K = src.K;
-    gp.K = K;
-    for (int k = l; k <= K; k += LPP) {
-        double v[3] = {0.0, 0.0, 0.0};
-        if (active) vertex(r, src.tab + k * kRowDoubles, v);
-        A[k] = gp.sgn * v[gp.dom];
-    }
-    __syncthreads();
-    bool bad = !active;
-    for (int k = l; k < K; k += LPP) bad |= !(A[k + 1] > A[k]);
-    gp.full = group_any<LPP>(bad);
-    gp.s_lo = 0;
-    gp.s_hi = -1;
-    if (gp.full) {
-        if (active) gp.s_hi = g.n[gp.dom] - 1;
-        return gp;
-    }
-    const int a = gp.dom;
-    const double c0 = gp.sgn * A[0], c1 = gp.sgn * A[K];  // sgn = +-1: the vertices' own coordinates
-    const double f0 = floor((fmin(c0, c1) - g.lo[a]) * g.inv_pitch[a]);
-    const double f1 = floor((fmax(c0, c1) - g.lo[a]) * g.inv_pitch[a]);
-    if (f1 < 0.0 || f0 > double(g.n[a] - 1)) return gp;
-    gp.s_lo = int(fmax(f0, 0.0));
-    gp.s_hi = int(fmin(f1, double(g.n[a] - 1)));
-    return gp;
-}
-
-// walk_lane over a stage_path_dom staging: the same slab range, start vertex
-// and stop test, with the segment end points recomputed from the table.
-template <int LPP, class M>
-__device__ __forceinline__ void walk_lane_dom(const GroupPath &gp, int l, const GridDev &g,
-                                              const double *__restrict__ A, const Rec &r, const PathSrc &src, M &m)
-{
-    const int K = gp.K;
-    const int a = gp.dom;
-    double p0[3], p1[3];
-    if (gp.full) {
-        if (l != 0 || gp.s_hi < gp.s_lo) return;
-        vertex(r, src.tab, p0);
-        for (int k = 0; k < K; ++k) {
-            vertex(r, src.tab + (k + 1) * kRowDoubles, p1);
-            m.segment(p1[0] - p0[0], p1[1] - p0[1]);
-            walk_segment_range(p0, p1, g, a, 0, g.n[a] - 1, m);
-            p0[0] = p1[0];
-            p0[1] = p1[1];
-            p0[2] = p1[2];
-        }
-        return;
-    }
-    const int ns = gp.s_hi - gp.s_lo + 1;
-    if (ns <= 0) return;
-    const int q = ns / LPP, rem = ns % LPP;
-    const int off = l * q + min(l, rem);
-    const int cntl = q + (l < rem ? 1 : 0);
-    if (cntl <= 0) return;
-    int s0, s1;
-    if (gp.sgn > 0.0) {
-        s0 = gp.s_lo + off;
-        s1 = s0 + cntl - 1;
-    } else {
-        s1 = gp.s_hi - off;
-        s0 = s1 - cntl + 1;
-    }
-    const double entry = gp.sgn > 0.0 ? g.lo[a] + s0 * g.pitch[a] : -(g.lo[a] + (s1 + 1) * g.pitch[a]);
-    const double exitc = gp.sgn > 0.0 ? g.lo[a] + (s1 + 1) * g.pitch[a] : -(g.lo[a] + s0 * g.pitch[a]);
-    int lo = 0, hi = K - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (A[mid] <= entry) lo = mid;
-        else hi = mid - 1;
-    }
-    vertex(r, src.tab + lo * kRowDoubles, p0);
-    for (int k = lo; k < K; ++k) {
-        vertex(r, src.tab + (k + 1) * kRowDoubles, p1);
-        walk_segment_range(p0, p1, g, a, s0, s1, m);
-        if (A[k + 1] >= exitc) break;
-        p0[0] = p1[0];
-        p0[1] = p1[1];
-        p0[2] = p1[2];
-    }
-}
-
-// Staging and lane walk of the binned and separate-commit block kernels: hull
-// paths keep every vertex in LDS (a hull vertex costs two quadratures), table
-// paths only A(k).
-template <int LPP, bool HULL>
-__device__ __forceinline__ GroupPath stage_group(const Rec &r, const PathSrc &src, const GridDev &g, double *P,
-                                                 int l, bool active)
-{
-    if constexpr (HULL)
-        return stage_path<LPP, true>(r, src, g, P, l, active);
-    else
-        return stage_path_dom<LPP>(r, src, g, P, l, active);
-}
-
-template <int LPP, bool HULL, class M>
-__device__ __forceinline__ void walk_group_lane(const GroupPath &gp, int l, const GridDev &g, const double *P,
-                                                const Rec &r, const PathSrc &src, M &m)
-{
-    if constexpr (HULL)
-        walk_lane<LPP>(gp, l, g, P, m);
-    else
-        walk_lane_dom<LPP>(gp, l, g, P, r, src, m);
-}
-
-// Doubles of LDS a group's staging takes per vertex.
-template <bool HULL>
-constexpr int kStageDoubles = HULL ? 3 : 1;
-
-// Walk sink of the block kernel: tracks re-entries, accumulates ||a_i||^2 and
-// stashes the lane's merged pieces (voxel | first-visit bit, chord) in LDS,
-// entry-major so that the lanes of a wave hit different banks.
-template <typename CT, int S>
-struct StashSink {
-    int *__restrict__ sj;
-    CT *__restrict__ sc;
-    int lane;
-    Reentry re;
-    double n2;
-    int count;
-    __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
-    __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
-    {
-        bool first;
-        const double aprev = re.visit(j, ix, iy, iz, c, first);
-        n2 += c * (2.0 * aprev + c);
-        if (count < S) {
-            sj[count * 64 + lane] = first ? (j | int(0x80000000u)) : j;
-            sc[count * 64 + lane] = CT(c);
-        }
-        ++count;
-    }
-};
-
-constexpr int kStash = 12;  // pieces per lane kept in LDS; longer lanes walk again
-
-template <typename T>
-__host__ __device__ constexpr size_t stash_bytes()
-{
-    return size_t(64) * kStash * (sizeof(int) + (sizeof(T) == 4 ? sizeof(float) : sizeof(double)));
-}
-
-// Fused DROP block kernel: one wave per workgroup, 64 / LPP protons per wave.
-template <typename T, int CHORD, int LPP, bool HULL>
-__global__ void __launch_bounds__(64) k_drop_block(ProtonsDev p, const float *__restrict__ b,
-                                                   const T *__restrict__ x, void *acc, int32_t *cnt, int *range,
-                                                   const PathSrc src,  GridDev g, int64_t lo,
-                                                   int64_t hi, double lambda, unsigned *status, long long *acc_lo,
-                                                   const int *halt)
-{
-    if (gate_closed(halt)) return;
     using CT = typename std::conditional<sizeof(T) == 4, float, double>::type;
     extern __shared__ double lds[];
-    constexpr int GPW = 64 / LPP;  // proton groups per workgroup
-    const int lane = threadIdx.x;
-    const int grp = lane / LPP;
-    const int l = lane % LPP;
-    const int64_t i = lo + int64_t(blockIdx.x) * GPW + grp;
-    bool active = i < hi;
-    Rec r{};
-    double bi = 0.0;
-    if (active) {
-        r = load_rec(p, i);
-        bi = double(b[i]);
-        if (!rec_finite(r) || !isfinite(bi)) {
-            if (l == 0) raise_status(status, PCT_DEV_NONFINITE);
-            active = false;
-        }
+    const Rec r = load_rec(p, i);
+    const double bi = double(b[i]);
+    if (!rec_finite(r) || !isfinite(bi)) {
+        raise_status(status, PCT_DEV_NONFINITE);
+        return;
     }
-    if (!active) r.cs = 1.0, r.sn = 0.0;
-    double *P = lds + grp * kStageDoubles<HULL> * src.nvmax;
-    char *stash = reinterpret_cast<char *>(lds + GPW * kStageDoubles<HULL> * src.nvmax);
-    int *sj = reinterpret_cast<int *>(stash);
-    CT *sc = reinterpret_cast<CT *>(stash + size_t(64) * kStash * sizeof(int));
-    const GroupPath gp = stage_group<LPP, HULL>(r, src, g, P, l, active);
+    const RowPath<HULL> path(src, g, r);
+    const int dom = dominant_axis(r);
+    RecWindow win(lds, src.nvmax, span);
+    bool have = false, onward = true;
+    double dot, n2;
+    row_dot<CT, CHORD, HULL>(path, win, dom, xa, have, onward, dot, n2);
+    if (!onward) raise_status(status, PCT_DEV_REENTRY);
+    if (!(n2 > 0.0)) return;
+    const double rho = lambda * (bi - dot) / n2;
+    const int sy = g.n[0], sz = g.n[0] * g.n[1];
+    row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+        if (!q.real) return;
+        const int j = q.ix + sy * q.iy + sz * q.iz;
+        scatter_one<T>(acc, acc_lo, cnt, j, rho * double(CT(q.c)), q.first, status);
+    });
+}
 
-    // one walk: ||a_i||^2, re-entries and the stash of pieces
-    StashSink<CT, kStash> st{sj, sc, lane, {}, 0.0, 0};
-    st.re.init(r);
-    {
-        Merge<StashSink<CT, kStash>, CHORD> m(st, g);
-        walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-        m.finish();
-    }
-    if (st.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-    const bool spill = st.count > kStash;
-    const int ns = min(st.count, kStash);
-    // a_i . x: gathers from the stash (independent loads)
-    double dot = 0.0;
-    if (!spill) {
-#pragma unroll 4
-        for (int q = 0; q < ns; ++q) {
-            const int j = sj[q * 64 + lane] & 0x7FFFFFFF;
-            dot += double(sc[q * 64 + lane]) * double(x[j]);
-        }
-    } else {
-        DotSink<T> ds;
-        ds.x = PlainX<T>{x};
-        ds.dot = 0.0;
-        ds.n2 = 0.0;
-        ds.re.init(r);
-        Merge<DotSink<T>, CHORD> m(ds, g);
-        walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-        m.finish();
-        dot = ds.dot;
-    }
-    dot = group_sum<LPP>(dot);
-    const double n2 = group_sum<LPP>(st.n2);
-    int jmin = INT_MAX, jmax = -1;
-    if (n2 > 0.0) {
-        const double rho = lambda * (bi - dot) / n2;
-        if (!spill) {
-            for (int q = 0; q < ns; ++q) {
-                const int e = sj[q * 64 + lane];
-                const int j = e & 0x7FFFFFFF;
-                const bool first = e < 0;
-                const double v = rho * double(sc[q * 64 + lane]);
-                scatter_one<T>(acc, acc_lo, cnt, j, v, first, status);
-                jmin = min(jmin, j);
-                jmax = max(jmax, j);
-            }
-        } else {
-            DropScatterSink<T> sc2;
-            sc2.acc = acc;
-            sc2.acc_lo = acc_lo;
-            sc2.cnt = cnt;
-            sc2.status = status;
-            sc2.rho = rho;
-            sc2.jmin = INT_MAX;
-            sc2.jmax = -1;
-            sc2.re.init(r);
-            Merge<DropScatterSink<T>, CHORD> m(sc2, g);
-            walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-            m.finish();
-            jmin = sc2.jmin;
-            jmax = sc2.jmax;
-        }
-    }
-    publish_range(jmin, jmax, range);
+// Separate schedule: the block kernel (k_drop_commit follows).
+template <typename T, int CHORD, bool HULL>
+__global__ void __launch_bounds__(kWave) k_drop_block(ProtonsDev p, const float *__restrict__ b,
+                                                      const T *__restrict__ x, void *acc, int32_t *cnt,
+                                                      const PathSrc src, GridDev g, int64_t lo, int64_t hi,
+                                                      double lambda, unsigned *status, long long *acc_lo,
+                                                      const int *halt, int span)
+{
+    if (gate_closed(halt)) return;
+    const int64_t i = row_of_workgroup(int(blockIdx.x), lo, hi);
+    if (i >= hi) return;
+    drop_row<T, CHORD, HULL>(p, b, PlainX<T>{x}, acc, acc_lo, cnt, src, g, i, span, lambda, status);
 }
 
 // ---------------------------------------------------------------------------
@@ -893,12 +551,13 @@ __global__ void __launch_bounds__(64) k_drop_block(ProtonsDev p, const float *__
 //   q-1's sums.  Block q reads  xbar_j = base_j + sum_j / s_j  (the committed
 //   value of block q-1, computed on the fly) and scatters into PK[q % 3].
 //   In the same launch, commit workgroups write X[(q+1) % 2] = base + update
-//   over the index ranges of blocks q-1 and q-2 (the only places where the two
-//   copies differ) and clear PK[(q-2) % 3].  Nothing read in a launch is
-//   written in it, so no grid-wide synchronisation is needed, and the commit's
-//   memory traffic overlaps the walk.  A flush kernel ends the sweep.
-// Range slots rotate over 4: block q accumulates slot q%4, reads q-1 and q-2,
-// and re-arms slot (q+1)%4 for the next block.
+//   where block q-1 or q-2 touched a voxel (the only places where the two
+//   copies differ; a block touches voxels nearly all over the volume in
+//   angle-major scans, so the commit scans all of it: publishing the touched
+//   index range costs more, its atomics meet on two words) and clear
+//   PK[(q-2) % 3].  Nothing read in a launch is written in it, so no grid-wide
+//   synchronisation is needed, and the commit's memory traffic overlaps the
+//   walk.  A flush kernel ends the sweep.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float committed_value(float base, unsigned long long w)
 {
@@ -910,27 +569,23 @@ __device__ __forceinline__ float committed_value(float base, unsigned long long 
 }
 
 struct LazyX {
+    struct Raw {
+        float base;
+        unsigned long long pk;
+    };
     const float *__restrict__ base;
     const unsigned long long *__restrict__ pk;
-    __device__ __forceinline__ double operator()(int j) const { return double(committed_value(base[j], pk[j])); }
+    __device__ __forceinline__ Raw load(int j) const { return Raw{base[j], pk[j]}; }
+    __device__ __forceinline__ static double value(const Raw &v) { return double(committed_value(v.base, v.pk)); }
+    __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
 };
 
 __device__ __forceinline__ void commit_part(const float *__restrict__ base, float *__restrict__ next,
                                             const unsigned long long *__restrict__ pk_prev,
-                                            unsigned long long *__restrict__ pk_old, const int *r_prev,
-                                            const int *r_old, int *r_reset, int nvox, int wg, int n_wg,
-                                            int full = 0)
+                                            unsigned long long *__restrict__ pk_old, int nvox, int wg, int n_wg)
 {
-    // full: the whole volume instead of the published ranges
-    const int j0 = full ? 0 : min(r_prev[0], r_old[0]);
-    const int j1 = full ? nvox - 1 : max(r_prev[1], r_old[1]);
-    if (wg == 0 && threadIdx.x == 0) {
-        r_reset[0] = INT_MAX;
-        r_reset[1] = -1;
-    }
-    if (j1 < j0 || j0 < 0) return;
     const int stride = 4 * n_wg * int(blockDim.x);
-    for (int j = (j0 & ~3) + 4 * (wg * int(blockDim.x) + int(threadIdx.x)); j <= j1; j += stride) {
+    for (int j = 4 * (wg * int(blockDim.x) + int(threadIdx.x)); j < nvox; j += stride) {
         const ulonglong2 p01 = *reinterpret_cast<const ulonglong2 *>(pk_prev + j);
         const ulonglong2 p23 = *reinterpret_cast<const ulonglong2 *>(pk_prev + j + 2);
         const ulonglong2 o01 = *reinterpret_cast<const ulonglong2 *>(pk_old + j);
@@ -948,328 +603,38 @@ __device__ __forceinline__ void commit_part(const float *__restrict__ base, floa
 }
 
 constexpr int kCommitWG = 1024;  // commit workgroups (64 threads) per fused launch
-static_assert(kCommitWG % 8 == 0, "proton workgroups must start on XCD 0");
+static_assert(kCommitWG % 8 == 0, "row workgroups must start on XCD 0");
 
-// Four waves per SIMD (at most 128 VGPRs): the walk is latency-bound, and the
-// extra wave hides more latency than the few spilled registers cost.
-template <int CHORD, int LPP, bool HULL>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) k_drop_fused(ProtonsDev p, const float *__restrict__ b,
-                                                   const float *__restrict__ base, float *__restrict__ next,
-                                                   const unsigned long long *__restrict__ pk_prev,
-                                                   unsigned long long *pk_cur, unsigned long long *pk_old, int *r_cur,
-                                                   const int *r_prev, const int *r_old, int *r_reset,
-                                                   const PathSrc src,  GridDev g, int64_t lo,
-                                                   int64_t hi, double lambda, unsigned *status, int nvox,
-                                                   int full)
+template <int CHORD, bool HULL>
+__global__ void __launch_bounds__(kWave) k_drop_fused(ProtonsDev p, const float *__restrict__ b,
+                                                      const float *__restrict__ base, float *__restrict__ next,
+                                                      const unsigned long long *__restrict__ pk_prev,
+                                                      unsigned long long *pk_cur, unsigned long long *pk_old,
+                                                      const PathSrc src, GridDev g, int64_t lo, int64_t hi,
+                                                      double lambda, unsigned *status, int nvox, int span)
 {
     if (int(blockIdx.x) < kCommitWG) {
-        commit_part(base, next, pk_prev, pk_old, r_prev, r_old, r_reset, nvox, int(blockIdx.x), kCommitWG, full);
+        commit_part(base, next, pk_prev, pk_old, nvox, int(blockIdx.x), kCommitWG);
         return;
     }
-    using CT = float;
-    extern __shared__ double lds[];
-    constexpr int GPW = 64 / LPP;
-    const int lane = threadIdx.x;
-    const int grp = lane / LPP;
-    const int l = lane % LPP;
-    // XCD-aware placement: workgroup w runs on XCD w mod 8, so the proton
-    // workgroups are dealt to the eight XCDs in contiguous runs of the block
-    // (8 * per_xcd workgroups are launched; the padding ones idle).  With the
-    // block ordered by entry slice and lateral position, each XCD then walks
-    // a band of neighbouring paths and finds their voxels in its own L2.
-    const int wq = int(blockIdx.x) - kCommitWG;
-    const int64_t n_wg = (hi - lo + GPW - 1) / GPW;
-    const int64_t per_xcd = (n_wg + 7) / 8;
-    const int64_t wg = int64_t(wq % 8) * per_xcd + wq / 8;
-    const int64_t i = lo + wg * GPW + grp;
-    bool active = wg < n_wg && i < hi;
-    Rec r{};
-    double bi = 0.0;
-    if (active) {
-        r = load_rec(p, i);
-        bi = double(b[i]);
-        if (!rec_finite(r) || !isfinite(bi)) {
-            if (l == 0) raise_status(status, PCT_DEV_NONFINITE);
-            active = false;
-        }
-    }
-    if (!active) r.cs = 1.0, r.sn = 0.0;
-    double *P = lds + grp * 3 * src.nvmax;
-    char *stash = reinterpret_cast<char *>(lds + GPW * 3 * src.nvmax);
-    int *sj = reinterpret_cast<int *>(stash);
-    CT *sc = reinterpret_cast<CT *>(stash + size_t(64) * kStash * sizeof(int));
-    const GroupPath gp = stage_path<LPP, HULL>(r, src, g, P, l, active);
-
-    StashSink<CT, kStash> st{sj, sc, lane, {}, 0.0, 0};
-    st.re.init(r);
-    {
-        Merge<StashSink<CT, kStash>, CHORD> m(st, g);
-        walk_lane<LPP>(gp, l, g, P, m);
-        m.finish();
-    }
-    if (st.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-    const bool spill = st.count > kStash;
-    const int ns = min(st.count, kStash);
-    const LazyX xa{base, pk_prev};
-    double dot = 0.0;
-    if (!spill) {
-#pragma unroll 4
-        for (int q = 0; q < ns; ++q) {
-            const int j = sj[q * 64 + lane] & 0x7FFFFFFF;
-            dot += double(sc[q * 64 + lane]) * xa(j);
-        }
-    } else {
-        DotSink<float, LazyX> ds;
-        ds.x = xa;
-        ds.dot = 0.0;
-        ds.n2 = 0.0;
-        ds.re.init(r);
-        Merge<DotSink<float, LazyX>, CHORD> m(ds, g);
-        walk_lane<LPP>(gp, l, g, P, m);
-        m.finish();
-        dot = ds.dot;
-    }
-    dot = group_sum<LPP>(dot);
-    const double n2 = group_sum<LPP>(st.n2);
-    int jmin = INT_MAX, jmax = -1;
-    if (n2 > 0.0) {
-        const double rho = lambda * (bi - dot) / n2;
-        if (!spill) {
-            for (int q = 0; q < ns; ++q) {
-                const int e = sj[q * 64 + lane];
-                const int j = e & 0x7FFFFFFF;
-                atomicAdd(pk_cur + j, pack_contribution(rho * double(sc[q * 64 + lane]), e < 0, status));
-                jmin = min(jmin, j);
-                jmax = max(jmax, j);
-            }
-        } else {
-            DropScatterSink<float> sc2;
-            sc2.acc = pk_cur;
-            sc2.cnt = nullptr;
-            sc2.status = status;
-            sc2.rho = rho;
-            sc2.jmin = INT_MAX;
-            sc2.jmax = -1;
-            sc2.re.init(r);
-            Merge<DropScatterSink<float>, CHORD> m(sc2, g);
-            walk_lane<LPP>(gp, l, g, P, m);
-            m.finish();
-            jmin = sc2.jmin;
-            jmax = sc2.jmax;
-        }
-    }
-    if (!full) publish_range(jmin, jmax, r_cur);   // full is uniform over the launch
+    const int64_t i = row_of_workgroup(int(blockIdx.x) - kCommitWG, lo, hi);
+    if (i >= hi) return;
+    drop_row<float, CHORD, HULL>(p, b, LazyX{base, pk_prev}, pk_cur, nullptr, nullptr, src, g, i, span, lambda,
+                                 status);
 }
 
-// ---------------------------------------------------------------------------
-// Traced-ahead schedule (FP32, 64 lanes per proton).  The rows do not depend
-// on x, so launch q traces the rows of block q+1 while it runs the DROP
-// update of block q from the rows traced in launch q-1 (and commits block
-// q-1 as in k_drop_fused): the walk leaves the chain of dependent block
-// steps.  A row record holds the image of the lane stash (kStash entries x
-// 64 lanes, entry-major), the lane piece counts and ||a_i||^2; a lane whose
-// count exceeds kStash walks its slabs again in the DROP step, exactly as in
-// k_drop_fused, so both schedules give bitwise the same result.
-// ---------------------------------------------------------------------------
-struct SlotDev {
-    int *vox;      // [record][kStash][64]
-    float *chord;  // [record][kStash][64]
-    int *cnt;      // [record][64]
-    double *n2;    // [record]
-};
-
-static_assert(kSlotRecordBytes == size_t(kStash) * 64 * (sizeof(int) + sizeof(float)) + 64 * sizeof(int) +
-                                      sizeof(double),
-              "row record layout");
-
-__host__ __device__ inline SlotDev slot_at(char *base, int64_t records)
+// Start of a fused sweep: X1 = x.
+__global__ void __launch_bounds__(256) k_sweep_begin(const float *__restrict__ x, float *__restrict__ x1, int nvox)
 {
-    SlotDev d;
-    d.vox = reinterpret_cast<int *>(base);
-    d.chord = reinterpret_cast<float *>(base + size_t(records) * kStash * 64 * sizeof(int));
-    d.cnt = reinterpret_cast<int *>(base + size_t(records) * kStash * 64 * (sizeof(int) + sizeof(float)));
-    d.n2 = reinterpret_cast<double *>(base + size_t(records) * (kStash * 64 * (sizeof(int) + sizeof(float)) +
-                                                                64 * sizeof(int)));
-    return d;
+    for (int j = int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += int(gridDim.x * blockDim.x)) x1[j] = x[j];
 }
 
-// Trace of record r of the block [wlo, whi) into slot wr (one proton per
-// one-wave workgroup).
-template <int CHORD, bool HULL>
-__device__ __forceinline__ void trace_role(const ProtonsDev &p, const SlotDev &wr, const PathSrc src,
-                                            const GridDev &g, int64_t wlo, int64_t whi, int64_t r, double *P,
-                                           int *sj, float *sc, unsigned *status)
-{
-    const int lane = threadIdx.x;
-    const int64_t i = wlo + r;
-    if (i >= whi) return;  // uniform: one proton per workgroup
-    Rec rec = load_rec(p, i);
-    bool active = true;
-    if (!rec_finite(rec)) {
-        if (lane == 0) raise_status(status, PCT_DEV_NONFINITE);
-        active = false;
-        rec.cs = 1.0;
-        rec.sn = 0.0;
-    }
-    const GroupPath gp = stage_path<64, HULL>(rec, src, g, P, lane, active);
-    StashSink<float, kStash> st{sj, sc, lane, {}, 0.0, 0};
-    st.re.init(rec);
-    {
-        Merge<StashSink<float, kStash>, CHORD> m(st, g);
-        walk_lane<64>(gp, lane, g, P, m);
-        m.finish();
-    }
-    if (st.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-    const double n2 = group_sum<64>(st.n2);
-    const int ns = min(st.count, kStash);
-    for (int k = 0; k < ns; ++k) {
-        const int64_t q = (r * kStash + k) * 64 + lane;
-        wr.vox[q] = sj[k * 64 + lane];
-        wr.chord[q] = sc[k * 64 + lane];
-    }
-    wr.cnt[r * 64 + lane] = active ? st.count : 0;
-    if (lane == 0) wr.n2[r] = active ? n2 : 0.0;
-}
-
-template <int CHORD, bool HULL>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_drop_pipe(ProtonsDev p, const float *__restrict__ b, const float *__restrict__ base, float *__restrict__ next,
-            const unsigned long long *__restrict__ pk_prev, unsigned long long *pk_cur, unsigned long long *pk_old,
-            int *r_cur, const int *r_prev, const int *r_old, int *r_reset, SlotDev rd, SlotDev wr,
-            const PathSrc src,  GridDev g, int64_t lo, int64_t hi, int64_t wlo, int64_t whi,
-            int n_commit, double lambda, unsigned *status, int nvox, int full)
-{
-    const int bid = int(blockIdx.x);
-    if (bid < n_commit) {
-        commit_part(base, next, pk_prev, pk_old, r_prev, r_old, r_reset, nvox, bid, n_commit, full);
-        return;
-    }
-    extern __shared__ double lds[];
-    double *P = lds;
-    char *stash = reinterpret_cast<char *>(lds + 3 * src.nvmax);
-    int *sj = reinterpret_cast<int *>(stash);
-    float *sc = reinterpret_cast<float *>(stash + size_t(64) * kStash * sizeof(int));
-    const int lane = threadIdx.x;
-    // workgroups: [commit | trace of block q+1 | DROP step of block q]; the
-    // trace, the longer chain, is dispatched first
-    const int64_t n_d = hi - lo;
-    const int64_t per_xcd = (n_d + 7) / 8;
-    const int64_t n_w8 = 8 * ((whi - wlo + 7) / 8);  // keeps the DROP workgroups XCD-aligned
-    if (bid - n_commit < n_w8) {
-        trace_role<CHORD, HULL>(p, wr, src, g, wlo, whi, int64_t(bid - n_commit), P, sj, sc, status);
-        return;
-    }
-    const int wq = int(bid - n_commit - n_w8);
-    {
-        // ---- DROP step of block q from its traced rows (XCD-aware placement)
-        const int64_t r = int64_t(wq % 8) * per_xcd + wq / 8;
-        bool active = r < n_d;
-        const int64_t i = lo + r;
-        double bi = 0.0, n2 = 0.0;
-        int cnt = 0;
-        if (active) {
-            bi = double(b[i]);
-            n2 = rd.n2[r];
-            cnt = rd.cnt[r * 64 + lane];
-            if (!isfinite(bi)) {
-                if (lane == 0) raise_status(status, PCT_DEV_NONFINITE);
-                active = false;
-            }
-        }
-        const bool spill = cnt > kStash;
-        const bool any_spill = group_any<64>(spill);
-        const LazyX xa{base, pk_prev};
-        int jr[kStash];
-        float cr[kStash];
-        double dot = 0.0;
-#pragma unroll
-        for (int k = 0; k < kStash; ++k) {
-            jr[k] = 0;
-            cr[k] = 0.f;
-            if (!spill && k < cnt) {
-                const int64_t q = (r * kStash + k) * 64 + lane;
-                jr[k] = rd.vox[q];
-                cr[k] = rd.chord[q];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kStash; ++k)
-            if (!spill && k < cnt) dot += double(cr[k]) * xa(jr[k] & 0x7FFFFFFF);
-        Rec rec{};
-        GroupPath gp{};
-        if (any_spill) {
-            // lanes beyond the stash walk their slabs again (rare)
-            if (active) rec = load_rec(p, i);
-            if (!active) rec.cs = 1.0, rec.sn = 0.0;
-            gp = stage_path<64, HULL>(rec, src, g, P, lane, active);
-            if (spill) {
-                DotSink<float, LazyX> ds;
-                ds.x = xa;
-                ds.dot = 0.0;
-                ds.n2 = 0.0;
-                ds.re.init(rec);
-                Merge<DotSink<float, LazyX>, CHORD> m(ds, g);
-                walk_lane<64>(gp, lane, g, P, m);
-                m.finish();
-                dot = ds.dot;
-            }
-        }
-        dot = group_sum<64>(dot);
-        int jmin = INT_MAX, jmax = -1;
-        if (active && n2 > 0.0) {
-            const double rho = lambda * (bi - dot) / n2;
-            if (!spill) {
-#pragma unroll
-                for (int k = 0; k < kStash; ++k) {
-                    if (k < cnt) {
-                        const int e = jr[k];
-                        const int j = e & 0x7FFFFFFF;
-                        atomicAdd(pk_cur + j, pack_contribution(rho * double(cr[k]), e < 0, status));
-                        jmin = min(jmin, j);
-                        jmax = max(jmax, j);
-                    }
-                }
-            } else {
-                DropScatterSink<float> sc2;
-                sc2.acc = pk_cur;
-                sc2.cnt = nullptr;
-                sc2.status = status;
-                sc2.rho = rho;
-                sc2.jmin = INT_MAX;
-                sc2.jmax = -1;
-                sc2.re.init(rec);
-                Merge<DropScatterSink<float>, CHORD> m(sc2, g);
-                walk_lane<64>(gp, lane, g, P, m);
-                m.finish();
-                jmin = sc2.jmin;
-                jmax = sc2.jmax;
-            }
-        }
-        if (!full) publish_range(jmin, jmax, r_cur);   // full is uniform over the launch
-    }
-}
-
-// Start of a fused sweep: X1 = x, all range slots empty.
-__global__ void __launch_bounds__(256) k_sweep_begin(const float *__restrict__ x, float *__restrict__ x1, int *slots,
-                                                     int nvox)
-{
-    const int t = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (t < 8 && blockIdx.x == 0) slots[t] = (t & 1) ? -1 : INT_MAX;
-    for (int j = t; j < nvox; j += int(gridDim.x * blockDim.x)) x1[j] = x[j];
-}
-
-// End of a fused sweep of T blocks: x = X[T%2] + update of block T-1 over the
-// ranges of blocks T-1 and T-2; clears the accumulators of both.
+// End of a fused sweep of T blocks: x = X[T%2] + update of block T-1; clears
+// the accumulators of blocks T-1 and T-2.
 __global__ void __launch_bounds__(256) k_sweep_end(float *x, const float *src, unsigned long long *pk_last,
-                                                   unsigned long long *pk_prev, const int *r_last, const int *r_prev,
-                                                   int nvox, int full)
+                                                   unsigned long long *pk_prev, int nvox)
 {
-    // full: the whole volume instead of the published ranges
-    const int j0 = full ? 0 : min(r_last[0], r_prev[0]);
-    const int j1 = full ? nvox - 1 : max(r_last[1], r_prev[1]);
-    if (j1 < j0 || j0 < 0) return;
-    for (int j = j0 + int(blockIdx.x * blockDim.x + threadIdx.x); j <= j1 && j < nvox;
-         j += int(gridDim.x * blockDim.x)) {
+    for (int j = int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += int(gridDim.x * blockDim.x)) {
         const unsigned long long w = pk_last[j];
         x[j] = committed_value(src[j], w);
         if (w != 0ull) pk_last[j] = 0ull;
@@ -1281,25 +646,24 @@ __global__ void __launch_bounds__(256) k_sweep_end(float *x, const float *src, u
 // Binned FP32 schedule: the block's D-weighted back-projection is staged per
 // slab of the block's dominant axis and summed in LDS, one workgroup per slab.
 //
-// Launch 1 (k_drop_bin) runs the proton groups exactly as k_drop_fused does
-// (walk, a_i.x against the committed iterate, ||a_i||^2, rho_i), but each lane
-// stores its packed contributions (the same 64-bit word: row count bit plus
-// rho_i a_ij in fixed point) into the bin of the piece's slab,
-// bins[s][p][0..kBinCap), with the number of entries in cnt[s][p].  Lanes own
-// disjoint slab ranges, so every (slab, proton) bin has a single writer: plain
-// stores, no atomics.  Pieces without a bin (a proton whose dominant axis is
-// not the block's, a path that is not monotone along it, more than kBinCap
-// pieces of one row in one slab) go to a packed overflow accumulator with a
-// global atomic, and raise the block's overflow flag.
+// Launch 1 (k_drop_bin) goes over each row's pieces once.  The pieces of a row
+// in one slab follow each other, so piece k of (slab, row) has a bin entry of
+// its own: the chord (FP32), the voxel's cell in the slab, and whether another
+// entry follows, written with plain stores.  At the end the row's rho_i =
+// lambda (b_i - a_i.x) / ||a_i||^2 is stored.  Pieces without a bin (a row whose
+// dominant axis is not the block's, a path that turns back along it, more than
+// kBinCap pieces of one row in one slab) take a second pass, which adds rho_i
+// a_ij to a packed overflow accumulator with a global atomic and raises the
+// block's overflow flag.
 //
 // Launch 2 (k_slab_commit) gives each slab (and z chunk) of the block's axis
-// to one workgroup: it adds the slab's bin entries into a dense LDS window of
-// the slab (64-bit integer adds), adds the overflow words of the window when
-// the flag is up, and commits x_j = x_j + sum_j / s_j for every voxel of the
-// window the block touched.  The integer sums per voxel are the ones the
-// atomic schedules form, so without compensation the result is bitwise
-// theirs; slabs are disjoint, so the commit is a plain read-modify-write of x
-// over exactly the touched voxels.
+// to one workgroup: it adds rho_i a_ij of the slab's bin entries, packed with
+// the row count bit, into a dense LDS window of the slab (64-bit integer
+// adds), adds the overflow words of the window when the flag is up, and
+// commits x_j = x_j + sum_j / s_j for every voxel of the window the block
+// touched.  The integer sums per voxel are the ones the atomic schedules form,
+// so without compensation the result is bitwise theirs; slabs are disjoint, so
+// the commit is a plain read-modify-write of x over exactly the touched voxels.
 //
 // Compensation (default): the commit keeps the rounding error of the FP32
 // iterate in a second FP32 word per voxel (lo, zero at the start of a call),
@@ -1309,17 +673,48 @@ __global__ void __launch_bounds__(256) k_sweep_end(float *x, const float *src, u
 // ---------------------------------------------------------------------------
 constexpr int kSlabWG = 1024;  // threads of a slab-commit workgroup
 
-struct BinsDev {
-    unsigned long long *w;  // [slab][kBinCap][cap]: packed words, entry-major (a slab's first
-                            // entries are contiguous)
-    unsigned *j1;           // [slab][kBinCap - 1][cap]: voxel index of entries 1.. of each bin
-    unsigned *j0;           // [parity][slab][cap]: voxel index of entry 0 | (entries - 1) << 30,
-                            // kEmptyBin for a bin without entries
-    float *rowmax;          // [cap]: largest |rho_i a_ij| of each row of the block
-    int cap;                // rows per block the bins hold (a multiple of 16)
-    int nslab;              // max(nx, ny)
+// One bin entry: the voxel's cell in the slab (an index of the slab's (b, z)
+// plane, all ones: none) and the chord.  The first entry of a (slab, row) holds
+// the cell in its low cell_bits, the epoch of its block above them and the
+// number of entries less one in the top two bits; the others hold the cell in
+// 30 bits and whether the row meets the voxel for the first time in the top one.
+// Every block of a sweep has its own epoch, so an entry that an earlier block
+// left says so by itself and nothing is cleared between blocks (the commit
+// spent 3 us of its 27 on it at 256 slabs x 6400 rows); epochs start again at 1,
+// over cleared bins, when their bits run out.
+constexpr unsigned kFirstBit = 0x80000000u, kNoCell = 0x3FFFFFFFu;
+struct BinEntry {
+    unsigned cell;
+    float c;
 };
-constexpr unsigned kEmptyBin = 0xFFFFFFFFu;
+
+struct BinsDev {
+    BinEntry *e0;   // [slab][cap]: first entries
+    BinEntry *ek;   // [kBinCap - 1][slab][cap]: entries 1..
+    double *rho;    // [cap]: rho_i of each row of the block, kSkipRow for a skipped one
+    float *rowmax;  // [cap]: largest |rho_i a_ij| of each row of the block
+    int cap;        // rows per block the bins hold (a multiple of 16)
+    int nslab;      // max(nx, ny)
+    int cell_bits;
+    unsigned epoch;  // of the block
+    __device__ __forceinline__ unsigned no_cell() const { return (1u << cell_bits) - 1u; }
+};
+
+// Where the iterate lies while a binned call runs: the caller's x with the
+// compensation words beside it, or, packed, both in the workspace as (x, lo)
+// pairs with z fastest, so that a slab of either in-plane axis is made of runs
+// along z and a commit touches one line where it would touch one per voxel.
+// Strides are in voxels; a cell of a slab is its index along the other in-plane
+// axis times cb plus its index along z times cz.
+struct IterateDev {
+    float *x;    // x, or the pairs
+    float *lo;   // compensation words (not packed)
+    int packed;  // 0 or 1
+    int sx, sy, sz;
+    __device__ __forceinline__ int at(int ix, int iy, int iz) const { return ix * sx + iy * sy + iz * sz; }
+    __device__ __forceinline__ float value(int j) const { return x[size_t(j) << packed]; }
+};
+constexpr unsigned long long kSkipRow = 0x7FF8DEADDEADDEADull;  // a NaN no arithmetic forms
 
 // Dominant in-plane axis of the block, from its first record's gantry angle.
 // It only routes pieces (rows of the other axis go to the overflow words,
@@ -1344,188 +739,99 @@ __device__ __forceinline__ unsigned udiv_exact(unsigned j, unsigned d, double in
     return q;
 }
 
-// One lane's pieces, in walk order (slab by slab in the direction of travel),
-// into the bins of row p of the block.  A slab's first entry is held until the
-// lane leaves the slab, then stored with the bin's entry count in the top bits
-// of its voxel word; further entries are stored as they come.
-struct BinWriter {
-    BinsDev bins;
-    int par, axis, nx, ny;
-    int p;
-    bool direct;  // the row has no bins: every piece to the overflow accumulator
-    unsigned long long *ovf;
-    int *ovf_flag;
-    int cur, k;
-    unsigned long long w0;
-    unsigned j0;
-    double inv_nx, inv_ny;  // 1 / nx, 1 / ny
-
-    __device__ __forceinline__ void overflow(unsigned j, unsigned long long w)
-    {
-        atomicAdd(ovf + j, w);
-        *ovf_flag = 1;
-    }
-    __device__ __forceinline__ void flush()
-    {
-        if (cur >= 0) {
-            const size_t q = size_t(cur) * bins.cap + p;
-            bins.w[size_t(cur) * kBinCap * bins.cap + p] = w0;
-            bins.j0[size_t(par) * bins.nslab * bins.cap + q] = j0 | (unsigned(min(k, kBinCap) - 1) << 30);
-        }
-        cur = -1;
-    }
-    __device__ __forceinline__ void put(int jj, unsigned long long w)
-    {
-        const unsigned j = unsigned(jj);
-        if (direct) {
-            overflow(j, w);
-            return;
-        }
-        const unsigned row = udiv_exact(j, unsigned(nx), inv_nx);  // j / nx
-        const int s = axis == 0 ? int(j - row * unsigned(nx))
-                                : int(row - udiv_exact(row, unsigned(ny), inv_ny) * unsigned(ny));
-        if (s != cur) {
-            flush();
-            cur = s;
-            k = 0;
-        }
-        if (k == 0) {
-            w0 = w;
-            j0 = j;
-        } else if (k < kBinCap) {
-            bins.w[(size_t(s) * kBinCap + k) * bins.cap + p] = w;
-            bins.j1[(size_t(s) * (kBinCap - 1) + (k - 1)) * bins.cap + p] = j;
-        } else {
-            overflow(j, w);
-        }
-        ++k;
-    }
-};
-
-// Walk sink of a lane that re-walks its slabs (stash overflow): packed
-// contributions straight into the bins.
-struct BinScatterSink {
-    BinWriter *bw;
-    unsigned *status;
-    Reentry re;
-    double rho;
-    double cmax;  // largest |rho a_ij| of the lane's pieces
-    __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
-    __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
-    {
-        bool first;
-        re.visit(j, ix, iy, iz, c, first);
-        const double v = rho * c;
-        cmax = fmax(cmax, fabs(v));
-        bw->put(j, pack_contribution(v, first, status));
-    }
-};
-
-template <int CHORD, int LPP, bool HULL>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_drop_bin(ProtonsDev p, const float *__restrict__ b, const float *__restrict__ x, BinsDev bins, int par,
-           unsigned long long *ovf, int *ovf_flag, const PathSrc src, GridDev g, int64_t lo, int64_t hi,
-           double lambda, unsigned *status, const int *halt)
+// Bound by VALU issue: about 1600 instructions a row (records 270 per round of 64
+// segments, pieces 80 per round of 64 records, 250 to read the record and form
+// its frame), 17 us at 6400 rows, the rest latency at four waves a SIMD.  One
+// wave per row: 36.0 us for a 6400-row block of the 256 x 256 x 64 scan and 19.6
+// us for 3200 rows on 200 x 200 x 32, against 61.2 and 33.4 us with each lane
+// walking a run of slabs of its own (3700 instructions a row, the lanes' segments
+// clipped and set up one by one) and 45 us with the same lanes carrying their
+// voxel from segment to segment (1400, but a wave took every branch a lane did).
+// Registers stay at four waves a SIMD: held to five or six, spills cost more.
+template <int CHORD, bool HULL>
+__global__ void __launch_bounds__(kWave) k_drop_bin(ProtonsDev p, const float *__restrict__ b,
+                                                    IterateDev it, BinsDev bins,
+                                                    unsigned long long *ovf, int *ovf_flag, const PathSrc src,
+                                                    GridDev g, int64_t lo, int64_t hi, double lambda,
+                                                    unsigned *status, const int *halt, int span)
 {
     if (gate_closed(halt)) return;
-    // also writes bins.rowmax[i - lo]: the row's largest |rho_i a_ij| (0 for a skipped row)
-    using CT = float;
     extern __shared__ double lds[];
-    constexpr int GPW = 64 / LPP;
-    const int lane = threadIdx.x;
-    const int grp = lane / LPP;
-    const int l = lane % LPP;
-    // XCD-aware placement as in k_drop_fused: contiguous runs of the block per XCD
-    const int wq = int(blockIdx.x);
-    const int64_t n_wg = (hi - lo + GPW - 1) / GPW;
-    const int64_t per_xcd = (n_wg + 7) / 8;
-    const int64_t wg = int64_t(wq % 8) * per_xcd + wq / 8;
-    const int64_t i = lo + wg * GPW + grp;
-    bool active = wg < n_wg && i < hi;
-    Rec r{};
-    double bi = 0.0;
-    if (active) {
-        r = load_rec(p, i);
-        bi = double(b[i]);
-        if (!rec_finite(r) || !isfinite(bi)) {
-            if (l == 0) raise_status(status, PCT_DEV_NONFINITE);
-            active = false;
-        }
-    }
-    if (!active) r.cs = 1.0, r.sn = 0.0;
-    double *P = lds + grp * kStageDoubles<HULL> * src.nvmax;
-    char *stash = reinterpret_cast<char *>(lds + GPW * kStageDoubles<HULL> * src.nvmax);
-    int *sj = reinterpret_cast<int *>(stash);
-    CT *sc = reinterpret_cast<CT *>(stash + size_t(64) * kStash * sizeof(int));
-    const GroupPath gp = stage_group<LPP, HULL>(r, src, g, P, l, active);
-
-    StashSink<CT, kStash> st{sj, sc, lane, {}, 0.0, 0};
-    st.re.init(r);
-    {
-        Merge<StashSink<CT, kStash>, CHORD> m(st, g);
-        walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-        m.finish();
-    }
-    if (st.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-    const bool spill = st.count > kStash;
-    const int ns = min(st.count, kStash);
-    const PlainX<float> xa{x};
-    double dot = 0.0;
-    if (!spill) {
-#pragma unroll 4
-        for (int q = 0; q < ns; ++q) {
-            const int j = sj[q * 64 + lane] & 0x7FFFFFFF;
-            dot += double(sc[q * 64 + lane]) * xa(j);
-        }
-    } else {
-        DotSink<float> ds;
-        ds.x = xa;
-        ds.dot = 0.0;
-        ds.n2 = 0.0;
-        ds.re.init(r);
-        Merge<DotSink<float>, CHORD> m(ds, g);
-        walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-        m.finish();
-        dot = ds.dot;
-    }
-    dot = group_sum<LPP>(dot);
-    const double n2 = group_sum<LPP>(st.n2);
-    double cmax = 0.0;
-    if (n2 > 0.0) {
-        const double rho = lambda * (bi - dot) / n2;
-        const int axis = block_axis(p, lo);
-        BinWriter bw{bins,     par, axis, g.n[0], g.n[1], int(i - lo), gp.full || gp.dom != axis, ovf, ovf_flag, -1,
-                     0,        0ull, 0u,  g.inv_n[0], g.inv_n[1]};
-        if (!spill) {
-            for (int q = 0; q < ns; ++q) {
-                const int e = sj[q * 64 + lane];
-                const double v = rho * double(sc[q * 64 + lane]);
-                cmax = fmax(cmax, fabs(v));
-                bw.put(e & 0x7FFFFFFF, pack_contribution(v, e < 0, status));
+    const int64_t i = row_of_workgroup(int(blockIdx.x), lo, hi);
+    if (i >= hi) return;
+    const int lane = int(threadIdx.x), row = int(i - lo);
+    const Rec r = load_rec(p, i);
+    const double bi = double(b[i]);
+    const bool finite = rec_finite(r) && isfinite(bi);
+    double rho = 0.0, n2 = 0.0;
+    float cmax = 0.f;
+    if (finite) {
+        const RowPath<HULL> path(src, g, r);
+        const int dom = dominant_axis(r);
+        RecWindow win(lds, src.nvmax, span);
+        bool have = false, onward = true;
+        const bool binned = dom == block_axis(p, lo);
+        const unsigned cap = unsigned(bins.cap), slabs = unsigned(bins.nslab), own = unsigned(dom ? g.n[1] : g.n[0]);
+        const int cb = it.packed ? g.n[2] : 1, cz = it.packed ? 1 : dom ? g.n[0] : g.n[1];
+        const unsigned tag = bins.epoch << bins.cell_bits, none = bins.no_cell();
+        double d = 0.0, s = 0.0;
+        float cw = 0.f, xw = 0.f;  // chord and gather of the pass before, in flight
+        bool spilled = !binned;
+        row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+            const float cf = q.real ? float(q.c) : 0.f;
+            d = fma(double(cw), double(xw), d);
+            cw = cf;
+            xw = 0.f;
+            if (q.real) {
+                xw = it.value(it.at(q.ix, q.iy, q.iz));
+                s = fma(q.c, fma(2.0, q.before, q.c), s);
+                cmax = fmaxf(cmax, cf);
+                spilled |= q.k >= kBinCap;
             }
-        } else {
-            BinScatterSink ss{&bw, status, {}, rho, 0.0};
-            ss.re.init(r);
-            Merge<BinScatterSink, CHORD> m(ss, g);
-            walk_group_lane<LPP, HULL>(gp, l, g, P, r, src, m);
-            m.finish();
-            cmax = ss.cmax;
+            // a record that is no piece still takes its place among the entries
+            if (binned && onward && unsigned(q.k) < unsigned(kBinCap) && unsigned(q.slab) < own) {
+                const unsigned cell = unsigned((dom ? q.ix : q.iy) * cb + q.iz * cz);
+                const unsigned at = unsigned(q.slab) * cap + unsigned(row);
+                BinEntry *to = q.k == 0 ? bins.e0 + at : bins.ek + (unsigned(q.k - 1) * slabs * cap + at);
+                const unsigned word = q.k == 0 ? (q.real ? cell : none) | tag | unsigned(q.more) << 30
+                                               : (q.real ? cell : kNoCell) | (q.first ? kFirstBit : 0u);
+                *to = BinEntry{word, cf};
+            }
+        });
+        d = fma(double(cw), double(xw), d);
+        const double dot = wave_sum(d);
+        n2 = wave_sum(s);
+        if (!onward && lane == 0) raise_status(status, PCT_DEV_REENTRY);
+        rho = lambda * (bi - dot) / n2;
+        const bool direct = !binned || !onward;
+        if (n2 > 0.0 && (direct || __any(spilled))) {
+            row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+                if (q.real && (direct || q.k >= kBinCap))
+                    atomicAdd(ovf + it.at(q.ix, q.iy, q.iz),
+                              pack_contribution(rho * double(float(q.c)), q.first, status));
+            });
+            if (lane == 0) *ovf_flag = 1;
         }
-        bw.flush();
+    } else if (lane == 0) {
+        raise_status(status, PCT_DEV_NONFINITE);
     }
-    cmax = group_max<LPP>(cmax);
-    if (l == 0 && wg < n_wg && i < hi) bins.rowmax[i - lo] = float(cmax);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off, 64));
+    if (lane == 0) {
+        const bool skip = !(n2 > 0.0);
+        bins.rho[row] = skip ? __longlong_as_double(static_cast<long long>(kSkipRow)) : rho;
+        bins.rowmax[row] = skip ? 0.f : float(fabs(rho * double(cmax)));
+    }
 }
 
-// Start of a binned sweep: every bin of both parities empty and both overflow
-// flags zero.
-__global__ void __launch_bounds__(256) k_bins_begin(unsigned *j0, size_t n, int *ovf_flag)
+// Start of the epochs: no entry in any bin; at the start of a sweep (`flags`)
+// the overflow flags zero too.
+__global__ void __launch_bounds__(256) k_bins_begin(BinEntry *e0, size_t n, int *ovf_flag, int flags)
 {
     const size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < 2) ovf_flag[t] = 0;
-    uint4 *c4 = reinterpret_cast<uint4 *>(j0);
-    for (size_t q = t; q < n / 4; q += size_t(gridDim.x) * blockDim.x)
-        c4[q] = make_uint4(kEmptyBin, kEmptyBin, kEmptyBin, kEmptyBin);
+    if (flags && t < 2) ovf_flag[t] = 0;
+    uint4 *c4 = reinterpret_cast<uint4 *>(e0);
+    for (size_t q = t; q < n / 2; q += size_t(gridDim.x) * blockDim.x) c4[q] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ void __launch_bounds__(256) k_zero_f32(float *v, int64_t n)
@@ -1534,55 +840,59 @@ __global__ void __launch_bounds__(256) k_zero_f32(float *v, int64_t n)
         v[q] = 0.f;
 }
 
-// Commit of block [lo, lo + nb) of the binned schedule: workgroup
-// (slab s, z chunk zi) sums the slab's bins into its LDS window and commits
-// the touched voxels.  Workgroups of chunk 0 also empty the other parity's
-// bins of their slab (read by the previous block's commit) and clear the other
-// parity's overflow flag.  Thread t takes rows t, t + kSlabWG, ... of the
-// block: the first entries of its rows are read coalesced, all at once, then
-// the second entries of the rows that have them, then the rare rest; in the
-// commit it takes a fixed set of window cells whose x loads are issued before
-// any store.
-constexpr int kRowsPerThread = 8;   // rows of a block per slab-commit thread
-constexpr int kCommitCells = 16;    // window cells per thread and pass of the commit
-
-// Window cell of voxel j in the slab's z range [z0, z1), or -1.
-// Window cell of voxel j of slab s in the slab's z range [z0, z1), or -1.
-// Every entry of slab s's bins lies in slab s, so along x (axis 0)
-// j - s = nx (iy + ny iz) exactly and the cell iy + ny (iz - z0) is that
-// quotient less ny z0 (an exact FP64 quotient, rounded); along y (axis 1)
-// j - nx s = ix + nx ny iz and one exact integer division splits it.
-__device__ __forceinline__ int window_cell(unsigned j, int axis, int s, int nlat, int z0, int z1, unsigned nx,
-                                          unsigned nxy, double inv_nx, double inv_nxy)
+// Word j of an array below 4 GB, by a 32-bit byte offset.
+template <typename W>
+__device__ __forceinline__ W *word_at(float *base, unsigned j)
 {
-    int cell;
-    if (axis == 0) {
-        cell = int(rint(double(j - unsigned(s)) * inv_nx)) - nlat * z0;
-    } else {
-        const unsigned rr = j - nx * unsigned(s);
-        const unsigned iz = udiv_exact(rr, nxy, inv_nxy);
-        cell = int(rr - iz * nxy) + nlat * (int(iz) - z0);
-    }
-    return cell >= 0 && cell < nlat * (z1 - z0) ? cell : -1;
+    return reinterpret_cast<W *>(reinterpret_cast<char *>(base) + j * unsigned(sizeof(W)));
 }
 
-__device__ __forceinline__ void window_add(unsigned long long *win, int cell, unsigned long long w)
-{
-    if (cell >= 0) atomicAdd(&win[cell], w);
-}
+// Commit of block [lo, lo + nb) of the binned schedule: workgroup (slab s,
+// chunk) sums the slab's bins of a range of cells into its LDS window and
+// commits the touched voxels.  Thread t takes rows t, t + kSlabWG, ... of the
+// block: their first and second entries are read coalesced, all at once (a
+// second entry that was not written is ignored; waiting for the first ones to
+// ask for it costs a round trip), then the rare third and fourth ones.  For the
+// commit each wave lists the touched cells of its share of the window, so that
+// the quotients run with full lanes (a tenth of the cells is touched).
+// Bound by its chain of dependent round trips (entries, window, x): 17.0 us for a
+// 6400-row block on 256 slabs and 13.4 us for 3200 rows on 200, 4.7 us of it the
+// launch.  Cleared bins by parity, second entries asked for after the first ones
+// and quotients over all cells took 26.9 and 19.6 us.
+constexpr int kRowsPerThread = 8;  // rows of a block per slab-commit thread
+constexpr int kListCells = 8;      // window cells per lane and list
+constexpr int kListBatch = 4;      // listed cells per lane whose x loads are in flight together
+constexpr size_t kListBytes = size_t(kSlabWG) * kListCells * sizeof(unsigned short);
+static_assert(kWinWords <= 65536, "listed cells are 16-bit");
 
+template <bool PACKED>
 __device__ __forceinline__ void slab_commit_body(const ProtonsDev &p, int64_t lo, int nb, const BinsDev &bins,
                                                  int par, unsigned long long *ovf, int *ovf_flag,
-                                                 float *__restrict__ x, float *__restrict__ xlo, const GridDev &g,
-                                                 int zc, int nzc, int comp, unsigned *status)
+                                                 const IterateDev &it, const GridDev &g, int chunk, int chunks,
+                                                 int comp, unsigned *status)
 {
     extern __shared__ unsigned long long win[];
     const int tid = int(threadIdx.x);
-    const int s = int(blockIdx.x) / nzc, zi = int(blockIdx.x) % nzc;
-    if (zi == 0) {
-        uint4 *c2 = reinterpret_cast<uint4 *>(bins.j0 + (size_t(1 - par) * bins.nslab + s) * bins.cap);
-        for (int q = tid; q < bins.cap / 4; q += kSlabWG) c2[q] = make_uint4(kEmptyBin, kEmptyBin, kEmptyBin, kEmptyBin);
-        if (s == 0 && tid == 0) ovf_flag[1 - par] = 0;
+    const int s = int(blockIdx.x) / chunks, part = int(blockIdx.x) % chunks;
+    const int axis = block_axis(p, lo);
+    const int nlat = g.n[1 - axis], cells = nlat * g.n[2];
+    const int c0 = part * chunk, nw = min(chunk, cells - c0);
+    if (blockIdx.x == 0 && tid == 0) ovf_flag[1 - par] = 0;
+    const bool work = s < g.n[axis] && nw > 0;
+    BinEntry er[kRowsPerThread], es[kRowsPerThread];
+    double rr[kRowsPerThread];
+    const size_t rank = size_t(bins.nslab) * bins.cap;
+    const BinEntry *e0 = bins.e0 + size_t(s) * bins.cap, *ek = bins.ek + size_t(s) * bins.cap;
+#pragma unroll
+    for (int m = 0; m < kRowsPerThread; ++m) {
+        const int r = tid + m * kSlabWG;
+        er[m] = es[m] = BinEntry{0u, 0.f};
+        rr[m] = 0.0;
+        if (work && r < nb) {
+            er[m] = e0[r];
+            es[m] = ek[r];
+            rr[m] = bins.rho[r];
+        }
     }
     if (blockIdx.x == 0) {
         // every voxel's block sum is bounded by the sum over the rows of their
@@ -1600,148 +910,195 @@ __device__ __forceinline__ void slab_commit_body(const ProtonsDev &p, int64_t lo
             if (!(tot < kSumMax)) atomicOr(status, PCT_DEV_ACC_RANGE);
         }
     }
-    const int axis = block_axis(p, lo);
-    if (s >= g.n[axis]) return;
-    const int nlat = g.n[1 - axis];
-    const int z0 = zi * zc, z1 = min(g.n[2], z0 + zc);
-    if (z0 >= z1) return;
-    const int nw = nlat * (z1 - z0);
-    const unsigned *j0 = bins.j0 + (size_t(par) * bins.nslab + s) * bins.cap;
-    const unsigned long long *w = bins.w + size_t(s) * kBinCap * bins.cap;
-    const unsigned *j1 = bins.j1 + size_t(s) * (kBinCap - 1) * bins.cap;
-    const int cap = bins.cap;
-    const unsigned nx = unsigned(g.n[0]), nxy = unsigned(g.n[0]) * unsigned(g.n[1]);
-    const double inv_nx = g.inv_n[0], inv_nxy = g.inv_nxy;
-    unsigned jr[kRowsPerThread];
-    unsigned long long wr[kRowsPerThread];
-#pragma unroll
-    for (int m = 0; m < kRowsPerThread; ++m) {
-        const int r = tid + m * kSlabWG;
-        jr[m] = kEmptyBin;
-        wr[m] = 0ull;
-        if (r < nb) {
-            jr[m] = j0[r];
-            wr[m] = w[r];
-        }
-    }
-    // the further entries of the rows with two or more (one batch of loads)
-    unsigned jb[kRowsPerThread][kBinCap - 1];
-    unsigned long long wb[kRowsPerThread][kBinCap - 1];
-#pragma unroll
-    for (int m = 0; m < kRowsPerThread; ++m) {
-        const int r = tid + m * kSlabWG;
-#pragma unroll
-        for (int k = 1; k < kBinCap; ++k) {
-            jb[m][k - 1] = kEmptyBin;
-            wb[m][k - 1] = 0ull;
-            if (jr[m] != kEmptyBin && (jr[m] >> 30) >= unsigned(k)) {
-                jb[m][k - 1] = j1[size_t(k - 1) * cap + r];
-                wb[m][k - 1] = w[size_t(k) * cap + r];
-            }
-        }
-    }
+    if (!work) return;
+    // entries of the row less one; -1 for a row without any in this block
+    auto more_of = [&](int m) {
+        const bool none = ((er[m].cell & kNoCell) >> bins.cell_bits) != bins.epoch ||
+                          static_cast<unsigned long long>(__double_as_longlong(rr[m])) == kSkipRow;
+        return none ? -1 : int(er[m].cell >> 30);
+    };
     // the window is cleared while the entries are in flight
     for (int q = tid; q < nw; q += kSlabWG) win[q] = 0ull;
     __syncthreads();
+    auto add = [&](unsigned cell, float c, double rho, bool first) {
+        const int q = int(cell) - c0;
+        if (unsigned(q) < unsigned(nw)) atomicAdd(&win[q], pack_contribution(rho * double(c), first, status));
+    };
+    const unsigned none = bins.no_cell();
+    static_assert(kBinCap == 4, "third and fourth entries below");
+    constexpr int kHalf = kRowsPerThread / 2;
 #pragma unroll
-    for (int m = 0; m < kRowsPerThread; ++m) {
-        if (jr[m] == kEmptyBin) continue;
-        const int c = int(jr[m] >> 30) + 1;
-        window_add(win, window_cell(jr[m] & 0x3FFFFFFFu, axis, s, nlat, z0, z1, nx, nxy, inv_nx, inv_nxy), wr[m]);
+    for (int h = 0; h < kRowsPerThread; h += kHalf) {
+        if (h * kSlabWG >= nb) break;
+        BinEntry e2[kHalf], e3[kHalf];
 #pragma unroll
-        for (int k = 1; k < kBinCap; ++k)
-            if (k < c)
-                window_add(win, window_cell(jb[m][k - 1], axis, s, nlat, z0, z1, nx, nxy, inv_nx, inv_nxy),
-                           wb[m][k - 1]);
+        for (int m = 0; m < kHalf; ++m) {
+            const int more = more_of(h + m);
+            e2[m] = e3[m] = BinEntry{kNoCell, 0.f};
+            if (more >= 2) e2[m] = ek[rank + (tid + (h + m) * kSlabWG)];
+            if (more >= 3) e3[m] = ek[2 * rank + (tid + (h + m) * kSlabWG)];
+        }
+#pragma unroll
+        for (int m = h; m < h + kHalf; ++m) {
+            const int more = more_of(m);
+            const unsigned cell = er[m].cell & none;
+            if (more >= 0 && cell != none) add(cell, er[m].c, rr[m], true);
+            if (more >= 1 && (es[m].cell & kNoCell) != kNoCell)
+                add(es[m].cell & kNoCell, es[m].c, rr[m], (es[m].cell & kFirstBit) != 0u);
+            __builtin_amdgcn_sched_barrier(0);  // (the adds kept apart: together they take hundreds of registers)
+        }
+#pragma unroll
+        for (int m = 0; m < kHalf; ++m) {
+            if ((e2[m].cell & kNoCell) != kNoCell)
+                add(e2[m].cell & kNoCell, e2[m].c, rr[h + m], (e2[m].cell & kFirstBit) != 0u);
+            if ((e3[m].cell & kNoCell) != kNoCell)
+                add(e3[m].cell & kNoCell, e3[m].c, rr[h + m], (e3[m].cell & kFirstBit) != 0u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     const bool of = ovf_flag[par] != 0;
     __syncthreads();
-    const double inv_nlat = g.inv_n[1 - axis];
-    for (int q0 = 0; q0 < nw; q0 += kCommitCells * kSlabWG) {
-        int jv[kCommitCells];
-        unsigned long long wv[kCommitCells];
-        float xv[kCommitCells], lv[kCommitCells];
+    // cell = outer * inner + rest
+    const unsigned inner = unsigned(PACKED ? g.n[2] : nlat);
+    const double inv_inner = PACKED ? g.inv_n[2] : g.inv_n[1 - axis];
+    const int sb = axis == 0 ? it.sy : it.sx, base = s * (axis == 0 ? it.sx : it.sy);
+    const unsigned s_outer = unsigned(PACKED ? sb : it.sz), s_inner = unsigned(PACKED ? it.sz : sb);
+    auto voxel = [&](int q) {
+        const unsigned cell = unsigned(c0 + q), outer = udiv_exact(cell, inner, inv_inner);
+        return unsigned(base) + outer * s_outer + (cell - outer * inner) * s_inner;
+    };
+    const int lane = tid & 63;
+    unsigned short *list = reinterpret_cast<unsigned short *>(win + chunk) + (tid >> 6) * (64 * kListCells);
+    for (int q0 = 0; q0 < nw; q0 += kListCells * kSlabWG) {
+        int listed = 0;
 #pragma unroll
-        for (int u = 0; u < kCommitCells; ++u) {
+        for (int u = 0; u < kListCells; ++u) {
             const int q = q0 + tid + u * kSlabWG;
-            jv[u] = -1;
-            wv[u] = 0ull;
-            if (q < nw) {
-                const unsigned zq = udiv_exact(unsigned(q), unsigned(nlat), inv_nlat);
-                const int a = q - int(zq) * nlat, zz = z0 + int(zq);
-                const int ix = axis == 0 ? s : a, iy = axis == 0 ? a : s;
-                jv[u] = ix + g.n[0] * (iy + g.n[1] * zz);
-                wv[u] = win[q];
+            unsigned long long w = q < nw ? win[q] : 0ull;
+            if (of && q < nw) {
+                const unsigned j = voxel(q);
+                const unsigned long long o = ovf[j];
+                if (o != 0ull) {
+                    w += o;
+                    win[q] = w;
+                    ovf[j] = 0ull;
+                }
             }
+            const unsigned long long mask = __ballot(w != 0ull);
+            if (w != 0ull) list[listed + __popcll(mask & ((1ull << lane) - 1ull))] = static_cast<unsigned short>(q);
+            listed += __popcll(mask);
         }
-        if (of) {
+        for (int i0 = 0; i0 < listed; i0 += 64 * kListBatch) {
+            unsigned jv[kListBatch];
+            unsigned long long wv[kListBatch];
+            float xv[kListBatch], lv[kListBatch];
 #pragma unroll
-            for (int u = 0; u < kCommitCells; ++u) {
-                if (jv[u] >= 0) {
-                    const unsigned long long o = ovf[jv[u]];
-                    if (o != 0ull) {
-                        wv[u] += o;
-                        ovf[jv[u]] = 0ull;
+            for (int u = 0; u < kListBatch; ++u) {
+                const int i = i0 + u * 64 + lane;
+                wv[u] = 0ull;
+                jv[u] = 0u;
+                xv[u] = lv[u] = 0.f;
+                if (i < listed) {
+                    const int q = list[i];
+                    wv[u] = win[q];
+                    jv[u] = voxel(q);
+                    if constexpr (PACKED) {
+                        const float2 v = *word_at<float2>(it.x, jv[u]);
+                        xv[u] = v.x;
+                        lv[u] = v.y;
+                    } else {
+                        xv[u] = *word_at<float>(it.x, jv[u]);
+                        if (comp) lv[u] = *word_at<float>(it.lo, jv[u]);
                     }
                 }
             }
-        }
 #pragma unroll
-        for (int u = 0; u < kCommitCells; ++u) {
-            xv[u] = 0.f;
-            lv[u] = 0.f;
-            if (wv[u] != 0ull) {
-                xv[u] = x[jv[u]];
-                if (comp) lv[u] = xlo[jv[u]];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kCommitCells; ++u) {
-            if (wv[u] == 0ull) continue;
-            if (comp) {
-                int c;
-                double sum;
-                unpack_accumulator(wv[u], c, sum);
-                const double v = double(xv[u]) + double(lv[u]) + sum / double(c);
-                const float h = float(v);
-                x[jv[u]] = h;
-                xlo[jv[u]] = float(v - double(h));
-            } else {
-                x[jv[u]] = committed_value(xv[u], wv[u]);
+            for (int u = 0; u < kListBatch; ++u) {
+                if (i0 + u * 64 + lane >= listed) continue;
+                if (comp) {
+                    int c;
+                    double sum;
+                    unpack_accumulator(wv[u], c, sum);
+                    const double v = double(xv[u]) + double(lv[u]) + sum / double(c);
+                    const float h = float(v), l = float(v - double(h));
+                    if constexpr (PACKED) {
+                        *word_at<float2>(it.x, jv[u]) = make_float2(h, l);
+                    } else {
+                        *word_at<float>(it.x, jv[u]) = h;
+                        *word_at<float>(it.lo, jv[u]) = l;
+                    }
+                } else if constexpr (PACKED) {
+                    *word_at<float2>(it.x, jv[u]) = make_float2(committed_value(xv[u], wv[u]), 0.f);
+                } else {
+                    *word_at<float>(it.x, jv[u]) = committed_value(xv[u], wv[u]);
+                }
             }
         }
     }
 }
 
+template <bool PACKED>
 __global__ void __launch_bounds__(kSlabWG) k_slab_commit(ProtonsDev p, int64_t lo, int nb, BinsDev bins, int par,
-                                                         unsigned long long *ovf, int *ovf_flag,
-                                                         float *__restrict__ x, float *__restrict__ xlo, GridDev g,
-                                                         int zc, int nzc, int comp, unsigned *status, GateDev gt)
+                                                         unsigned long long *ovf, int *ovf_flag, IterateDev it,
+                                                         GridDev g, int chunk, int chunks, int comp, unsigned *status,
+                                                         GateDev gt)
 {
     if (gate_closed(gt.halt)) return;
-    slab_commit_body(p, lo, nb, bins, par, ovf, ovf_flag, x, xlo, g, zc, nzc, comp, status);
+    slab_commit_body<PACKED>(p, lo, nb, bins, par, ovf, ovf_flag, it, g, chunk, chunks, comp, status);
     gate_commit_end(gt);
 }
 
-// Commit of one block: a dense, coalesced scan of the block's touched index
-// range; voxels with a non-zero row count get x_j += acc_j / s_j and are reset.
-// Also re-arms the range words of the next block.
-template <typename T>
-__device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt, const int *range_this,
-                                                 int *range_next, long long *acc_lo)
+// Copies of the iterate between the caller's order (x fastest) and (x, lo) pairs
+// with z fastest, through a tile of kTile x kTile voxels of one (x, z) plane.
+constexpr int kTile = 32;
+
+__global__ void __launch_bounds__(256) k_pack_iterate(const float *__restrict__ x, float2 *__restrict__ pairs,
+                                                      GridDev g)
 {
-    const int j0 = range_this[0], j1 = range_this[1];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        range_next[0] = INT_MAX;
-        range_next[1] = -1;
+    __shared__ float tile[kTile][kTile + 1];
+    const int tx = int(threadIdx.x) % kTile, ty = int(threadIdx.x) / kTile;
+    const int x0 = int(blockIdx.x) * kTile, z0 = int(blockIdx.z) * kTile;
+    for (int iy = int(blockIdx.y); iy < g.n[1]; iy += int(gridDim.y)) {
+        for (int q = ty; q < kTile; q += 8)
+            if (x0 + tx < g.n[0] && z0 + q < g.n[2])
+                tile[q][tx] = x[x0 + tx + int64_t(g.n[0]) * (iy + int64_t(g.n[1]) * (z0 + q))];
+        __syncthreads();
+        for (int q = ty; q < kTile; q += 8)
+            if (x0 + q < g.n[0] && z0 + tx < g.n[2])
+                pairs[(int64_t(iy) * g.n[0] + x0 + q) * g.n[2] + z0 + tx] = make_float2(tile[tx][q], 0.f);
+        __syncthreads();
     }
-    if (j1 < j0 || j0 < 0) return;  // nothing touched
+}
+
+__global__ void __launch_bounds__(256) k_unpack_iterate(float *__restrict__ x, const float2 *__restrict__ pairs,
+                                                        GridDev g)
+{
+    __shared__ float tile[kTile][kTile + 1];
+    const int tx = int(threadIdx.x) % kTile, ty = int(threadIdx.x) / kTile;
+    const int x0 = int(blockIdx.x) * kTile, z0 = int(blockIdx.z) * kTile;
+    for (int iy = int(blockIdx.y); iy < g.n[1]; iy += int(gridDim.y)) {
+        for (int q = ty; q < kTile; q += 8)
+            if (x0 + q < g.n[0] && z0 + tx < g.n[2])
+                tile[q][tx] = pairs[(int64_t(iy) * g.n[0] + x0 + q) * g.n[2] + z0 + tx].x;
+        __syncthreads();
+        for (int q = ty; q < kTile; q += 8)
+            if (x0 + tx < g.n[0] && z0 + q < g.n[2])
+                x[x0 + tx + int64_t(g.n[0]) * (iy + int64_t(g.n[1]) * (z0 + q))] = tile[tx][q];
+        __syncthreads();
+    }
+}
+
+// Commit of one block: a dense, coalesced scan of the volume; voxels with a
+// non-zero row count get x_j += acc_j / s_j and are reset.
+template <typename T>
+__device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt, int nvox, long long *acc_lo)
+{
     const int stride = int(gridDim.x * blockDim.x);
     if constexpr (sizeof(T) == 4) {
         // four 64-bit words per thread (the accumulator has 4 words of padding
         // past the last voxel; untouched words are zero)
         unsigned long long *pk = static_cast<unsigned long long *>(accv);
-        for (int j = (j0 & ~3) + 4 * int(blockIdx.x * blockDim.x + threadIdx.x); j <= j1; j += 4 * stride) {
+        for (int j = 4 * int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += 4 * stride) {
             const ulonglong2 w01 = *reinterpret_cast<const ulonglong2 *>(pk + j);
             const ulonglong2 w23 = *reinterpret_cast<const ulonglong2 *>(pk + j + 2);
             const unsigned long long w[4] = {w01.x, w01.y, w23.x, w23.y};
@@ -1758,7 +1115,7 @@ __device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt,
         }
         return;
     }
-    for (int j = j0 + int(blockIdx.x * blockDim.x + threadIdx.x); j <= j1; j += stride) {
+    for (int j = int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += stride) {
         {
             const int c = cnt[j];
             if (c != 0) {
@@ -1779,22 +1136,12 @@ __device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt,
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kWG) k_drop_commit(T *x, void *accv, int32_t *cnt, const int *range_this,
-                                                     int *range_next, long long *acc_lo, GateDev gt)
+__global__ void __launch_bounds__(kWG) k_drop_commit(T *x, void *accv, int32_t *cnt, int nvox, long long *acc_lo,
+                                                     GateDev gt)
 {
     if (gate_closed(gt.halt)) return;
-    drop_commit_body<T>(x, accv, cnt, range_this, range_next, acc_lo);
+    drop_commit_body<T>(x, accv, cnt, nvox, acc_lo);
     gate_commit_end(gt);
-}
-
-__global__ void k_reset_ranges(int *hdr)
-{
-    if (threadIdx.x == 0) {
-        hdr[kHdrRange0] = INT_MAX;
-        hdr[kHdrRange0 + 1] = -1;
-        hdr[kHdrRange1] = INT_MAX;
-        hdr[kHdrRange1 + 1] = -1;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2150,12 +1497,11 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
                                                         const float *__restrict__ base, float *__restrict__ next,
                                                         const unsigned long long *__restrict__ pk_prev,
                                                         unsigned long long *pk_cur, unsigned long long *pk_old,
-                                                        int *r_cur, const int *r_prev, const int *r_old,
-                                                        int *r_reset, int64_t lo, int64_t hi, double lambda,
+                                                        int64_t lo, int64_t hi, double lambda,
                                                         unsigned *status, int nvox)
 {
     if (int(blockIdx.x) < kCommitWG) {
-        commit_part(base, next, pk_prev, pk_old, r_prev, r_old, r_reset, nvox, int(blockIdx.x), kCommitWG);
+        commit_part(base, next, pk_prev, pk_old, nvox, int(blockIdx.x), kCommitWG);
         return;
     }
     using S = StoredChord<CT>;
@@ -2212,7 +1558,6 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
     }
     if (bad) raise_status(status, PCT_DEV_BAD_ROW);
     dot = group_sum<LPR>(dot);
-    int jmin = INT_MAX, jmax = -1;
     if (active && n2 > 0.0) {
         const double rho = lambda * (bi - dot) / n2;
 #pragma unroll
@@ -2220,8 +1565,6 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
             if (a + l + int64_t(k) * LPR < e) {
                 const int j = jr[k] & 0x7FFFFFFF;
                 atomicAdd(pk_cur + j, pack_contribution(rho * double(cr[k]), jr[k] < 0, status));
-                jmin = min(jmin, j);
-                jmax = max(jmax, j);
             }
         }
         for (int64_t q = a + l + int64_t(kRowRegs) * LPR; q < e; q += LPR) {
@@ -2229,11 +1572,8 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
             const int j = v & 0x7FFFFFFF;
             if (j >= nvox) continue;
             atomicAdd(pk_cur + j, pack_contribution(rho * double(S::get(chord[q])), v < 0, status));
-            jmin = min(jmin, j);
-            jmax = max(jmax, j);
         }
     }
-    publish_range(jmin, jmax, r_cur);
 }
 
 // ---------------------------------------------------------------------------
@@ -2519,138 +1859,44 @@ void profile_release(pct_plan &pl)
     }
 }
 
-// Launch of one block's fused kernel with the chosen lanes per proton.
-template <typename T, int CHORD, bool HULL>
-static void launch_block(int lanes, hipStream_t s, const ProtonsDev &p, const float *b, T *x, void *acc, int32_t *cnt,
-                         int *range, const PathSrc &src, const GridDev &g, int64_t lo, int64_t hi,
-                         double lambda, unsigned *status, long long *acc_lo, const int *halt)
-{
-    const int64_t n = hi - lo;
-    switch (lanes) {
-#define PCT_LAUNCH_LPP(LPP)                                                                                      \
-    case LPP: {                                                                                                  \
-        if constexpr (!HULL || LPP == 64) {                                                                      \
-            const unsigned grid = unsigned((n + (64 / LPP) - 1) / (64 / LPP));                                \
-            const size_t lds = size_t(64 / LPP) * kStageDoubles<HULL> * size_t(src.nvmax) * sizeof(double) + stash_bytes<T>(); \
-            hipLaunchKernelGGL((k_drop_block<T, CHORD, LPP, HULL>), dim3(grid), dim3(64), lds, s, p, b, x, acc, \
-                               cnt, range, src, g, lo, hi, lambda, status, acc_lo, halt);                       \
-        }                                                                                                        \
-        break;                                                                                                   \
-    }
-        PCT_LAUNCH_LPP(8)
-        PCT_LAUNCH_LPP(16)
-        PCT_LAUNCH_LPP(32)
-        PCT_LAUNCH_LPP(64)
-#undef PCT_LAUNCH_LPP
-    default:
-        hipLaunchKernelGGL((k_drop_rows<T, CHORD, HULL>), dim3(grid_for(n)), dim3(kWG), 0, s, p, b, x, acc, cnt,
-                           range, src, g, lo, hi, lambda, status, acc_lo, halt);
-    }
-}
-
-// Launch q of a fused FP32 sweep (see k_drop_fused): commit workgroups first,
-// then the proton workgroups of block [lo, hi).
-template <int CHORD, bool HULL>
-static void launch_fused(int lanes, hipStream_t s, const ProtonsDev &p, const float *b, const float *base,
-                         float *next, const unsigned long long *pk_prev, unsigned long long *pk_cur,
-                         unsigned long long *pk_old, int *r_cur, const int *r_prev, const int *r_old, int *r_reset,
-                         const PathSrc &src, const GridDev &g, int64_t lo, int64_t hi, double lambda,
-                         unsigned *status, int nvox, int full)
-{
-    const int64_t n = hi - lo;
-    switch (lanes) {
-#define PCT_LAUNCH_FUSED(LPP)                                                                                    \
-    case LPP: {                                                                                                  \
-        if constexpr (!HULL || LPP == 64) {                                                                      \
-            const int64_t n_wg = (n + (64 / LPP) - 1) / (64 / LPP);                                          \
-            const unsigned grid = unsigned(kCommitWG + 8 * ((n_wg + 7) / 8));                                \
-            const size_t lds = size_t(64 / LPP) * 3 * size_t(src.nvmax) * sizeof(double) + stash_bytes<float>(); \
-            hipLaunchKernelGGL((k_drop_fused<CHORD, LPP, HULL>), dim3(grid), dim3(64), lds, s, p, b, base, next, \
-                               pk_prev, pk_cur, pk_old, r_cur, r_prev, r_old, r_reset, src, g, lo, hi, lambda,  \
-                               status, nvox, full);                                                              \
-        }                                                                                                        \
-        break;                                                                                                   \
-    }
-        PCT_LAUNCH_FUSED(8)
-        PCT_LAUNCH_FUSED(16)
-        PCT_LAUNCH_FUSED(32)
-        PCT_LAUNCH_FUSED(64)
-#undef PCT_LAUNCH_FUSED
-    default: break;
-    }
-}
-
 static_assert(kRowsPerThread * kSlabWG >= kBinMaxRows, "slab commit covers the largest binned block");
 
-// Packed words of a slab-commit window: 128 KB of LDS once the kernel is
-// allowed that much dynamic LDS, else 64 KB.
+// Packed words of a slab-commit window: 128 KB of LDS (and 16 KB of lists) once
+// the kernel is allowed that much dynamic LDS, else 40 KB.
 static int slab_window_words()
 {
     static const int words = [] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_slab_commit),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 int(kWinWords * sizeof(unsigned long long)));
+        hipError_t e = hipSuccess;
+        for (const void *f : {reinterpret_cast<const void *>(&k_slab_commit<false>),
+                              reinterpret_cast<const void *>(&k_slab_commit<true>)})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        int(kWinWords * sizeof(unsigned long long) + kListBytes));
         (void)hipGetLastError();
-        return e == hipSuccess ? kWinWords : kWinWords / 2;
+        return e == hipSuccess ? kWinWords : kWinWords * 5 / 16;
     }();
     return words;
 }
 
-// Launch of block [lo, hi) of the binned schedule (see k_drop_bin).
-// With ev0/ev1 the launch records its own start and end in those events
-// (profiling: no extra stream packets around the kernel).
-template <int CHORD, bool HULL>
-static void launch_bin(int lanes, hipStream_t s, const ProtonsDev &p, const float *b, const float *x,
-                       const BinsDev &bins, int par, unsigned long long *ovf, int *ovf_flag, const PathSrc &src,
-                       const GridDev &g, int64_t lo, int64_t hi, double lambda, unsigned *status,
-                       const int *halt, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr)
+// Workgroups of a block kernel over n rows: a multiple of eight (see
+// row_of_workgroup).
+static inline unsigned row_grid(int64_t n) { return unsigned(8 * ((n + 7) / 8)); }
+
+// Records of a row's window: enough for a path across the grid at 45 degrees,
+// with room for what it does outside and for its slope along z, in at most 64
+// KB of LDS (a row with more takes several windows).
+static int record_span(const pct_plan &pl)
 {
-    const int64_t n = hi - lo;
-    switch (lanes) {
-#define PCT_LAUNCH_BIN(LPP)                                                                                      \
-    case LPP: {                                                                                                  \
-        if constexpr (!HULL || LPP == 64) {                                                                      \
-            const int64_t n_wg = (n + (64 / LPP) - 1) / (64 / LPP);                                          \
-            const unsigned grid = unsigned(8 * ((n_wg + 7) / 8));                                            \
-            const size_t lds = size_t(64 / LPP) * kStageDoubles<HULL> * size_t(src.nvmax) * sizeof(double) + \
-                               stash_bytes<float>();                                                      \
-            if (ev0)                                                                                             \
-                hipExtLaunchKernelGGL((k_drop_bin<CHORD, LPP, HULL>), dim3(grid), dim3(64), uint32_t(lds), s, ev0, \
-                                      ev1, 0u, p, b, x, bins, par, ovf, ovf_flag, src, g, lo, hi, lambda, status, \
-                                      halt);                                                                     \
-            else                                                                                                 \
-                hipLaunchKernelGGL((k_drop_bin<CHORD, LPP, HULL>), dim3(grid), dim3(64), lds, s, p, b, x, bins,  \
-                                   par, ovf, ovf_flag, src, g, lo, hi, lambda, status, halt);                   \
-        }                                                                                                        \
-        break;                                                                                                   \
-    }
-        PCT_LAUNCH_BIN(8)
-        PCT_LAUNCH_BIN(16)
-        PCT_LAUNCH_BIN(32)
-        PCT_LAUNCH_BIN(64)
-#undef PCT_LAUNCH_BIN
-    default: break;
-    }
+    const double depth = pl.mlp.u_out - pl.mlp.u_in;
+    const double lateral = std::min({1.5 * depth / std::min(pl.grid.pitch[0], pl.grid.pitch[1]),
+                                     double(pl.grid.nx) + double(pl.grid.ny)});
+    const double along_z = std::min(0.25 * depth / pl.grid.pitch[2], double(pl.grid.nz));
+    const double want = std::ceil((lateral + along_z + 24.0) / kWave);
+    return kWave * int(std::min(std::max(want, 1.0), 60.0));
 }
 
-// Lanes per proton: enough lanes that each walks a few slabs of the dominant
-// axis, within the LDS budget of the staged vertex coordinates.
-constexpr int64_t kPipeMaxBlock = 4096;
-
-static int choose_lanes(const pct_plan &pl, int requested)
-{
-    constexpr size_t kLdsBudget = 64 * 1024;
-    int lanes = requested;
-    if (lanes == 0) {
-        const int ndom = std::max(pl.grid.nx, pl.grid.ny);
-        lanes = ndom >= 160 ? 64 : ndom >= 64 ? 32 : 16;
-    }
-    if (pl.hull && lanes != 1) lanes = 64;  // the hull instantiations use 64 lanes per proton
-    if (lanes > 1 && size_t(64 / lanes) * 3 * size_t(path_vertices_max(pl)) * sizeof(double) + stash_bytes<double>() >
-                         kLdsBudget)
-        lanes = 1;
-    return lanes;
-}
+// Block steps of a call from which the iterate is packed (see IterateDev).
+constexpr int64_t kPackBlocks = 8;
 
 void graph_release(pct_plan &pl)
 {
@@ -2664,11 +1910,10 @@ void graph_release(pct_plan &pl)
 }
 
 // Buffers of the fused FP32 schedule: X[0] = x, X[1] in the workspace,
-// accumulators PK[0..2], range slots R[0..3] (header words from kHdrSlots).
+// accumulators PK[0..2].
 struct FusedBufs {
     float *X[2];
     unsigned long long *PK[3];
-    int *R[4];
     int nv;
     unsigned copy_grid;
 };
@@ -2681,8 +1926,6 @@ static FusedBufs fused_bufs(const pct_plan &pl, void *ws, float *x)
     F.X[1] = reinterpret_cast<float *>(wsb(ws) + L.x1);
     for (int k = 0; k < 3; ++k)
         F.PK[k] = reinterpret_cast<unsigned long long *>(wsb(ws) + L.acc + size_t(k) * L.acc_stride);
-    int *hdr = reinterpret_cast<int *>(wsb(ws) + L.hdr);
-    for (int k = 0; k < 4; ++k) F.R[k] = hdr + kHdrSlots + 2 * k;
     F.nv = int(pl.nvox);
     F.copy_grid = unsigned(std::min<int64_t>(2048, (pl.nvox + 255) / 256));
     return F;
@@ -2694,15 +1937,11 @@ struct FusedStep {
     float *next;
     const unsigned long long *pk_prev;
     unsigned long long *pk_cur, *pk_old;
-    int *r_cur;
-    const int *r_prev, *r_old;
-    int *r_reset;
 };
 
 static FusedStep fused_step(const FusedBufs &F, int64_t q)
 {
-    return FusedStep{F.X[q % 2],       F.X[(q + 1) % 2], F.PK[(q + 2) % 3], F.PK[q % 3],      F.PK[(q + 1) % 3],
-                     F.R[q % 4],       F.R[(q + 3) % 4], F.R[(q + 2) % 4],  F.R[(q + 1) % 4]};
+    return FusedStep{F.X[q % 2], F.X[(q + 1) % 2], F.PK[(q + 2) % 3], F.PK[q % 3], F.PK[(q + 1) % 3]};
 }
 
 // One fused sweep over blocks [b0, b1): copy, one launch per block (launch_q
@@ -2710,9 +1949,9 @@ static FusedStep fused_step(const FusedBufs &F, int64_t q)
 // samples the per-block launches evenly.
 template <class LaunchQ>
 static void enqueue_fused(pct_plan &pl, const FusedBufs &F, int64_t b0, int64_t b1, int64_t block, int64_t n,
-                          hipStream_t s, bool record_events, int64_t every, LaunchQ launch_q, int full = 0)
+                          hipStream_t s, bool record_events, int64_t every, LaunchQ launch_q)
 {
-    hipLaunchKernelGGL(k_sweep_begin, dim3(F.copy_grid), dim3(256), 0, s, F.X[0], F.X[1], F.R[0], F.nv);
+    hipLaunchKernelGGL(k_sweep_begin, dim3(F.copy_grid), dim3(256), 0, s, F.X[0], F.X[1], F.nv);
     int64_t q = 0;
     for (int64_t t = b0; t < b1; ++t, ++q) {
         const int64_t lo = t * block;
@@ -2728,7 +1967,7 @@ static void enqueue_fused(pct_plan &pl, const FusedBufs &F, int64_t b0, int64_t 
     if (q > 0) {
         const int64_t last = q - 1;
         hipLaunchKernelGGL(k_sweep_end, dim3(F.copy_grid), dim3(256), 0, s, F.X[0], F.X[q % 2], F.PK[last % 3],
-                           F.PK[(last + 2) % 3], F.R[last % 4], F.R[(last + 3) % 4], F.nv, full);
+                           F.PK[(last + 2) % 3], F.nv);
     }
 }
 
@@ -2791,11 +2030,15 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
         hipError_t e = prof_prepare(pl);
         if (e != hipSuccess) return e;
     }
-    const int lanes = choose_lanes(pl, o.lanes);
+    // one lane per row on request, and where the wave kernels' records do not
+    // hold the row; else a wave per row
+    const int lanes = o.lanes == 1 || grid_dev(pl.grid).xy_shift == 0 || pl.K > kMaxRowSegments ? 1 : kWave;
+    const int span = record_span(pl);
     const int64_t nblk = o.block_end - o.block_begin;
     const int64_t every = std::max<int64_t>(1, (nblk + kProfSamples - 1) / kProfSamples);
     Layout L = layout_for(pl.nvox, pl.K, o.dtype);
     const PathSrc src = path_src(pl, wsb(ws) + L.table);
+    const size_t rec_lds = record_bytes(src.nvmax, span);
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     int *hdr = reinterpret_cast<int *>(wsb(ws) + L.hdr);
     void *acc = wsb(ws) + L.acc;
@@ -2808,26 +2051,26 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
     const bool det = sizeof(T) == 8 && (o.flags & PCT_DROP_DETERMINISTIC) != 0;
     long long *acc_lo = det ? reinterpret_cast<long long *>(wsb(ws) + L.acc + L.acc_stride) : nullptr;
 
-    // Separate schedule: re-arm the range words, then block kernel + commit
-    // per block.
+    // Separate schedule: block kernel + commit per block.
     auto enqueue_sweep = [&](hipStream_t s, bool record_events) {
-        hipLaunchKernelGGL(k_reset_ranges, dim3(1), dim3(64), 0, s, hdr);
         int64_t seq = 0;
         for (int64_t t = o.block_begin; t < o.block_end; ++t, ++seq) {
             int64_t lo = t * o.block;
             int64_t hi = std::min<int64_t>(n, lo + o.block);
-            int *r_this = hdr + (seq % 2 == 0 ? kHdrRange0 : kHdrRange1);
-            int *r_next = hdr + (seq % 2 == 0 ? kHdrRange1 : kHdrRange0);
             const bool sample = record_events && (seq % every == 0) && pl.prof_used[0] < kProfSamples;
             if (sample) (void)hipEventRecord(prof_event(pl, 0, 2 * pl.prof_used[0]), s);
-            launch_block<T, CHORD, HULL>(lanes, s, p, b, x, acc, cnt, r_this, src, g, lo, hi, o.lambda, status,
-                                         acc_lo, gate.halt);
+            if (lanes == 1)
+                hipLaunchKernelGGL((k_drop_rows<T, CHORD, HULL>), dim3(grid_for(hi - lo)), dim3(kWG), 0, s, p, b, x, acc,
+                                   cnt, src, g, lo, hi, o.lambda, status, acc_lo, gate.halt);
+            else
+                hipLaunchKernelGGL((k_drop_block<T, CHORD, HULL>), dim3(row_grid(hi - lo)), dim3(kWave), rec_lds, s, p,
+                               b, x, acc, cnt, src, g, lo, hi, o.lambda, status, acc_lo, gate.halt, span);
             if (sample) {
                 (void)hipEventRecord(prof_event(pl, 0, 2 * pl.prof_used[0] + 1), s);
                 pl.prof_used[0]++;
                 (void)hipEventRecord(prof_event(pl, 1, 2 * pl.prof_used[1]), s);
             }
-            hipLaunchKernelGGL(k_drop_commit<T>, dim3(commit_grid), dim3(kWG), 0, s, x, acc, cnt, r_this, r_next,
+            hipLaunchKernelGGL(k_drop_commit<T>, dim3(commit_grid), dim3(kWG), 0, s, x, acc, cnt, int(pl.nvox),
                                acc_lo, gate);
             if (sample) {
                 (void)hipEventRecord(prof_event(pl, 1, 2 * pl.prof_used[1] + 1), s);
@@ -2839,44 +2082,57 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
     // block and a slab's window fits the LDS budget
     const int nslab = std::max(pl.grid.nx, pl.grid.ny);
     const int win_words = sizeof(T) == 4 ? slab_window_words() : 0;
+    int cell_bits = 1;  // of a slab's cells and the value that says none
+    while ((int64_t(1) << cell_bits) <= int64_t(nslab) * pl.grid.nz) ++cell_bits;
     const bool binned = sizeof(T) == 4 && lanes > 1 && !(o.flags & (PCT_DROP_SEPARATE_COMMIT | PCT_DROP_FUSED_COMMIT)) &&
-                        nslab <= win_words && o.block <= kBinMaxRows && pl.nvox < (int64_t(1) << 30) &&
-                        ws_bytes >= L.total + 2 * slot_bytes(o.block) + bin_bytes(o.block, nslab);
+                        nslab <= 8192 && o.block <= kBinMaxRows && pl.nvox < (int64_t(1) << 30) && cell_bits < 30 &&
+                        ws_bytes >= L.total + bin_bytes(o.block, nslab);
     const bool comp = binned && !(o.flags & PCT_DROP_NO_COMPENSATION);
+    // the packed iterate costs two copies of the volume a call (about 8 us each
+    // at 256 x 256 x 64) and saves the commits of x-dominant blocks their strided
+    // lines (30 against 26 us each before the other changes to the commit)
+    const bool packed = binned && nblk * o.n_iter >= kPackBlocks && pl.nvox < (int64_t(1) << 29);
+    IterateDev it{};
+    if (binned) {
+        it.packed = packed ? 1 : 0;
+        it.x = reinterpret_cast<float *>(packed ? static_cast<void *>(wsb(ws) + L.x1) : static_cast<void *>(x));
+        it.lo = reinterpret_cast<float *>(wsb(ws) + L.lo);
+        it.sx = packed ? pl.grid.nz : 1;
+        it.sy = packed ? pl.grid.nx * pl.grid.nz : pl.grid.nx;
+        it.sz = packed ? 1 : pl.grid.nx * pl.grid.ny;
+    }
     const bool fused = sizeof(T) == 4 && lanes > 1 && !(o.flags & PCT_DROP_SEPARATE_COMMIT) && !binned && !cancellable;
-    // tracing ahead doubles the workgroups of a launch; with blocks above
-    // kPipeMaxBlock protons the plain fused schedule is the faster one
-    // (measured: 3200-proton blocks 165 vs 169 ms per sweep traced ahead, 6400-proton
-    // blocks 953 vs 871 ms on the 256 x 256 x 64 scan)
-    const bool pipe = fused && lanes == 64 && !(o.flags & PCT_DROP_NO_TRACE_AHEAD) && o.block <= kPipeMaxBlock &&
-                      ws_bytes >= L.total + 2 * slot_bytes(o.block);
     auto sweep = [&](hipStream_t s, bool record_events) {
         if constexpr (sizeof(T) == 4) {
             if (binned) {
                 BinsDev bins;
                 const int64_t cap = bin_rows(o.block);
-                char *bbase = wsb(ws) + L.total + 2 * slot_bytes(o.block);
+                char *bbase = wsb(ws) + L.total;
                 const size_t nrow = size_t(nslab) * size_t(cap);
-                bins.w = reinterpret_cast<unsigned long long *>(bbase);
-                bins.j1 = reinterpret_cast<unsigned *>(bbase + nrow * kBinCap * 8);
-                bins.j0 = reinterpret_cast<unsigned *>(bbase + nrow * (kBinCap * 8 + (kBinCap - 1) * 4));
-                bins.rowmax = reinterpret_cast<float *>(bbase + nrow * (kBinCap * 8 + (kBinCap - 1) * 4 + 2 * 4));
+                bins.e0 = reinterpret_cast<BinEntry *>(bbase);
+                bins.ek = bins.e0 + nrow;
+                bins.rho = reinterpret_cast<double *>(bins.ek + nrow * (kBinCap - 1));
+                bins.rowmax = reinterpret_cast<float *>(bins.rho + cap);
                 bins.cap = int(cap);
                 bins.nslab = nslab;
-                const size_t ncnt = 2 * nrow;
+                bins.cell_bits = cell_bits;
+                const unsigned epochs = (1u << (30 - cell_bits)) - 1u;
                 int *ovf_flag = hdr + kHdrOvf;
                 unsigned long long *ovf = static_cast<unsigned long long *>(acc);
-                const int zc = std::min(pl.grid.nz, win_words / nslab);
-                const int nzc = (pl.grid.nz + zc - 1) / zc;
-                const size_t win_lds = size_t(nslab) * size_t(zc) * sizeof(unsigned long long);
-                float *xlo = reinterpret_cast<float *>(wsb(ws) + L.lo);
-                hipLaunchKernelGGL(k_bins_begin, dim3(unsigned(std::min<size_t>(1024, (ncnt / 4 + 255) / 256 + 1))),
-                                   dim3(256), 0, s, bins.j0, ncnt, ovf_flag);
+                const int64_t cells = int64_t(nslab) * pl.grid.nz;
+                const int chunk = int(std::min<int64_t>(cells, win_words));
+                const int chunks = int((cells + chunk - 1) / chunk);
+                const size_t win_lds = size_t(chunk) * sizeof(unsigned long long) + kListBytes;
+                auto commit = packed ? &k_slab_commit<true> : &k_slab_commit<false>;
                 int64_t seq = 0;
                 for (int64_t t = o.block_begin; t < o.block_end; ++t, ++seq) {
                     const int64_t lo = t * o.block;
                     const int64_t hi = std::min<int64_t>(n, lo + o.block);
                     const int par = int(seq & 1);
+                    bins.epoch = unsigned(seq % epochs) + 1u;
+                    if (bins.epoch == 1u)
+                        hipLaunchKernelGGL(k_bins_begin, dim3(unsigned(std::min<size_t>(1024, (nrow / 2 + 255) / 256 + 1))),
+                                           dim3(256), 0, s, bins.e0, nrow, ovf_flag, seq == 0 ? 1 : 0);
                     // sampled blocks: both kernels timed by their own launch events
                     const bool sample = record_events && (seq % every == 0) && pl.prof_used[0] < kProfSamples;
                     hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -2888,68 +2144,33 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
                         pl.prof_used[0]++;
                         pl.prof_used[1]++;
                     }
-                    launch_bin<CHORD, HULL>(lanes, s, p, b, reinterpret_cast<const float *>(x), bins, par, ovf,
-                                            ovf_flag + par, src, g, lo, hi, o.lambda, status, gate.halt, e[0], e[1]);
+                    const dim3 grid(row_grid(hi - lo));
                     if (sample)
-                        hipExtLaunchKernelGGL(k_slab_commit, dim3(unsigned(nslab * nzc)), dim3(kSlabWG),
-                                              uint32_t(win_lds), s, e[2], e[3], 0u, p, lo, int(hi - lo), bins, par,
-                                              ovf, ovf_flag, reinterpret_cast<float *>(x), xlo, g, zc, nzc,
-                                              comp ? 1 : 0, status, gate);
+                        hipExtLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave), uint32_t(rec_lds), s, e[0],
+                                              e[1], 0u, p, b, it, bins, ovf, ovf_flag + par, src, g, lo, hi,
+                                              o.lambda, status, gate.halt, span);
                     else
-                        hipLaunchKernelGGL(k_slab_commit, dim3(unsigned(nslab * nzc)), dim3(kSlabWG), win_lds, s, p,
-                                           lo, int(hi - lo), bins, par, ovf, ovf_flag, reinterpret_cast<float *>(x),
-                                           xlo, g, zc, nzc, comp ? 1 : 0, status, gate);
+                        hipLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave), rec_lds, s, p, b, it, bins, ovf,
+                                           ovf_flag + par, src, g, lo, hi, o.lambda, status, gate.halt, span);
+                    if (sample)
+                        hipExtLaunchKernelGGL(commit, dim3(unsigned(nslab * chunks)), dim3(kSlabWG), uint32_t(win_lds),
+                                              s, e[2], e[3], 0u, p, lo, int(hi - lo), bins, par, ovf, ovf_flag, it, g,
+                                              chunk, chunks, comp ? 1 : 0, status, gate);
+                    else
+                        hipLaunchKernelGGL(commit, dim3(unsigned(nslab * chunks)), dim3(kSlabWG), win_lds, s, p, lo,
+                                           int(hi - lo), bins, par, ovf, ovf_flag, it, g, chunk, chunks, comp ? 1 : 0,
+                                           status, gate);
                 }
-                return;
-            }
-            if (pipe) {
-                const FusedBufs F = fused_bufs(pl, ws, x);
-                SlotDev slot[2] = {slot_at(wsb(ws) + L.total, o.block),
-                                   slot_at(wsb(ws) + L.total + slot_bytes(o.block), o.block)};
-                const size_t lds = 3 * size_t(src.nvmax) * sizeof(double) + stash_bytes<float>();
-                auto block_range = [&](int64_t t, int64_t &a, int64_t &e) {
-                    a = e = 0;
-                    if (t < o.block_end) {
-                        a = t * o.block;
-                        e = std::min<int64_t>(n, a + o.block);
-                    }
-                };
-                enqueue_fused(pl, F, o.block_begin, o.block_end, o.block, n, s, record_events, every,
-                              [&](hipStream_t s, int64_t q, int64_t lo, int64_t hi, const FusedStep &f) {
-                                  int64_t wlo, whi;
-                                  if (q == 0) {  // prologue: trace the first block
-                                      block_range(o.block_begin, wlo, whi);
-                                      hipLaunchKernelGGL((k_drop_pipe<CHORD, HULL>), dim3(unsigned(8 * ((whi - wlo + 7) / 8))),
-                                                         dim3(64),
-                                                         lds, s, p, b, f.base, f.next, f.pk_prev, f.pk_cur,
-                                                         f.pk_old, f.r_cur, f.r_prev, f.r_old, f.r_reset, slot[1],
-                                                         slot[0], src, g, int64_t(0), int64_t(0), wlo, whi, 0,
-                                                         o.lambda, status, F.nv, 1);
-                                  }
-                                  // the commit scans the whole volume (full = 1): a block's
-                                  // touched index range spans nearly all of it in these
-                                  // angle-major scans, and skipping the range words saves the
-                                  // DROP step their same-address atomics (165 -> 159 ms per
-                                  // sweep on the 10^7-proton 200x200x32 scan)
-                                  block_range(o.block_begin + q + 1, wlo, whi);
-                                  const int64_t n_d = hi - lo;
-                                  const unsigned grid =
-                                      unsigned(kCommitWG + 8 * ((whi - wlo + 7) / 8) + 8 * ((n_d + 7) / 8));
-                                  hipLaunchKernelGGL((k_drop_pipe<CHORD, HULL>), dim3(grid), dim3(64), lds, s, p, b, f.base,
-                                                     f.next, f.pk_prev, f.pk_cur, f.pk_old, f.r_cur, f.r_prev,
-                                                     f.r_old, f.r_reset, slot[q % 2], slot[(q + 1) % 2], src,
-                                                     g, lo, hi, wlo, whi, kCommitWG, o.lambda, status, F.nv, 1);
-                              }, 1);
                 return;
             }
             if (fused) {
                 const FusedBufs F = fused_bufs(pl, ws, x);
                 enqueue_fused(pl, F, o.block_begin, o.block_end, o.block, n, s, record_events, every,
                               [&](hipStream_t s, int64_t, int64_t lo, int64_t hi, const FusedStep &f) {
-                                  launch_fused<CHORD, HULL>(lanes, s, p, b, f.base, f.next, f.pk_prev, f.pk_cur, f.pk_old,
-                                                      f.r_cur, f.r_prev, f.r_old, f.r_reset, src, g, lo, hi,
-                                                      o.lambda, status, F.nv, 1);   // whole-volume commit
-                              }, 1);
+                                  hipLaunchKernelGGL((k_drop_fused<CHORD, HULL>),
+                                                     dim3(kCommitWG + row_grid(hi - lo)), dim3(kWave), rec_lds, s,
+                                                     p, b, f.base, f.next, f.pk_prev, f.pk_cur, f.pk_old, src, g, lo, hi, o.lambda, status, F.nv, span);
+                              });
                 return;
             }
         }
@@ -2965,17 +2186,26 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
         reinterpret_cast<uint64_t>(x),        reinterpret_cast<uint64_t>(ws),
         uint64_t(n), uint64_t(o.block), uint64_t(o.block_begin), uint64_t(o.block_end),
         uint64_t(o.dtype), uint64_t(CHORD), uint64_t(lanes),
-        uint64_t(fused) + 2 * uint64_t(pipe) + 4 * uint64_t(binned) + 8 * uint64_t(comp) + 16 * uint64_t(cancellable) +
-            32 * uint64_t(det),
+        uint64_t(fused) + 4 * uint64_t(binned) + 8 * uint64_t(comp) + 16 * uint64_t(cancellable) +
+            32 * uint64_t(det) + 64 * uint64_t(packed),
         bits_of(o.lambda),
         0};
     if (cancellable) hipLaunchKernelGGL(k_gate_begin, dim3(1), dim3(64), 0, s, gate);
-    if (comp) {
+    const dim3 tiles(unsigned((pl.grid.nx + kTile - 1) / kTile), unsigned(std::min(pl.grid.ny, 65535)),
+                     unsigned((pl.grid.nz + kTile - 1) / kTile));
+    if (packed) {
+        hipLaunchKernelGGL(k_pack_iterate, tiles, dim3(256), 0, s, reinterpret_cast<const float *>(x),
+                           reinterpret_cast<float2 *>(it.x), g);
+    } else if (comp) {
         // the compensation words start at zero in every call (outside the graph)
         hipLaunchKernelGGL(k_zero_f32, dim3(unsigned(std::min<int64_t>(2048, (pl.nvox + 255) / 256))), dim3(256), 0, s,
                            reinterpret_cast<float *>(wsb(ws) + L.lo), pl.nvox);
     }
-    return run_sweeps(pl, key, use_graph, o.n_iter, prof, s, sweep);
+    const int st = run_sweeps(pl, key, use_graph, o.n_iter, prof, s, sweep);
+    if (!packed || st != hipSuccess) return st;
+    hipLaunchKernelGGL(k_unpack_iterate, tiles, dim3(256), 0, s, reinterpret_cast<float *>(x),
+                       reinterpret_cast<const float2 *>(it.x), g);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -3127,7 +2357,7 @@ static void launch_rows_fused(int lanes, hipStream_t s, const RowsDev &rows, con
     case LPR: {                                                                                                  \
         const unsigned grid = unsigned(kCommitWG + (n + (64 / LPR) - 1) / (64 / LPR));                        \
         hipLaunchKernelGGL((k_drop_rows_fused<CT, LPR>), dim3(grid), dim3(64), 0, s, rows, b, f.base, f.next,     \
-                           f.pk_prev, f.pk_cur, f.pk_old, f.r_cur, f.r_prev, f.r_old, f.r_reset, lo, hi, lambda,  \
+                           f.pk_prev, f.pk_cur, f.pk_old, lo, hi, lambda,                                          \
                            status, nvox);                                                                        \
         break;                                                                                                   \
     }

@@ -286,9 +286,10 @@ __device__ __forceinline__ PathState path_prepare(const Rec &r, const PathSrc &m
     }
 }
 
-__device__ __forceinline__ void hull_vertex(const Rec &r, const PathSrc &m, const PathState &ps, int k, double *P)
+// Vertex k of a hull path in the beam frame.
+__device__ __forceinline__ void hull_point(const Rec &r, const PathSrc &m, const PathState &ps, int k, double &u,
+                                           double &t, double &v)
 {
-    double u, t, v;
     const int j = k - ps.pre;
     if (ps.miss) {
         u = k == 0 ? m.u_in : m.u_out;
@@ -318,19 +319,21 @@ __device__ __forceinline__ void hull_vertex(const Rec &r, const PathSrc &m, cons
         t = c[0] * ps.t0 + c[1] * r.th_in + c[2] * ps.t1 + c[3] * r.th_out;
         v = c[0] * ps.v0 + c[1] * r.ph_in + c[2] * ps.v1 + c[3] * r.ph_out;
     }
-    P[0] = u * r.cs - t * r.sn;
-    P[1] = u * r.sn + t * r.cs;
-    P[2] = v;
 }
 
 // Vertex k (0 <= k < ps.nv) in lab coordinates (mm).
 template <bool HULL>
 __device__ __forceinline__ void path_vertex(const Rec &r, const PathSrc &m, const PathState &ps, int k, double P[3])
 {
-    if constexpr (HULL)
-        hull_vertex(r, m, ps, k, P);
-    else
+    if constexpr (HULL) {
+        double u, t, v;
+        hull_point(r, m, ps, k, u, t, v);
+        P[0] = u * r.cs - t * r.sn;
+        P[1] = u * r.sn + t * r.cs;
+        P[2] = v;
+    } else {
         vertex(r, m.tab + k * kRowDoubles, P);
+    }
 }
 
 // Walk of the whole polyline of one proton.
