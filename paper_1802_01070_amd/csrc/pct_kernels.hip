@@ -1971,6 +1971,23 @@ static void enqueue_fused(pct_plan &pl, const FusedBufs &F, int64_t b0, int64_t 
     }
 }
 
+// Whether a call's sweeps are recorded into a graph.  Recording costs about 6
+// us a launch, replaying saves about 1 us a block step, and only of short ones
+// (block steps of tens of us hide their launches): 63 FP64 steps of 3200 rows
+// on the 64 x 64 x 4 grid, six sweeps: 7.5 ms replayed, 8.4 ms recorded and
+// replayed, 7.8 ms launched; 782 binned steps of 6400 rows: 39.9 ms both ways, 4
+// ms more the first time.  A call that can be cancelled is always recorded: its
+// enqueue holds the plan's lock, which the request needs.
+constexpr int kGraphSweeps = 4;
+constexpr int64_t kLaunchSteps = 2048;
+
+static bool graph_sweeps(const pct_drop_opts &o)
+{
+    if (o.flags & (PCT_DROP_NO_GRAPH | PCT_DROP_PROFILE)) return false;
+    return (o.flags & PCT_DROP_CANCELLABLE) || o.n_iter >= kGraphSweeps ||
+           (o.block_end - o.block_begin) * o.n_iter > kLaunchSteps;
+}
+
 // Runs n_iter sweeps: directly on the stream, or captured once into a HIP
 // graph (cached on the plan for an identical launch key) and replayed.
 template <class Sweep>
@@ -2176,7 +2193,7 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
         }
         enqueue_sweep(s, record_events);
     };
-    const bool use_graph = !(o.flags & PCT_DROP_NO_GRAPH) && !prof;
+    const bool use_graph = graph_sweeps(o);
     std::vector<uint64_t> key = {
         reinterpret_cast<uint64_t>(p.t_in),   reinterpret_cast<uint64_t>(p.v_in),
         reinterpret_cast<uint64_t>(p.th_in),  reinterpret_cast<uint64_t>(p.ph_in),
@@ -2401,7 +2418,7 @@ int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *
                           }
                       });
     };
-    const bool use_graph = !(o.flags & PCT_DROP_NO_GRAPH) && !prof;
+    const bool use_graph = graph_sweeps(o);
     std::vector<uint64_t> key = {reinterpret_cast<uint64_t>(rows.offsets), reinterpret_cast<uint64_t>(rows.vox),
                                  reinterpret_cast<uint64_t>(rows.chord),   reinterpret_cast<uint64_t>(rows.n2),
                                  reinterpret_cast<uint64_t>(b),            reinterpret_cast<uint64_t>(x),

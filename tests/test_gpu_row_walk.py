@@ -12,7 +12,8 @@ import torch
 
 import oracle
 from paper_1802_01070_amd import api, synth
-from paper_1802_01070_amd._lib import PCT_DROP_FUSED_COMMIT, PCT_DROP_NO_COMPENSATION, PCT_DROP_SEPARATE_COMMIT
+from paper_1802_01070_amd._lib import (PCT_DROP_FUSED_COMMIT, PCT_DROP_NO_COMPENSATION, PCT_DROP_NO_GRAPH,
+                                      PCT_DROP_SEPARATE_COMMIT)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -91,3 +92,22 @@ def test_packed_iterate_gives_the_same_result(blocks, n_iter, dims):
     api.pct_drop_iterate(plan, pr, bd, x, block=block, lam=0.5, n_iter=n_iter)
     ref = oracle.drop(grid, mlp, p, b, x0, block=block, lam=0.5, n_iter=n_iter)
     assert error(x, ref) <= 1e-5
+
+
+@pytest.mark.parametrize("n_iter", [3, 4])
+def test_recorded_sweeps_match_launched_ones(n_iter):
+    """Either side of the number of sweeps from which a call records a graph;
+    the block sums are whole numbers, so the results are the same bits."""
+    grid = synth.Grid(40, 40, 6)
+    mlp = synth.MLPModel(u_in=-30.0, u_out=30.0)
+    p, b = records(grid, mlp, 150, 7)
+    plan = api.Plan(grid, mlp, DEV, n_hint=64)
+    pr, bd = api.Protons(p, DEV), torch.from_numpy(b).to(DEV)
+
+    def run(flags):
+        x = torch.ones(grid.nvox, device=DEV)
+        for _ in range(2):
+            api.pct_drop_iterate(plan, pr, bd, x, block=16, lam=0.5, n_iter=n_iter, flags=flags)
+        return x
+
+    assert torch.equal(run(0), run(PCT_DROP_NO_GRAPH))
