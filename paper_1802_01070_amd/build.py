@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libpct.so")
 SOURCES = ["pct_api.cpp", "pct_kernels.hip", "pct_fbp.hip", "pct_sort.hip"]
-HEADERS = ["pct_internal.h", "pct_path.hpp", "pct_sort.h"]
+HEADERS = ["pct_internal.h", "pct_path.hpp", "pct_walk.hpp", "pct_lane_walk.hpp", "pct_sort.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

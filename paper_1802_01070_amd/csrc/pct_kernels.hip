@@ -2,7 +2,7 @@
 //
 //   k_trace        ordered emission list of each proton's path (debug/parity)
 //   k_forward      y = A x, ||a_i||^2   (one lane per proton, gathers)
-//   k_backproject  g += A^T r           (one lane per proton, LDS-summed, atomics)
+//   k_backproject  g += A^T r           (one lane per proton, LDS lines, atomics)
 //   k_drop_bin     DROP block, a wave per row: records -> a_i.x, ||a_i||^2 ->
 //                  rho_i, chords into slab bins (FP32)
 //   k_slab_commit  x_j += acc_j / s_j slab by slab from the bins
@@ -24,11 +24,10 @@
 
 #include "pct_internal.h"
 #include "pct_path.hpp"
+#include "pct_lane_walk.hpp"
 #include "pct_walk.hpp"
 
 namespace pct {
-
-constexpr int kWG = 256;
 
 __device__ __forceinline__ void raise_status(unsigned *status, unsigned bit)
 {
@@ -80,43 +79,17 @@ __global__ void k_gate_begin(GateDev gt)
     }
 }
 
-// Merges consecutive pieces in the same voxel and hands merged pieces (with
-// the chord rounded to the solver's format) to Inner::final.
-template <class Inner, int CHORD>
-struct Merge {
-    Inner &in;
-    int nx, ny;
-    int cj, cx, cy, cz;
-    double cc;
-
-    __device__ __forceinline__ Merge(Inner &inner, const GridDev &grid)
-        : in(inner), nx(grid.n[0]), ny(grid.n[1]), cj(-1), cx(0), cy(0), cz(0), cc(0.0)
-    {
-    }
-
-    __device__ __forceinline__ void segment(double dx, double dy) { in.segment(dx, dy); }
-
-    __device__ __forceinline__ void piece(int ix, int iy, int iz, double c)
-    {
-        int j = ix + nx * (iy + ny * iz);
-        if (j == cj) {
-            cc += c;
-            return;
-        }
-        if (cj >= 0) in.final(cj, cx, cy, cz, round_chord<CHORD>(cc));
-        cj = j;
-        cx = ix;
-        cy = iy;
-        cz = iz;
-        cc = c;
-    }
-
-    __device__ __forceinline__ void finish()
-    {
-        if (cj >= 0) in.final(cj, cx, cy, cz, round_chord<CHORD>(cc));
-        cj = -1;
-    }
-};
+// The whole path of one row, piece by piece, into sink.piece; false if the path
+// does not move on along the row's dominant axis in every segment.
+template <bool HULL, class Sink>
+__device__ __forceinline__ bool walk_row(const Rec &r, const PathSrc &src, const GridDev &g, Sink &sink)
+{
+    const LanePath<HULL> path(src, g, r);
+    LaneWalk<HULL> walk(path, g, r);
+    walk.run(0, path.K, sink);
+    walk.finish(sink);
+    return walk.onward;
+}
 
 // ---------------------------------------------------------------------------
 // trace
@@ -125,8 +98,7 @@ struct TraceSink {
     int32_t *vox;
     double *chord;
     int32_t cap, n;
-    __device__ __forceinline__ void segment(double, double) {}
-    __device__ __forceinline__ void final(int j, int, int, int, double c)
+    __device__ __forceinline__ void piece(int j, int, int, int, double c)
     {
         if (n < cap) {
             vox[n] = j;
@@ -146,9 +118,7 @@ __global__ void __launch_bounds__(kWG) k_trace(ProtonsDev p, int64_t first, int6
     Rec r = load_rec(p, first + q);
     TraceSink ts{vox + q * max_nnz, chord + q * max_nnz, max_nnz, 0};
     if (rec_finite(r)) {
-        Merge<TraceSink, PCT_CHORD_F64> m(ts, g);
-        walk_path<HULL>(r, src, g, m);
-        m.finish();
+        walk_row<HULL>(r, src, g, ts);
     } else {
         raise_status(status, PCT_DEV_NONFINITE);
     }
@@ -170,90 +140,108 @@ struct PlainX {
     __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
 };
 
-template <typename T, class XA = PlainX<T>>
+// The value read for a piece is used when the next piece comes, so the reads
+// stay in flight behind the walk.
+template <typename T, bool NORM, int CHORD = PCT_CHORD_F64>
 struct DotSink {
-    XA x;
-    Reentry re;
-    double dot, n2;
-    __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
-    __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
+    const T *__restrict__ x;
+    Reentry *re;
+    T pending = T(0);
+    double c0 = 0.0, dot = 0.0, n2 = 0.0;
+    __device__ __forceinline__ void piece(int j, int ix, int iy, int iz, double c)
     {
-        bool first;
-        double aprev = re.visit(j, ix, iy, iz, c, first);
-        dot += c * x(j);
-        n2 += c * (2.0 * aprev + c);
+        c = round_chord<CHORD>(c);
+        dot = fma(c0, double(pending), dot);
+        pending = x[j];
+        c0 = c;
+        if constexpr (NORM) {
+            bool first;
+            const double before = re->visit(j, ix, iy, iz, c, first);
+            n2 = fma(c, 2.0 * before + c, n2);
+        }
     }
+    __device__ __forceinline__ double sum() const { return fma(c0, double(pending), dot); }
 };
 
-template <typename T, bool HULL>
+// One lane per row: bound by FP64 instructions (about 80 a segment and 25 a
+// crossing, 4 waves a SIMD, 3 with norms).  2e6 rows of 220 segments on the 256 x
+// 256 x 64 grid: 2.6 ms, 3.65 with norms (5.8 for either with a walk from plane
+// to plane of each segment's clipped part and a register window of pieces).
+template <typename T, bool HULL, bool NORM>
 __global__ void __launch_bounds__(kWG) k_forward(ProtonsDev p, int64_t first, int64_t n, const T *__restrict__ x,
                                                  T *y, T *nrm2, const PathSrc src, GridDev g, unsigned *status)
 {
     int64_t i = first + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     Rec r = load_rec(p, i);
-    DotSink<T> s;
-    s.x = PlainX<T>{x};
-    s.dot = s.n2 = 0.0;
-    s.re.init(r);
+    __shared__ std::conditional_t<NORM, Reentry::Lds, int> lds;
+    Reentry re(reinterpret_cast<Reentry::Lds &>(lds), r);
+    DotSink<T, NORM> s{x, &re};
     if (rec_finite(r)) {
-        Merge<DotSink<T>, PCT_CHORD_F64> m(s, g);
-        walk_path<HULL>(r, src, g, m);
-        m.finish();
-        if (s.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
+        const bool onward = walk_row<HULL>(r, src, g, s);
+        if (!onward || (NORM && re.unsafe)) raise_status(status, PCT_DEV_REENTRY);
     } else {
         raise_status(status, PCT_DEV_NONFINITE);
     }
-    y[i] = T(s.dot);
-    if (nrm2) nrm2[i] = T(s.n2);
+    y[i] = T(s.sum());
+    if constexpr (NORM) nrm2[i] = T(s.n2);
 }
 
 // ---------------------------------------------------------------------------
 // back projection
 // ---------------------------------------------------------------------------
-// Back projection g += A^T r, one lane per proton.  The 256 rows of a
-// workgroup are consecutive in the scan, and an angle-sorted scan's
-// consecutive rows cross nearly the same voxels, so the workgroup first sums
-// its pieces in an LDS table keyed by voxel (open addressing, a few probes)
-// and each distinct voxel then reaches HBM with one atomic.  A piece that
-// finds no slot goes straight to HBM, and so do the later pieces of its lane
-// (the table is filling up: an unsorted scan).
+// Back projection g += A^T r, one lane per proton.  HBM atomics bound it: about
+// 2.3e10 lanes a second, wherever they point, unless neighbouring lanes name
+// neighbouring voxels.  The 256 rows of a workgroup are consecutive in the scan,
+// and an angle-sorted scan's consecutive rows cross nearly the same voxels, so
+// the workgroup sums its pieces in an LDS table.  Its key is a line of eight
+// consecutive voxels (open addressing, a few probes): the table then reaches HBM
+// line by line, eight lanes to one request.  The rows advance together, kSteps
+// segments at a time, and the table is emptied after each such part: the voxels
+// of a part fit it, where those of whole rows (22 000 of the head scan's 256 rows)
+// would not.  A piece that finds no slot goes straight to HBM, and so do the later
+// pieces of its lane in that part (a scan in acquisition order).
+// 2e6 rows of 220 segments on the 256 x 256 x 64 grid, FP32 / FP64: sorted 5.3 /
+// 4.8 ms (18.0 / 18.0 with a table keyed by voxel for the whole row; 12.4 / 11.0
+// with that key in parts; lines of 4: 6.2, of 16: 6.3; 5.1 without the flush);
+// acquisition order 17.5 / 18.0 ms (26.0 / 23.1; parts of 16 segments 20.5).
 template <typename T>
 struct BpTable {
-    static constexpr int kSlots = sizeof(T) == 4 ? 8192 : 4096;  // 64 KB / 48 KB of LDS
-    static constexpr int kBits = sizeof(T) == 4 ? 13 : 12;
-    static constexpr int kProbes = 8;
+    static constexpr int kLine = 8;       // consecutive voxels of a key
+    static constexpr int kBits = sizeof(T) == 4 ? 10 : 9;
+    static constexpr int kKeys = 1 << kBits;
+    static constexpr int kSlots = kKeys * kLine;
+    static constexpr int kProbes = 4;
+    static constexpr int kSteps = 8;
 };
 
 template <typename T>
 struct HashScatterSink {
-    int *keys;
-    T *vals;
-    T *g;
+    LdsPtr<int> keys;
+    LdsPtr<T> vals;
+    HbmPtr<T> g;
     double r;
     bool full;  // a probe sequence of this lane found no slot
-    __device__ __forceinline__ void segment(double, double) {}
-    __device__ __forceinline__ void final(int j, int, int, int, double c)
+    __device__ __forceinline__ void piece(int j, int, int, int, double c)
     {
         using B = BpTable<T>;
         const T v = T(r * c);
-        if (!full) {
-            unsigned s = (unsigned(j) * 2654435761u) >> (32 - B::kBits);
-            for (int q = 0; q < B::kProbes; ++q) {
-                int k = *reinterpret_cast<volatile int *>(keys + s);
-                if (k == -1) {
-                    const int old = atomicCAS(keys + s, -1, j);
-                    k = old == -1 ? j : old;
-                }
-                if (k == j) {
-                    atomicAdd(vals + s, v);
-                    return;
-                }
-                s = (s + 1) & (B::kSlots - 1);
+        const int line = j / B::kLine;
+        unsigned s = (unsigned(line) * 2654435761u) >> (32 - B::kBits);
+#pragma unroll 1
+        for (int q = full ? B::kProbes : 0; q < B::kProbes; ++q) {
+            int k = __hip_atomic_load(keys + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (k == -1 && __hip_atomic_compare_exchange_strong(keys + s, &k, line, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_WORKGROUP))
+                k = line;
+            if (k == line) {
+                __hip_atomic_fetch_add(vals + (s * B::kLine + unsigned(j) % B::kLine), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                return;
             }
-            full = true;
+            s = (s + 1) & (B::kKeys - 1);
         }
-        atomicAdd(g + j, v);
+        full = true;
+        __hip_atomic_fetch_add(g + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
 
@@ -263,13 +251,10 @@ __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first
                                                      unsigned *status)
 {
     using B = BpTable<T>;
-    __shared__ int keys[B::kSlots];
+    __shared__ int keys[B::kKeys];
     __shared__ T vals[B::kSlots];
-    for (int q = threadIdx.x; q < B::kSlots; q += kWG) {
-        keys[q] = -1;
-        vals[q] = T(0);
-    }
-    __syncthreads();
+    for (int q = threadIdx.x; q < B::kSlots; q += kWG) vals[q] = T(0);
+    for (int q = threadIdx.x; q < B::kKeys; q += kWG) keys[q] = -1;
     const int64_t i = first + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     bool active = i < n;
     double ri = 0.0;
@@ -283,19 +268,29 @@ __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first
             if (!rec_finite(r) || !isfinite(ri)) {
                 raise_status(status, PCT_DEV_NONFINITE);
                 active = false;
+                r = Rec{};
             }
         }
     }
-    if (active) {
-        HashScatterSink<T> s{keys, vals, gout, ri, false};
-        Merge<HashScatterSink<T>, PCT_CHORD_F64> m(s, g);
-        walk_path<HULL>(r, src, g, m);
-        m.finish();
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < B::kSlots; q += kWG) {
-        const int k = keys[q];
-        if (k >= 0) atomicAdd(gout + k, vals[q]);
+    const LanePath<HULL> path(src, g, r);
+    LaneWalk<HULL> walk(path, g, r);
+    HashScatterSink<T> s{(LdsPtr<int>)keys, (LdsPtr<T>)vals, (HbmPtr<T>)gout, ri, false};
+    const int K = active ? path.K : 0;
+    for (int k0 = 0; __syncthreads_or(k0 < K); k0 += B::kSteps) {
+        s.full = false;
+        if (k0 < K) {
+            walk.run(k0, min(k0 + B::kSteps, K), s);
+            if (k0 + B::kSteps >= K) walk.finish(s);
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < B::kSlots; q += kWG) {
+            const int k = keys[q / B::kLine];
+            if (k < 0) continue;
+            const T v = vals[q];
+            if (v != T(0)) atomicAdd(gout + (k * B::kLine + q % B::kLine), v);
+            vals[q] = T(0);
+            if (q % B::kLine == 0) keys[q / B::kLine] = -1;
+        }
     }
 }
 
@@ -389,17 +384,17 @@ __device__ __forceinline__ void scatter_one(void *acc, long long *acc_lo, int32_
 // Scatter of one row: acc_j += rho a_ij and s_j += 1 once per row.  FP32 value
 // type: packed 64-bit accumulator; FP64: double accumulator (or the integer
 // pair) plus int count.
-template <typename T>
+template <typename T, int CHORD>
 struct DropScatterSink {
     void *acc;
-    long long *acc_lo = nullptr;  // FP64 deterministic mode: low words of the integer pair
+    long long *acc_lo;  // FP64 deterministic mode: low words of the integer pair
     int32_t *cnt;
     unsigned *status;
     Reentry re;
     double rho;
-    __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
-    __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
+    __device__ __forceinline__ void piece(int j, int ix, int iy, int iz, double c)
     {
+        c = round_chord<CHORD>(c);
         bool first;
         re.visit(j, ix, iy, iz, c, first);
         scatter_one<T>(acc, acc_lo, cnt, j, rho * c, first, status);
@@ -428,30 +423,15 @@ __global__ void __launch_bounds__(kWG) k_drop_rows(ProtonsDev p, const float *__
             active = false;
         }
     }
-    DropScatterSink<T> sc;
-    if (active) {
-        DotSink<T> s;
-        s.x = PlainX<T>{x};
-        s.dot = s.n2 = 0.0;
-        s.re.init(r);
-        {
-            Merge<DotSink<T>, CHORD> m(s, g);
-            walk_path<HULL>(r, src, g, m);
-            m.finish();
-        }
-        if (s.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-        if (s.n2 > 0.0) {
-            sc.acc = acc;
-            sc.acc_lo = acc_lo;
-            sc.cnt = cnt;
-            sc.status = status;
-            sc.rho = lambda * (bi - s.dot) / s.n2;
-            sc.re.init(r);
-            Merge<DropScatterSink<T>, CHORD> m(sc, g);
-            walk_path<HULL>(r, src, g, m);
-            m.finish();
-        }
-    }
+    if (!active) return;
+    __shared__ Reentry::Lds lds;
+    Reentry re(lds, r);
+    DotSink<T, true, CHORD> s{x, &re};
+    const bool onward = walk_row<HULL>(r, src, g, s);
+    if (!onward || re.unsafe) raise_status(status, PCT_DEV_REENTRY);
+    if (!(s.n2 > 0.0)) return;
+    DropScatterSink<T, CHORD> sc{acc, acc_lo, cnt, status, Reentry(lds, r), lambda * (bi - s.sum()) / s.n2};
+    walk_row<HULL>(r, src, g, sc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1339,8 +1319,7 @@ __global__ void __launch_bounds__(kSelWG) k_region_scatter(ProtonsDev p, const f
 // Counting sink: merged pieces of a row.
 struct CountSink {
     int32_t n;
-    __device__ __forceinline__ void segment(double, double) {}
-    __device__ __forceinline__ void final(int, int, int, int, double) { ++n; }
+    __device__ __forceinline__ void piece(int, int, int, int, double) { ++n; }
 };
 
 // Row lengths (after consecutive merge) into offsets[1..n].
@@ -1354,9 +1333,7 @@ __global__ void __launch_bounds__(kWG) k_row_lengths(ProtonsDev p, int64_t n, lo
     Rec r = load_rec(p, i);
     CountSink cs{0};
     if (rec_finite(r)) {
-        Merge<CountSink, PCT_CHORD_F64> m(cs, g);
-        walk_path<HULL>(r, src, g, m);
-        m.finish();
+        walk_row<HULL>(r, src, g, cs);
     } else {
         raise_status(status, PCT_DEV_NONFINITE);
     }
@@ -1444,9 +1421,9 @@ struct RowSink {
     int64_t pos, end;
     Reentry re;
     double n2;
-    __device__ __forceinline__ void segment(double dx, double dy) { re.segment(dx, dy); }
-    __device__ __forceinline__ void final(int j, int ix, int iy, int iz, double c)
+    __device__ __forceinline__ void piece(int j, int ix, int iy, int iz, double c)
     {
+        c = round_chord<CT>(c);
         bool first;
         const double aprev = re.visit(j, ix, iy, iz, c, first);
         n2 += c * (2.0 * aprev + c);
@@ -1467,13 +1444,11 @@ __global__ void __launch_bounds__(kWG) k_rows_build(ProtonsDev p, int64_t n, con
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     Rec r = load_rec(p, i);
-    RowSink<CT> rs{vox, chord, offsets[i], offsets[i + 1], {}, 0.0};
-    rs.re.init(r);
+    __shared__ Reentry::Lds lds;
+    RowSink<CT> rs{vox, chord, offsets[i], offsets[i + 1], Reentry(lds, r), 0.0};
     if (rec_finite(r)) {
-        Merge<RowSink<CT>, CT> m(rs, g);
-        walk_path<HULL>(r, src, g, m);
-        m.finish();
-        if (rs.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
+        const bool onward = walk_row<HULL>(r, src, g, rs);
+        if (!onward || rs.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
     } else {
         raise_status(status, PCT_DEV_NONFINITE);
     }
@@ -1761,23 +1736,30 @@ int launch_forward(const pct_plan &pl, const ProtonsDev &p, int64_t n, const voi
     const PathSrc src = path_src(pl, wsb(ws) + L.table);
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     GridDev g = grid_dev(pl.grid);
-    auto go = [&](auto hull) {
-        constexpr bool H = decltype(hull)::value;
+    auto go = [&](auto hull, auto norm, auto value) {
+        using T = decltype(value);
         launch_pieces(n, [&](int64_t first, int64_t cnt) {
-            if (dtype == PCT_F64)
-                hipLaunchKernelGGL((k_forward<double, H>), dim3(grid_for(cnt)), dim3(kWG), 0, s, p, first,
-                                   first + cnt, static_cast<const double *>(x), static_cast<double *>(y),
-                                   static_cast<double *>(nrm2), src, g, status);
-            else
-                hipLaunchKernelGGL((k_forward<float, H>), dim3(grid_for(cnt)), dim3(kWG), 0, s, p, first,
-                                   first + cnt, static_cast<const float *>(x), static_cast<float *>(y),
-                                   static_cast<float *>(nrm2), src, g, status);
+            hipLaunchKernelGGL((k_forward<T, decltype(hull)::value, decltype(norm)::value>), dim3(grid_for(cnt)),
+                               dim3(kWG), 0, s, p, first, first + cnt, static_cast<const T *>(x),
+                               static_cast<T *>(y), static_cast<T *>(nrm2), src, g, status);
         });
     };
+    auto typed = [&](auto hull, auto norm) {
+        if (dtype == PCT_F64)
+            go(hull, norm, 0.0);
+        else
+            go(hull, norm, 0.0f);
+    };
+    auto normed = [&](auto hull) {
+        if (nrm2)
+            typed(hull, std::true_type{});
+        else
+            typed(hull, std::false_type{});
+    };
     if (src.hull)
-        go(std::true_type{});
+        normed(std::true_type{});
     else
-        go(std::false_type{});
+        normed(std::false_type{});
     return hipGetLastError();
 }
 
