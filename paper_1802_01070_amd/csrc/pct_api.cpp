@@ -559,7 +559,7 @@ int pct_drop_iterate_rows(const pct_plan *plan, const pct_rows *rows, const floa
     oo.block_end = end;
     pct_plan &pl = *const_cast<pct_plan *>(plan);
     std::lock_guard<std::mutex> lock(pl.mu);
-    return hip_status(launch_drop_rows(pl, *rows, b, static_cast<float *>(x), oo, ws,
+    return hip_status(launch_drop_rows(pl, *rows, b, static_cast<float *>(x), oo, ws, ws_bytes,
                                        stream));
 }
 

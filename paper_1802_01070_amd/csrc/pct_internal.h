@@ -81,13 +81,14 @@ inline size_t bin_bytes(int64_t records, int nslab)
 }
 
 // header words (int32 index): status word, the two overflow flags of the
-// binned schedule (by block parity), and the block-boundary gate of
+// binned schedule (by block parity), the axis of a block of stored rows, and the block-boundary gate of
 // cancellable calls: the host's cancel request, the gate word, the count of
 // ended workgroups of the running commit launch and (int64) the block steps
 // applied
 enum : int {
     kHdrStatus = 0,
     kHdrOvf = 16,
+    kHdrAxis = 18,
     kHdrCancel = 20,
     kHdrHalt = 21,
     kHdrGateCount = 22,
@@ -157,7 +158,7 @@ int launch_rows_count(const pct_plan &pl, const ProtonsDev &p, int64_t n, int64_
 int launch_rows_build(const pct_plan &pl, const ProtonsDev &p, int64_t n, int chord_type, const int64_t *offsets,
                       int32_t *vox, void *chord, double *n2, void *ws, void *stream);
 int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *x, const pct_drop_opts &o, void *ws,
-                     void *stream);
+                     size_t ws_bytes, void *stream);
 int launch_span_histogram(const pct_plan &pl, const ProtonsDev &p, int64_t n, int64_t *hist, void *stream);
 int launch_order_blocks(const pct_plan &pl, const ProtonsDev &p, int64_t n, const float *b, int64_t block,
                         const ProtonsBufDev &out, float *b_out, void *stream);

@@ -9,6 +9,8 @@
 //   k_drop_block   DROP block, a wave per row, one atomic per piece (separate
 //                  schedule); k_drop_fused: with the commit of the block before
 //   k_drop_rows    the same with one lane per row
+//   k_rows_bin     DROP block over stored rows: entries for k_slab_commit
+//   k_drop_rows_fused  the same with atomics, and the commit of the block before
 //   k_drop_commit  x_j += acc_j / s_j, reset
 //   k_tv           smoothed total variation value and gradient
 #include <hip/hip_ext.h>
@@ -849,12 +851,12 @@ template <bool PACKED>
 __device__ __forceinline__ void slab_commit_body(const ProtonsDev &p, int64_t lo, int nb, const BinsDev &bins,
                                                  int par, unsigned long long *ovf, int *ovf_flag,
                                                  const IterateDev &it, const GridDev &g, int chunk, int chunks,
-                                                 int comp, unsigned *status)
+                                                 int comp, const int *stored_axis, unsigned *status)
 {
     extern __shared__ unsigned long long win[];
     const int tid = int(threadIdx.x);
     const int s = int(blockIdx.x) / chunks, part = int(blockIdx.x) % chunks;
-    const int axis = block_axis(p, lo);
+    const int axis = stored_axis ? *stored_axis : block_axis(p, lo);
     const int nlat = g.n[1 - axis], cells = nlat * g.n[2];
     const int c0 = part * chunk, nw = min(chunk, cells - c0);
     if (blockIdx.x == 0 && tid == 0) ovf_flag[1 - par] = 0;
@@ -1020,11 +1022,11 @@ __device__ __forceinline__ void slab_commit_body(const ProtonsDev &p, int64_t lo
 template <bool PACKED>
 __global__ void __launch_bounds__(kSlabWG) k_slab_commit(ProtonsDev p, int64_t lo, int nb, BinsDev bins, int par,
                                                          unsigned long long *ovf, int *ovf_flag, IterateDev it,
-                                                         GridDev g, int chunk, int chunks, int comp, unsigned *status,
-                                                         GateDev gt)
+                                                         GridDev g, int chunk, int chunks, int comp,
+                                                         const int *stored_axis, unsigned *status, GateDev gt)
 {
     if (gate_closed(gt.halt)) return;
-    slab_commit_body<PACKED>(p, lo, nb, bins, par, ovf, ovf_flag, it, g, chunk, chunks, comp, status);
+    slab_commit_body<PACKED>(p, lo, nb, bins, par, ovf, ovf_flag, it, g, chunk, chunks, comp, stored_axis, status);
     gate_commit_end(gt);
 }
 
@@ -1465,7 +1467,8 @@ struct RowsDev {
 
 constexpr int kRowRegs = 8;  // pieces per lane kept in registers between the gather and the scatter
 
-// Fused FP32 DROP block over stored rows: LPR lanes per row, 64 / LPR rows per
+// Fused FP32 DROP block over stored rows, where the call names its lanes per row or
+// the workspace holds no bins for its blocks: LPR lanes per row, 64 / LPR rows per
 // one-wave workgroup; commit workgroups first (see k_drop_fused).
 template <int CT, int LPR>
 __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const float *__restrict__ b,
@@ -1549,6 +1552,156 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
             atomicAdd(pk_cur + j, pack_contribution(rho * double(S::get(chord[q])), v < 0, status));
         }
     }
+}
+
+// First kernel of a stored-row block of the binned schedule, one wave per row:
+// what k_drop_bin leaves in the bins, from pieces that are read.  A row goes by
+// bins when its slabs follow each other in one direction along the block's axis
+// and every slab's first piece is the row's first in its voxel; any other row,
+// one of more than kBinRegs * 64 pieces, and pieces past kBinCap of a slab are
+// added to the overflow words.  The block's axis is the one along which its first
+// row covers more voxels; the row's wave leaves it for the commit.
+// 3200 FP16 rows of 290 pieces on 200 x 200 x 32: 15.5 us and 13.9 for the commit,
+// where adding every piece to HBM words (k_drop_rows_fused, 9.3e5 atomics on
+// scattered words at 2.3e10 a second) takes 33.2.  Bound by its chain of round
+// trips (offsets, pieces, gather) and 7.4 MB of entries.
+constexpr int kBinRegs = 8;
+
+template <int CT>
+__global__ void __launch_bounds__(kWave) k_rows_bin(RowsDev rows, const float *__restrict__ b, IterateDev it,
+                                                    BinsDev bins, unsigned long long *ovf, int *ovf_flag, int *axis_out,
+                                                    GridDev g, int64_t lo, int64_t hi, double lambda, unsigned *status,
+                                                    int nvox)
+{
+    using S = StoredChord<CT>;
+    const typename S::type *__restrict__ chord = static_cast<const typename S::type *>(rows.chord);
+    const int64_t i = row_of_workgroup(int(blockIdx.x), lo, hi);
+    if (i >= hi) return;
+    const int lane = int(threadIdx.x), row = int(i - lo);
+    const long long a = rows.offsets[i], e = rows.offsets[i + 1], fa = rows.offsets[lo], fe = rows.offsets[lo + 1];
+    const double bi = double(b[i]), n2 = rows.n2[i];
+    const int len = int(min(e - a, 0x7FFFFFFFll));
+    const bool finite = isfinite(bi);
+    if (!finite && lane == 0) raise_status(status, PCT_DEV_NONFINITE);
+    struct Voxel {
+        int x, y, z;
+    };
+    auto decode = [&](int j) {
+        const unsigned z = udiv_exact(unsigned(j), unsigned(g.n[0]) * unsigned(g.n[1]), g.inv_nxy);
+        const unsigned in = unsigned(j) - z * (unsigned(g.n[0]) * unsigned(g.n[1]));
+        const unsigned y = udiv_exact(in, unsigned(g.n[0]), g.inv_n[0]);
+        return Voxel{int(in - y * unsigned(g.n[0])), int(y), int(z)};
+    };
+    int vr[kBinRegs];
+    float cr[kBinRegs];
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kBinRegs; ++k) {
+        const int q = lane + k * kWave;
+        vr[k] = 0;
+        cr[k] = 0.f;
+        if (finite && q < len) {
+            vr[k] = rows.vox[a + q];
+            cr[k] = S::get(chord[a + q]);
+        }
+    }
+    int axis = 0;
+    if (fe > fa) {
+        const int j0 = rows.vox[fa] & 0x7FFFFFFF, j1 = rows.vox[fe - 1] & 0x7FFFFFFF;
+        if (j0 < nvox && j1 < nvox) {
+            const Voxel v0 = decode(j0), v1 = decode(j1);
+            axis = abs(v1.x - v0.x) >= abs(v1.y - v0.y) ? 0 : 1;
+        }
+    }
+    if (row == 0 && lane == 0) *axis_out = axis;
+    const int cb = it.packed ? g.n[2] : 1, cz = it.packed ? 1 : axis ? g.n[0] : g.n[1];
+    // piece by piece: the gather, and where slabs start
+    float xr[kBinRegs];
+    unsigned long long starts[kBinRegs + 1];
+    double dot = 0.0;
+    bool up = false, down = false, met = false;
+    int before = -1;
+#pragma unroll
+    for (int k = 0; k < kBinRegs; ++k) {
+        starts[k] = ~0ull;
+        xr[k] = 0.f;
+        if (!finite || k * kWave >= len) continue;
+        const bool on = lane + k * kWave < len;
+        int j = vr[k] & 0x7FFFFFFF;
+        if (j >= nvox) {  // rows built for another plan: chord 0 and voxel 0
+            bad = true;
+            j = vr[k] = 0;
+            cr[k] = 0.f;
+        }
+        const Voxel v = decode(j);
+        if (on) xr[k] = it.value(it.at(v.x, v.y, v.z));
+        const int slab = axis ? v.y : v.x, prev = lane_before(slab, before);
+        const bool inner = on && (k > 0 || lane > 0);
+        up |= inner && slab > prev;
+        down |= inner && slab < prev;
+        const bool start = !on || !inner || slab != prev;
+        met |= on && start && vr[k] >= 0;
+        starts[k] = __ballot(start);
+        before = lane_value(slab, kWave - 1);
+    }
+    starts[kBinRegs] = ~0ull;
+#pragma unroll
+    for (int k = 0; k < kBinRegs; ++k)
+        if (finite && lane + k * kWave < len) dot += double(cr[k]) * double(xr[k]);
+    for (int q = lane + kBinRegs * kWave; finite && q < len; q += kWave) {
+        const int j = rows.vox[a + q] & 0x7FFFFFFF;
+        if (j < nvox) {
+            const Voxel v = decode(j);
+            dot += double(S::get(chord[a + q])) * double(it.value(it.at(v.x, v.y, v.z)));
+        } else {
+            bad = true;
+        }
+    }
+    if (bad) raise_status(status, PCT_DEV_BAD_ROW);
+    dot = group_sum<kWave>(dot);
+    const bool skip = !finite || !(n2 > 0.0);
+    const double rho = skip ? 0.0 : lambda * (bi - dot) / n2;
+    if (lane == 0) {
+        bins.rho[row] = skip ? __longlong_as_double(static_cast<long long>(kSkipRow)) : rho;
+        bins.rowmax[row] = 0.f;  // sums of stored rows are not bounded
+    }
+    if (skip) return;
+    const bool direct = len > kBinRegs * kWave || __any(met) || (__any(up) && __any(down));
+    const unsigned cap = unsigned(bins.cap), slabs = unsigned(bins.nslab), tag = bins.epoch << bins.cell_bits;
+    int run = 0;  // pieces of the slab that the round before ended in
+    bool spilled = false;
+#pragma unroll
+    for (int k = 0; k < kBinRegs; ++k) {
+        if (k * kWave >= len) continue;
+        const unsigned long long below = starts[k] & (~0ull >> (kWave - 1 - lane));
+        const unsigned long long above = lane == kWave - 1 ? 0ull : starts[k] & (~0ull << (lane + 1));
+        const int rank = below != 0ull ? lane - (kWave - 1 - __clzll(below)) : run + lane;
+        const int rest = starts[k + 1] != 0ull ? __ffsll(static_cast<long long>(starts[k + 1])) - 1 : kWave;
+        const int more = above != 0ull ? __ffsll(static_cast<long long>(above)) - 2 - lane : kWave - 1 - lane + rest;
+        run = starts[k] != 0ull ? 1 + __clzll(starts[k]) : run + kWave;
+        if (lane + k * kWave >= len) continue;
+        const Voxel v = decode(vr[k] & 0x7FFFFFFF);
+        if (direct || rank >= kBinCap) {
+            atomicAdd(ovf + it.at(v.x, v.y, v.z), pack_contribution(rho * double(cr[k]), vr[k] < 0, status));
+            spilled = true;
+            continue;
+        }
+        const unsigned p = unsigned(axis ? v.y : v.x) * cap + unsigned(row);
+        const unsigned cell = unsigned((axis ? v.x : v.y) * cb + v.z * cz);
+        BinEntry *to = rank == 0 ? bins.e0 + p : bins.ek + (unsigned(rank - 1) * slabs * cap + p);
+        const unsigned word = rank == 0 ? cell | tag | unsigned(min(more, 3)) << 30
+                                        : cell | (vr[k] < 0 ? kFirstBit : 0u);
+        *to = BinEntry{word, cr[k]};
+    }
+    for (int q = lane + kBinRegs * kWave; q < len; q += kWave) {
+        const int v = rows.vox[a + q], j = v & 0x7FFFFFFF;
+        if (j >= nvox) continue;
+        const Voxel w = decode(j);
+        atomicAdd(ovf + it.at(w.x, w.y, w.z),
+                  pack_contribution(rho * double(S::get(chord[a + q])), v < 0, status));
+        spilled = true;
+    }
+    if (__any(spilled) && lane == 0) *ovf_flag = 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -2020,6 +2173,129 @@ static inline uint64_t bits_of(double v)
     return u;
 }
 
+// ---- binned schedule, host side ----------------------------------------------
+struct BinnedCall {
+    bool ok = false;  // the workspace holds the slab bins of a block and a slab's window fits the LDS budget
+    bool packed = false, comp = false;
+    BinsDev bins{};
+    IterateDev it{};
+    size_t nrow = 0, win_lds = 0;
+    unsigned epochs = 0;
+    int chunk = 0, chunks = 0;
+    int *ovf_flag = nullptr;
+    unsigned long long *ovf = nullptr;
+    unsigned *status = nullptr;
+};
+
+static BinnedCall binned_call(const pct_plan &pl, float *x, void *ws, size_t ws_bytes, int64_t block, int64_t steps,
+                              bool comp)
+{
+    BinnedCall B;
+    const Layout L = layout_for(pl.nvox, pl.K, PCT_F32);
+    const int nslab = std::max(pl.grid.nx, pl.grid.ny);
+    const int64_t cells = int64_t(nslab) * pl.grid.nz;
+    int cell_bits = 1;  // of a slab's cells and the value that says none
+    while ((int64_t(1) << cell_bits) <= cells) ++cell_bits;
+    B.ok = nslab <= 8192 && block <= kBinMaxRows && pl.nvox < (int64_t(1) << 30) && cell_bits < 30 &&
+           ws_bytes >= L.total + bin_bytes(block, nslab);
+    if (!B.ok) return B;
+    B.comp = comp;
+    // the packed iterate costs two copies of the volume a call (about 8 us each
+    // at 256 x 256 x 64) and saves the commits of x-dominant blocks their strided
+    // lines (30 against 26 us each before the other changes to the commit)
+    B.packed = steps >= kPackBlocks && pl.nvox < (int64_t(1) << 29);
+    B.it.packed = B.packed ? 1 : 0;
+    B.it.x = reinterpret_cast<float *>(B.packed ? static_cast<void *>(wsb(ws) + L.x1) : static_cast<void *>(x));
+    B.it.lo = reinterpret_cast<float *>(wsb(ws) + L.lo);
+    B.it.sx = B.packed ? pl.grid.nz : 1;
+    B.it.sy = B.packed ? pl.grid.nx * pl.grid.nz : pl.grid.nx;
+    B.it.sz = B.packed ? 1 : pl.grid.nx * pl.grid.ny;
+    const int64_t cap = bin_rows(block);
+    B.nrow = size_t(nslab) * size_t(cap);
+    B.bins.e0 = reinterpret_cast<BinEntry *>(wsb(ws) + L.total);
+    B.bins.ek = B.bins.e0 + B.nrow;
+    B.bins.rho = reinterpret_cast<double *>(B.bins.ek + B.nrow * (kBinCap - 1));
+    B.bins.rowmax = reinterpret_cast<float *>(B.bins.rho + cap);
+    B.bins.cap = int(cap);
+    B.bins.nslab = nslab;
+    B.bins.cell_bits = cell_bits;
+    B.epochs = (1u << (30 - cell_bits)) - 1u;
+    B.chunk = int(std::min<int64_t>(cells, slab_window_words()));
+    B.chunks = int((cells + B.chunk - 1) / B.chunk);
+    B.win_lds = size_t(B.chunk) * sizeof(unsigned long long) + kListBytes;
+    int *hdr = reinterpret_cast<int *>(wsb(ws) + L.hdr);
+    B.ovf_flag = hdr + kHdrOvf;
+    B.ovf = reinterpret_cast<unsigned long long *>(wsb(ws) + L.acc);
+    B.status = reinterpret_cast<unsigned *>(hdr) + kHdrStatus;
+    return B;
+}
+
+// One sweep.  bin(s, lo, hi, bins, parity, e0, e1) launches the block's first
+// kernel, timed by the events when there are any; stored_axis: where that kernel
+// leaves the block's axis, or nullptr (the records tell).
+template <class Bin>
+static void enqueue_binned(pct_plan &pl, const BinnedCall &B, const ProtonsDev &p, const pct_drop_opts &o, int64_t n,
+                           hipStream_t s, bool record_events, int64_t every, const int *stored_axis,
+                           const GateDev &gate, Bin &&bin)
+{
+    BinsDev bins = B.bins;
+    const GridDev g = grid_dev(pl.grid);
+    auto commit = B.packed ? &k_slab_commit<true> : &k_slab_commit<false>;
+    int64_t seq = 0;
+    for (int64_t t = o.block_begin; t < o.block_end; ++t, ++seq) {
+        const int64_t lo = t * o.block;
+        const int64_t hi = std::min<int64_t>(n, lo + o.block);
+        const int par = int(seq & 1);
+        bins.epoch = unsigned(seq % B.epochs) + 1u;
+        if (bins.epoch == 1u)
+            hipLaunchKernelGGL(k_bins_begin, dim3(unsigned(std::min<size_t>(1024, (B.nrow / 2 + 255) / 256 + 1))),
+                               dim3(256), 0, s, bins.e0, B.nrow, B.ovf_flag, seq == 0 ? 1 : 0);
+        // sampled blocks: both kernels timed by their own launch events
+        const bool sample = record_events && (seq % every == 0) && pl.prof_used[0] < kProfSamples;
+        hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
+        if (sample) {
+            e[0] = prof_event(pl, 0, 2 * pl.prof_used[0]);
+            e[1] = prof_event(pl, 0, 2 * pl.prof_used[0] + 1);
+            e[2] = prof_event(pl, 1, 2 * pl.prof_used[1]);
+            e[3] = prof_event(pl, 1, 2 * pl.prof_used[1] + 1);
+            pl.prof_used[0]++;
+            pl.prof_used[1]++;
+        }
+        bin(s, lo, hi, bins, par, e[0], e[1]);
+        const dim3 grid(unsigned(bins.nslab * B.chunks));
+        if (sample)
+            hipExtLaunchKernelGGL(commit, grid, dim3(kSlabWG), uint32_t(B.win_lds), s, e[2], e[3], 0u, p, lo,
+                                  int(hi - lo), bins, par, B.ovf, B.ovf_flag, B.it, g, B.chunk, B.chunks,
+                                  B.comp ? 1 : 0, stored_axis, B.status, gate);
+        else
+            hipLaunchKernelGGL(commit, grid, dim3(kSlabWG), B.win_lds, s, p, lo, int(hi - lo), bins, par, B.ovf,
+                               B.ovf_flag, B.it, g, B.chunk, B.chunks, B.comp ? 1 : 0, stored_axis, B.status, gate);
+    }
+}
+
+// Around the sweeps of a call: the packed iterate formed and taken back, or the
+// compensation words zeroed (they start at zero in every call, outside the graph).
+static void binned_begin(const pct_plan &pl, const BinnedCall &B, float *x, hipStream_t s)
+{
+    const dim3 tiles(unsigned((pl.grid.nx + kTile - 1) / kTile), unsigned(std::min(pl.grid.ny, 65535)),
+                     unsigned((pl.grid.nz + kTile - 1) / kTile));
+    if (B.packed)
+        hipLaunchKernelGGL(k_pack_iterate, tiles, dim3(256), 0, s, x, reinterpret_cast<float2 *>(B.it.x),
+                           grid_dev(pl.grid));
+    else if (B.comp)
+        hipLaunchKernelGGL(k_zero_f32, dim3(unsigned(std::min<int64_t>(2048, (pl.nvox + 255) / 256))), dim3(256), 0, s,
+                           B.it.lo, pl.nvox);
+}
+static int binned_end(const pct_plan &pl, const BinnedCall &B, float *x, hipStream_t s)
+{
+    if (!B.packed) return hipSuccess;
+    const dim3 tiles(unsigned((pl.grid.nx + kTile - 1) / kTile), unsigned(std::min(pl.grid.ny, 65535)),
+                     unsigned((pl.grid.nz + kTile - 1) / kTile));
+    hipLaunchKernelGGL(k_unpack_iterate, tiles, dim3(256), 0, s, x, reinterpret_cast<const float2 *>(B.it.x),
+                       grid_dev(pl.grid));
+    return hipGetLastError();
+}
+
 template <typename T, int CHORD, bool HULL>
 static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *b, T *x,
                      const pct_drop_opts &o, void *ws, size_t ws_bytes, hipStream_t s)
@@ -2077,89 +2353,29 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
             }
         }
     };
-    // binned schedule (FP32 default): the workspace holds the slab bins of a
-    // block and a slab's window fits the LDS budget
-    const int nslab = std::max(pl.grid.nx, pl.grid.ny);
-    const int win_words = sizeof(T) == 4 ? slab_window_words() : 0;
-    int cell_bits = 1;  // of a slab's cells and the value that says none
-    while ((int64_t(1) << cell_bits) <= int64_t(nslab) * pl.grid.nz) ++cell_bits;
-    const bool binned = sizeof(T) == 4 && lanes > 1 && !(o.flags & (PCT_DROP_SEPARATE_COMMIT | PCT_DROP_FUSED_COMMIT)) &&
-                        nslab <= 8192 && o.block <= kBinMaxRows && pl.nvox < (int64_t(1) << 30) && cell_bits < 30 &&
-                        ws_bytes >= L.total + bin_bytes(o.block, nslab);
-    const bool comp = binned && !(o.flags & PCT_DROP_NO_COMPENSATION);
-    // the packed iterate costs two copies of the volume a call (about 8 us each
-    // at 256 x 256 x 64) and saves the commits of x-dominant blocks their strided
-    // lines (30 against 26 us each before the other changes to the commit)
-    const bool packed = binned && nblk * o.n_iter >= kPackBlocks && pl.nvox < (int64_t(1) << 29);
-    IterateDev it{};
-    if (binned) {
-        it.packed = packed ? 1 : 0;
-        it.x = reinterpret_cast<float *>(packed ? static_cast<void *>(wsb(ws) + L.x1) : static_cast<void *>(x));
-        it.lo = reinterpret_cast<float *>(wsb(ws) + L.lo);
-        it.sx = packed ? pl.grid.nz : 1;
-        it.sy = packed ? pl.grid.nx * pl.grid.nz : pl.grid.nx;
-        it.sz = packed ? 1 : pl.grid.nx * pl.grid.ny;
-    }
+    BinnedCall B;  // FP32 default
+    if (sizeof(T) == 4 && lanes > 1 && !(o.flags & (PCT_DROP_SEPARATE_COMMIT | PCT_DROP_FUSED_COMMIT)))
+        B = binned_call(pl, reinterpret_cast<float *>(x), ws, ws_bytes, o.block, nblk * o.n_iter,
+                        !(o.flags & PCT_DROP_NO_COMPENSATION));
+    const bool binned = B.ok;
     const bool fused = sizeof(T) == 4 && lanes > 1 && !(o.flags & PCT_DROP_SEPARATE_COMMIT) && !binned && !cancellable;
     auto sweep = [&](hipStream_t s, bool record_events) {
         if constexpr (sizeof(T) == 4) {
             if (binned) {
-                BinsDev bins;
-                const int64_t cap = bin_rows(o.block);
-                char *bbase = wsb(ws) + L.total;
-                const size_t nrow = size_t(nslab) * size_t(cap);
-                bins.e0 = reinterpret_cast<BinEntry *>(bbase);
-                bins.ek = bins.e0 + nrow;
-                bins.rho = reinterpret_cast<double *>(bins.ek + nrow * (kBinCap - 1));
-                bins.rowmax = reinterpret_cast<float *>(bins.rho + cap);
-                bins.cap = int(cap);
-                bins.nslab = nslab;
-                bins.cell_bits = cell_bits;
-                const unsigned epochs = (1u << (30 - cell_bits)) - 1u;
-                int *ovf_flag = hdr + kHdrOvf;
-                unsigned long long *ovf = static_cast<unsigned long long *>(acc);
-                const int64_t cells = int64_t(nslab) * pl.grid.nz;
-                const int chunk = int(std::min<int64_t>(cells, win_words));
-                const int chunks = int((cells + chunk - 1) / chunk);
-                const size_t win_lds = size_t(chunk) * sizeof(unsigned long long) + kListBytes;
-                auto commit = packed ? &k_slab_commit<true> : &k_slab_commit<false>;
-                int64_t seq = 0;
-                for (int64_t t = o.block_begin; t < o.block_end; ++t, ++seq) {
-                    const int64_t lo = t * o.block;
-                    const int64_t hi = std::min<int64_t>(n, lo + o.block);
-                    const int par = int(seq & 1);
-                    bins.epoch = unsigned(seq % epochs) + 1u;
-                    if (bins.epoch == 1u)
-                        hipLaunchKernelGGL(k_bins_begin, dim3(unsigned(std::min<size_t>(1024, (nrow / 2 + 255) / 256 + 1))),
-                                           dim3(256), 0, s, bins.e0, nrow, ovf_flag, seq == 0 ? 1 : 0);
-                    // sampled blocks: both kernels timed by their own launch events
-                    const bool sample = record_events && (seq % every == 0) && pl.prof_used[0] < kProfSamples;
-                    hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
-                    if (sample) {
-                        e[0] = prof_event(pl, 0, 2 * pl.prof_used[0]);
-                        e[1] = prof_event(pl, 0, 2 * pl.prof_used[0] + 1);
-                        e[2] = prof_event(pl, 1, 2 * pl.prof_used[1]);
-                        e[3] = prof_event(pl, 1, 2 * pl.prof_used[1] + 1);
-                        pl.prof_used[0]++;
-                        pl.prof_used[1]++;
-                    }
-                    const dim3 grid(row_grid(hi - lo));
-                    if (sample)
-                        hipExtLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave), uint32_t(rec_lds), s, e[0],
-                                              e[1], 0u, p, b, it, bins, ovf, ovf_flag + par, src, g, lo, hi,
-                                              o.lambda, status, gate.halt, span);
-                    else
-                        hipLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave), rec_lds, s, p, b, it, bins, ovf,
-                                           ovf_flag + par, src, g, lo, hi, o.lambda, status, gate.halt, span);
-                    if (sample)
-                        hipExtLaunchKernelGGL(commit, dim3(unsigned(nslab * chunks)), dim3(kSlabWG), uint32_t(win_lds),
-                                              s, e[2], e[3], 0u, p, lo, int(hi - lo), bins, par, ovf, ovf_flag, it, g,
-                                              chunk, chunks, comp ? 1 : 0, status, gate);
-                    else
-                        hipLaunchKernelGGL(commit, dim3(unsigned(nslab * chunks)), dim3(kSlabWG), win_lds, s, p, lo,
-                                           int(hi - lo), bins, par, ovf, ovf_flag, it, g, chunk, chunks, comp ? 1 : 0,
-                                           status, gate);
-                }
+                enqueue_binned(pl, B, p, o, n, s, record_events, every, nullptr, gate,
+                               [&](hipStream_t s, int64_t lo, int64_t hi, const BinsDev &bins, int par, hipEvent_t e0,
+                                   hipEvent_t e1) {
+                                   const dim3 grid(row_grid(hi - lo));
+                                   if (e0)
+                                       hipExtLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave),
+                                                             uint32_t(rec_lds), s, e0, e1, 0u, p, b, B.it, bins, B.ovf,
+                                                             B.ovf_flag + par, src, g, lo, hi, o.lambda, status,
+                                                             gate.halt, span);
+                                   else
+                                       hipLaunchKernelGGL((k_drop_bin<CHORD, HULL>), grid, dim3(kWave), rec_lds, s, p,
+                                                          b, B.it, bins, B.ovf, B.ovf_flag + par, src, g, lo, hi,
+                                                          o.lambda, status, gate.halt, span);
+                               });
                 return;
             }
             if (fused) {
@@ -2185,26 +2401,15 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
         reinterpret_cast<uint64_t>(x),        reinterpret_cast<uint64_t>(ws),
         uint64_t(n), uint64_t(o.block), uint64_t(o.block_begin), uint64_t(o.block_end),
         uint64_t(o.dtype), uint64_t(CHORD), uint64_t(lanes),
-        uint64_t(fused) + 4 * uint64_t(binned) + 8 * uint64_t(comp) + 16 * uint64_t(cancellable) +
-            32 * uint64_t(det) + 64 * uint64_t(packed),
+        uint64_t(fused) + 4 * uint64_t(binned) + 8 * uint64_t(B.comp) + 16 * uint64_t(cancellable) +
+            32 * uint64_t(det) + 64 * uint64_t(B.packed),
         bits_of(o.lambda),
         0};
     if (cancellable) hipLaunchKernelGGL(k_gate_begin, dim3(1), dim3(64), 0, s, gate);
-    const dim3 tiles(unsigned((pl.grid.nx + kTile - 1) / kTile), unsigned(std::min(pl.grid.ny, 65535)),
-                     unsigned((pl.grid.nz + kTile - 1) / kTile));
-    if (packed) {
-        hipLaunchKernelGGL(k_pack_iterate, tiles, dim3(256), 0, s, reinterpret_cast<const float *>(x),
-                           reinterpret_cast<float2 *>(it.x), g);
-    } else if (comp) {
-        // the compensation words start at zero in every call (outside the graph)
-        hipLaunchKernelGGL(k_zero_f32, dim3(unsigned(std::min<int64_t>(2048, (pl.nvox + 255) / 256))), dim3(256), 0, s,
-                           reinterpret_cast<float *>(wsb(ws) + L.lo), pl.nvox);
-    }
+    if (binned) binned_begin(pl, B, reinterpret_cast<float *>(x), s);
     const int st = run_sweeps(pl, key, use_graph, o.n_iter, prof, s, sweep);
-    if (!packed || st != hipSuccess) return st;
-    hipLaunchKernelGGL(k_unpack_iterate, tiles, dim3(256), 0, s, reinterpret_cast<float *>(x),
-                       reinterpret_cast<const float2 *>(it.x), g);
-    return hipGetLastError();
+    if (!binned || st != hipSuccess) return st;
+    return binned_end(pl, B, reinterpret_cast<float *>(x), s);
 }
 
 template <typename T>
@@ -2369,7 +2574,7 @@ static void launch_rows_fused(int lanes, hipStream_t s, const RowsDev &rows, con
 }
 
 int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *x, const pct_drop_opts &o, void *ws,
-                     void *stream)
+                     size_t ws_bytes, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool prof = (o.flags & PCT_DROP_PROFILE) != 0;
@@ -2384,7 +2589,36 @@ int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     const RowsDev rd{reinterpret_cast<const long long *>(rows.offsets), rows.vox, rows.chord, rows.n2};
     const int64_t n = rows.n;
+    // by bins unless the call names its lanes per row: the same sums, so the same x
+    // (a 3200-row block of the 200 x 200 x 32 scan: 29.4 us against 33.2)
+    BinnedCall B;
+    if (o.lanes == 0) B = binned_call(pl, x, ws, ws_bytes, o.block, nblk * o.n_iter, false);
+    int *axis = reinterpret_cast<int *>(wsb(ws) + L.hdr) + kHdrAxis;
+    const GridDev g = grid_dev(pl.grid);
+    auto bin = [&](auto chord, hipStream_t s, int64_t lo, int64_t hi, const BinsDev &bins, int par, hipEvent_t e0,
+                   hipEvent_t e1) {
+        constexpr int CT = decltype(chord)::value;
+        if (e0)
+            hipExtLaunchKernelGGL(k_rows_bin<CT>, dim3(row_grid(hi - lo)), dim3(kWave), 0u, s, e0, e1, 0u, rd, b, B.it,
+                                  bins, B.ovf, B.ovf_flag + par, axis, g, lo, hi, o.lambda, status, int(pl.nvox));
+        else
+            hipLaunchKernelGGL(k_rows_bin<CT>, dim3(row_grid(hi - lo)), dim3(kWave), 0, s, rd, b, B.it, bins, B.ovf,
+                               B.ovf_flag + par, axis, g, lo, hi, o.lambda, status, int(pl.nvox));
+    };
     auto sweep = [&](hipStream_t s, bool record_events) {
+        if (B.ok) {
+            enqueue_binned(pl, B, ProtonsDev{}, o, n, s, record_events, every, axis, GateDev{},
+                           [&](hipStream_t s, int64_t lo, int64_t hi, const BinsDev &bins, int par, hipEvent_t e0,
+                               hipEvent_t e1) {
+                               if (rows.chord_type == PCT_CHORD_F16)
+                                   bin(std::integral_constant<int, PCT_CHORD_F16>{}, s, lo, hi, bins, par, e0, e1);
+                               else if (rows.chord_type == PCT_CHORD_BF16)
+                                   bin(std::integral_constant<int, PCT_CHORD_BF16>{}, s, lo, hi, bins, par, e0, e1);
+                               else
+                                   bin(std::integral_constant<int, PCT_CHORD_F32>{}, s, lo, hi, bins, par, e0, e1);
+                           });
+            return;
+        }
         const FusedBufs F = fused_bufs(pl, ws, x);
         enqueue_fused(pl, F, o.block_begin, o.block_end, o.block, n, s, record_events, every,
                       [&](hipStream_t s, int64_t, int64_t lo, int64_t hi, const FusedStep &f) {
@@ -2408,8 +2642,11 @@ int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *
                                  uint64_t(o.block),                        uint64_t(o.block_begin),
                                  uint64_t(o.block_end),                    uint64_t(rows.chord_type),
                                  uint64_t(lanes),                          bits_of(o.lambda),
-                                 1};
-    return run_sweeps(pl, key, use_graph, o.n_iter, prof, s, sweep);
+                                 uint64_t(B.ok) + 2 * uint64_t(B.packed), 1};
+    if (B.ok) binned_begin(pl, B, x, s);
+    const int st = run_sweeps(pl, key, use_graph, o.n_iter, prof, s, sweep);
+    if (!B.ok || st != hipSuccess) return st;
+    return binned_end(pl, B, x, s);
 }
 
 static int tv_into(const pct_plan &pl, const void *x, int dtype, double eps, double *value_dev, void *grad,
