@@ -601,7 +601,7 @@ static int sort_setup(const pct_plan *plan, const pct_sort_opts *o, SortDev &s)
     s.n_angles = o->n_angles;
     s.n_slabs = int32_t(ns);
     s.bits_s = bit_width(uint32_t(s.n_slabs - 1));
-    s.passes = (32 + s.bits_s + bit_width(uint32_t(s.n_angles)) + 7) / 8;
+    s.key_bits = 32 + s.bits_s + bit_width(uint32_t(s.n_angles));
     s.dphi = 2.0 * M_PI / double(o->n_angles);
     s.z0 = plan->grid.origin[2];
     s.slab = o->slab_mm;

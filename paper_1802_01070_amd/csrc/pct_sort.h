@@ -14,7 +14,7 @@ struct SortDev {
     int32_t n_angles;   // angle bins; n_angles itself marks a non-finite record
     int32_t n_slabs;    // slabs of the entry height v_in
     int32_t bits_s;     // key bits of the slab field
-    int32_t passes;     // 8-bit digit passes over the key
+    int32_t key_bits;   // of the whole key
     double dphi;        // 2 pi / n_angles
     double z0;          // lower z edge of the grid
     double slab;        // slab thickness (mm)
@@ -26,7 +26,7 @@ struct SortLayout {
     size_t rec;         // n packed records of 10 floats (9 fields, then b)
     size_t total;
     int64_t n_tiles;    // tiles of kSortTile records
-    int64_t n_hist;     // 256 * n_tiles digit counts
+    int64_t n_hist;     // digit counts, one per digit and tile
     int64_t n_parts;    // partial sums of the count scan
 };
 

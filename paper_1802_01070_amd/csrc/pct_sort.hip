@@ -8,23 +8,30 @@
 // (ord: the FP32 bit pattern mapped so that unsigned order is numeric order,
 // with -0 taken as +0; a non-finite record gets a = n_angles and sorts last),
 // and the (key, position) pairs go through a least-significant-digit radix
-// sort with 8-bit digits, one pass per digit the key uses:
+// sort with 9-bit digits, one pass per digit the key uses:
 //
-//   k_sort_keys         one thread per record: the key, the position, and a
-//                       packed 40-byte copy of the record (9 fields and b)
-//   k_sort_hist         one workgroup per tile of 2048 pairs: digit counts in
+//   k_sort_keys         one thread per record: the key, and a packed 40-byte copy
+//                       of the record (9 fields and b)
+//   k_sort_hist         one workgroup per tile of 4096 pairs: digit counts in
 //                       LDS, written digit-major (count of digit d in tile g at
 //                       d * n_tiles + g), so that one exclusive scan of the
 //                       counts gives every (digit, tile) its output offset
-//   k_sort_count_*      that scan: partial sums of 4096 counts, a one-workgroup
-//                       scan of the partials, then the scan of each segment
-//   k_sort_scatter      one workgroup per tile, 8 rounds of 256 pairs in input
+//   k_sort_count_*      that scan: partial sums of 4096 counts, then the scan of
+//                       each segment from the sum of the partials before it
+//   k_sort_scatter      one workgroup per tile, a wave per 512 pairs in input
 //                       order: a lane's rank among the lanes of its wave with
-//                       the same digit comes from 8 ballots (one per digit
-//                       bit), the counts of earlier waves and rounds from LDS;
-//                       equal digits keep their input order (stable).  The
-//                       tile's pairs are staged in LDS in digit order and
-//                       written out as one run per digit
+//                       the same digit comes from 9 ballots (one per digit
+//                       bit), the count of the wave's earlier pairs from LDS, so
+//                       the waves meet only once, to add up their counts; equal
+//                       digits keep their input order (stable).  The tile's pairs
+//                       are staged in LDS in digit order and written out as one
+//                       run per digit
+//
+// A pass needs only the digits to come: the first pass takes the position from
+// the place and, where what is left of the key and the position fit 64 bits (a
+// 45-bit key and 2^28 records do), the later ones move one word a record instead of
+// a key and a position; the last writes the position alone.
+//
 //   k_sort_gather       one thread per output record: copy the record from its
 //                       input position, read from the packed copy (the angles
 //                       of a continuous scan are uniform in acquisition order,
@@ -47,11 +54,15 @@ namespace pct {
 namespace {
 
 constexpr int kSortWG = 256;
-constexpr int kSortWaves = kSortWG / 64;
+constexpr int kRadixBits = 9;
+constexpr int kDigits = 1 << kRadixBits;
+constexpr int kRadixWG = 512;                                   // = kDigits: a thread per digit
+constexpr int kRadixWaves = kRadixWG / 64;
 constexpr int kSortRounds = 8;
-constexpr int64_t kSortTile = int64_t(kSortWG) * kSortRounds;   // records per tile
+constexpr int64_t kSortTile = int64_t(kRadixWG) * kSortRounds;  // records per tile
 constexpr int kScanPer = 16;
 constexpr int64_t kScanSeg = int64_t(kSortWG) * kScanPer;       // counts per scan workgroup
+static_assert(kRadixWG == kDigits && kSortRounds * 64 < 65536, "a thread per digit, 16-bit counts");
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -74,7 +85,7 @@ __device__ inline unsigned long long sort_key(const SortDev &s, float phi32, flo
 }
 
 __global__ void __launch_bounds__(kSortWG) k_sort_keys(ProtonsDev p, const float *b, int64_t n, SortDev s,
-                                                       unsigned long long *key, uint32_t *idx, float *rec)
+                                                       unsigned long long *key, float *rec)
 {
     // the workgroup's packed records are staged in LDS and written out as
     // 16-byte stores over its contiguous 10 * 256 floats
@@ -85,7 +96,6 @@ __global__ void __launch_bounds__(kSortWG) k_sort_keys(ProtonsDev p, const float
     if (i < n) {
         const float t = p.t_in[i], v = p.v_in[i], phi = p.gantry[i];
         key[i] = sort_key(s, phi, v, t);
-        idx[i] = uint32_t(i);
         float *r = st + 10 * threadIdx.x;
         r[0] = t;
         r[1] = v;
@@ -106,43 +116,65 @@ __global__ void __launch_bounds__(kSortWG) k_sort_keys(ProtonsDev p, const float
     for (int q = (nf / 4) * 4 + threadIdx.x; q < nf; q += kSortWG) out[q] = st[q];
 }
 
-__global__ void __launch_bounds__(kSortWG) k_sort_hist(const unsigned long long *key, int64_t n, int shift,
-                                                       int64_t n_tiles, uint32_t *hist)
+// Tile of a workgroup (n_tiles or more: none).  Workgroup w runs on XCD w mod 8, and
+// what neighbouring tiles write lies side by side (their counts of a digit, their
+// runs), so each XCD takes a contiguous run of tiles and its L2 fills the lines.
+__device__ inline int64_t tile_of_workgroup(int64_t n_tiles)
 {
-    __shared__ uint32_t h[256];
+    return int64_t(blockIdx.x % 8) * ((n_tiles + 7) / 8) + blockIdx.x / 8;
+}
+unsigned tile_grid(int64_t n_tiles) { return unsigned(8 * ((n_tiles + 7) / 8)); }
+
+__global__ void __launch_bounds__(kRadixWG) k_sort_hist(const unsigned long long *key, int64_t n, int shift,
+                                                        int64_t n_tiles, uint32_t *hist)
+{
+    __shared__ uint32_t h[kDigits];
+    const int64_t tile = tile_of_workgroup(n_tiles), tile0 = tile * kSortTile;
+    if (tile >= n_tiles) return;
+    unsigned long long k[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int64_t i = tile0 + int64_t(r) * kRadixWG + threadIdx.x;
+        k[r] = i < n ? key[i] : 0ull;
+    }
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t tile0 = int64_t(blockIdx.x) * kSortTile;
+#pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const int64_t i = tile0 + int64_t(r) * kSortWG + threadIdx.x;
-        if (i < n) atomicAdd(&h[unsigned(key[i] >> shift) & 255u], 1u);
+        const int64_t i = tile0 + int64_t(r) * kRadixWG + threadIdx.x;
+        if (i < n) atomicAdd(&h[unsigned(k[r] >> shift) & unsigned(kDigits - 1)], 1u);
     }
     __syncthreads();
-    hist[int64_t(threadIdx.x) * n_tiles + blockIdx.x] = h[threadIdx.x];
+    hist[int64_t(threadIdx.x) * n_tiles + tile] = h[threadIdx.x];
 }
 
-// Exclusive prefix sum of v over the workgroup in thread order; total gets
-// the sum.  lds: kSortWG words.
+// Exclusive prefix sum of v over a workgroup of WG threads in thread order; total
+// gets the sum.  lds: WG / 64 words.
+template <int WG>
 __device__ inline uint32_t wg_exclusive_scan(uint32_t v, uint32_t *lds, uint32_t &total)
 {
-    const int t = threadIdx.x;
-    lds[t] = v;
-    __syncthreads();
-    for (int off = 1; off < kSortWG; off <<= 1) {
-        const uint32_t a = t >= off ? lds[t - off] : 0u;
-        __syncthreads();
-        lds[t] += a;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t a = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += a;
     }
-    const uint32_t incl = lds[t];
-    total = lds[kSortWG - 1];
+    if (lane == 63) lds[wave] = incl;
     __syncthreads();
-    return incl - v;
+    uint32_t before = 0;
+    total = 0;
+    for (int w = 0; w < WG / 64; ++w) {
+        const uint32_t c = lds[w];
+        before += w < wave ? c : 0u;
+        total += c;
+    }
+    __syncthreads();
+    return before + incl - v;
 }
 
 __global__ void __launch_bounds__(kSortWG) k_sort_count_reduce(const uint32_t *hist, int64_t nh, uint32_t *part)
 {
-    __shared__ uint32_t lds[kSortWG];
+    __shared__ uint32_t lds[kSortWG / 64];
     const int64_t seg = int64_t(blockIdx.x) * kScanSeg;
     uint32_t sum = 0;
     for (int j = 0; j < kScanPer; ++j) {
@@ -150,40 +182,25 @@ __global__ void __launch_bounds__(kSortWG) k_sort_count_reduce(const uint32_t *h
         if (e < nh) sum += hist[e];
     }
     uint32_t total;
-    wg_exclusive_scan(sum, lds, total);
+    wg_exclusive_scan<kSortWG>(sum, lds, total);
     if (threadIdx.x == 0) part[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(kSortWG) k_sort_count_top(uint32_t *part, int64_t np)
-{
-    __shared__ uint32_t lds[kSortWG];
-    const int64_t per = (np + kSortWG - 1) / kSortWG;
-    const int64_t lo = min(np, int64_t(threadIdx.x) * per);
-    const int64_t hi = min(np, lo + per);
-    uint32_t sum = 0;
-    for (int64_t e = lo; e < hi; ++e) sum += part[e];
-    uint32_t total;
-    uint32_t run = wg_exclusive_scan(sum, lds, total);
-    for (int64_t e = lo; e < hi; ++e) {
-        const uint32_t v = part[e];
-        part[e] = run;
-        run += v;
-    }
 }
 
 __global__ void __launch_bounds__(kSortWG) k_sort_count_down(uint32_t *hist, int64_t nh, const uint32_t *part)
 {
-    __shared__ uint32_t lds[kSortWG];
+    __shared__ uint32_t lds[kSortWG / 64];
     const int64_t first = int64_t(blockIdx.x) * kScanSeg + int64_t(threadIdx.x) * kScanPer;
     uint32_t v[kScanPer];
-    uint32_t sum = 0;
+    uint32_t sum = 0, mine = 0;
     for (int j = 0; j < kScanPer; ++j) {
         const int64_t e = first + j;
         v[j] = e < nh ? hist[e] : 0u;
         sum += v[j];
     }
-    uint32_t total;
-    uint32_t run = part[blockIdx.x] + wg_exclusive_scan(sum, lds, total);
+    for (unsigned q = threadIdx.x; q < blockIdx.x; q += kSortWG) mine += part[q];
+    uint32_t base, total;
+    wg_exclusive_scan<kSortWG>(mine, lds, base);
+    uint32_t run = base + wg_exclusive_scan<kSortWG>(sum, lds, total);
     for (int j = 0; j < kScanPer; ++j) {
         const int64_t e = first + j;
         if (e < nh) hist[e] = run;
@@ -191,77 +208,114 @@ __global__ void __launch_bounds__(kSortWG) k_sort_count_down(uint32_t *hist, int
     }
 }
 
-__global__ void __launch_bounds__(kSortWG) k_sort_scatter(const unsigned long long *key_in, const uint32_t *idx_in,
-                                                          int64_t n, int shift, int64_t n_tiles, const uint32_t *off,
-                                                          unsigned long long *key_out, uint32_t *idx_out)
+// One pass.  PACKED: the pairs are words of the key's digits to come above the
+// position (bits_n bits); idx_in is the place in the first pass (nullptr, raw
+// keys) and not used in later ones, and the last pass (key_out nullptr) writes
+// idx_out alone.  Otherwise key and position lie in two arrays, the position
+// being the place in the first pass.
+// Bound by its writes, runs of about eight words a digit: 56.7 us a pass of 1e7
+// records (160 MB), 63.6 with the tiles dealt to the XCDs in turn, and 18.1 for the
+// counts (23.3).  A 45-bit key takes five passes of 94 us; six of 8-bit digits,
+// each moving a key and a position and ranking its waves together round by round,
+// took 125 us each.
+template <bool PACKED>
+__global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long long *key_in, const uint32_t *idx_in,
+                                                           int64_t n, int shift, int bits_n, int64_t n_tiles,
+                                                           const uint32_t *off, unsigned long long *key_out,
+                                                           uint32_t *idx_out)
 {
-    __shared__ uint32_t base[256];                  // next output slot of each digit
-    __shared__ uint32_t first[256];                 // output slot of the tile's first pair of each digit
-    __shared__ uint32_t local[256];                 // tile-local start of each digit (pairs in digit order)
-    __shared__ uint32_t cnt[kSortWaves][256];       // this round's count per wave and digit
-    __shared__ unsigned long long skey[kSortTile];  // the tile's pairs, staged in digit order
-    __shared__ uint32_t sidx[kSortTile];
+    __shared__ uint32_t first[kDigits];                           // output slot of the tile's first pair of each digit
+    __shared__ uint32_t local[kDigits];                           // tile-local start of each digit (pairs in digit order)
+    __shared__ volatile unsigned short cnt[kRadixWaves][kDigits]; // pairs of each wave and digit
+    __shared__ unsigned long long skey[kSortTile];                // the tile's pairs, staged in digit order
+    __shared__ unsigned short sdigit[PACKED ? kSortTile : 1];     // (a whole key tells)
+    __shared__ uint32_t sidx[PACKED ? 1 : kSortTile];
+    __shared__ uint32_t lds[kRadixWaves];
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = t >> 6;
+    const int64_t tile = tile_of_workgroup(n_tiles);
+    if (tile >= n_tiles) return;
+    const int64_t i0 = tile * kSortTile + int64_t(wave) * (64 * kSortRounds) + lane;
+    unsigned long long k[kSortRounds];
+    uint32_t ix[kSortRounds], rank[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int64_t i = i0 + 64 * r;
+        k[r] = i < n ? key_in[i] : 0ull;
+        ix[r] = uint32_t(i);
+        if constexpr (!PACKED)
+            if (idx_in && i < n) ix[r] = idx_in[i];
+    }
     // pairs of digit t in this tile: the next offset of the scanned counts
     // (digit-major) minus this one; the last entry ends at n
-    const int64_t e = int64_t(t) * n_tiles + blockIdx.x;
+    const int64_t e = int64_t(t) * n_tiles + tile;
     const uint32_t o0 = off[e];
-    const uint32_t o1 = e + 1 < 256 * n_tiles ? off[e + 1] : uint32_t(n);
-    base[t] = o0;
-    first[t] = o0;
-    for (int w = 0; w < kSortWaves; ++w) cnt[w][t] = 0;
+    const uint32_t o1 = e + 1 < kDigits * n_tiles ? off[e + 1] : uint32_t(n);
+    for (int w = 0; w < kRadixWaves; ++w) cnt[w][t] = 0;
     uint32_t tile_total;
-    local[t] = wg_exclusive_scan(o1 - o0, cnt[0], tile_total);   // cnt[0] is scratch here, cleared below
-    cnt[0][t] = 0;
-    __syncthreads();
-    const int64_t tile0 = int64_t(blockIdx.x) * kSortTile;
+    first[t] = o0;
+    local[t] = wg_exclusive_scan<kRadixWG>(o1 - o0, lds, tile_total);
     const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
-        const int64_t i = tile0 + int64_t(r) * kSortWG + t;
-        const bool valid = i < n;
-        unsigned long long k = 0;
-        uint32_t ix = 0;
-        if (valid) {
-            k = key_in[i];
-            ix = idx_in[i];
-        }
-        const unsigned d = unsigned(k >> shift) & 255u;
+        const bool valid = i0 + 64 * r < n;
+        const unsigned d = unsigned(k[r] >> shift) & unsigned(kDigits - 1);
         unsigned long long same = __ballot(valid);
-        for (int bit = 0; bit < 8; ++bit) {
+#pragma unroll
+        for (int bit = 0; bit < kRadixBits; ++bit) {
             const unsigned long long m = __ballot((d >> bit) & 1u);
             same &= ((d >> bit) & 1u) ? m : ~m;
         }
-        const uint32_t rank = uint32_t(__popcll(same & below));
-        if (valid && rank == 0) cnt[wave][d] = uint32_t(__popcll(same));
-        __syncthreads();
-        if (valid) {
-            uint32_t dst = base[d] + rank;
-            for (int w = 0; w < wave; ++w) dst += cnt[w][d];
-            const uint32_t lp = local[d] + (dst - first[d]);
-            if (lp < uint32_t(kSortTile)) {
-                skey[lp] = k;
-                sidx[lp] = ix;
-            }
-        }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int w = 0; w < kSortWaves; ++w) {
-            add += cnt[w][t];
-            cnt[w][t] = 0;
-        }
-        base[t] += add;
-        __syncthreads();
+        // LDS accesses of a wave are carried out in order: every lane reads the
+        // count before the first lane of its digit raises it
+        const uint32_t lower = uint32_t(__popcll(same & below)), seen = cnt[wave][d];
+        rank[r] = seen + lower;
+        if (valid && lower == 0) cnt[wave][d] = static_cast<unsigned short>(seen + uint32_t(__popcll(same)));
     }
+    __syncthreads();
+    uint32_t run = local[t];
+    for (int w = 0; w < kRadixWaves; ++w) {
+        const uint32_t c = cnt[w][t];
+        cnt[w][t] = static_cast<unsigned short>(run);
+        run += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        if (i0 + 64 * r >= n) continue;
+        const unsigned long long rest = k[r] >> shift;
+        const unsigned d = unsigned(rest) & unsigned(kDigits - 1);
+        const uint32_t lp = cnt[wave][d] + rank[r];
+        if (lp >= uint32_t(kSortTile)) continue;
+        if constexpr (PACKED) {
+            sdigit[lp] = static_cast<unsigned short>(d);
+            const unsigned long long pos = shift == 0 ? static_cast<unsigned long long>(ix[r])
+                                                      : k[r] & ((1ull << bits_n) - 1ull);
+            skey[lp] = (rest >> kRadixBits) << bits_n | pos;
+        } else {
+            skey[lp] = k[r];
+            sidx[lp] = ix[r];
+        }
+    }
+    __syncthreads();
     // write the staged pairs out in digit order: consecutive threads write
     // consecutive slots of each digit's run
-    for (uint32_t q = uint32_t(t); q < tile_total && q < uint32_t(kSortTile); q += kSortWG) {
-        const unsigned long long k = skey[q];
-        const unsigned d = unsigned(k >> shift) & 255u;
+    for (uint32_t q = uint32_t(t); q < tile_total && q < uint32_t(kSortTile); q += kRadixWG) {
+        unsigned d;
+        if constexpr (PACKED)
+            d = sdigit[q];
+        else
+            d = unsigned(skey[q] >> shift) & unsigned(kDigits - 1);
         const uint32_t dst = first[d] + (q - local[d]);
-        if (int64_t(dst) < n) {
-            key_out[dst] = k;
+        if (int64_t(dst) >= n) continue;
+        if constexpr (PACKED) {
+            if (key_out)
+                key_out[dst] = skey[q];
+            else
+                idx_out[dst] = uint32_t(skey[q] & ((1ull << bits_n) - 1ull));
+        } else {
+            key_out[dst] = skey[q];
             idx_out[dst] = sidx[q];
         }
     }
@@ -295,7 +349,7 @@ SortLayout sort_layout(int64_t n)
 {
     SortLayout L{};
     L.n_tiles = (n + kSortTile - 1) / kSortTile;
-    L.n_hist = 256 * L.n_tiles;
+    L.n_hist = kDigits * L.n_tiles;
     L.n_parts = (L.n_hist + kScanSeg - 1) / kScanSeg;
     size_t o = 0;
     L.keys0 = o;
@@ -331,17 +385,28 @@ int launch_sort_scan(const SortDev &s, const ProtonsDev &p, int64_t n, const flo
     auto *part = reinterpret_cast<uint32_t *>(w + L.part);
     auto *rec = reinterpret_cast<float *>(w + L.rec);
     const unsigned blocks = unsigned((n + kSortWG - 1) / kSortWG);
-    hipLaunchKernelGGL(k_sort_keys, dim3(blocks), dim3(kSortWG), 0, st, p, b, n, s, k0, i0, rec);
-    for (int pass = 0; pass < s.passes; ++pass) {
-        const int shift = 8 * pass;
-        hipLaunchKernelGGL(k_sort_hist, dim3(unsigned(L.n_tiles)), dim3(kSortWG), 0, st, k0, n, shift, L.n_tiles,
+    auto bits = [](uint64_t v) {
+        int b = 0;
+        for (; v != 0; v >>= 1) ++b;
+        return b;
+    };
+    const int bits_n = bits(uint64_t(n - 1));
+    const int passes = (s.key_bits + kRadixBits - 1) / kRadixBits;
+    const bool packed = s.key_bits - kRadixBits + bits_n <= 64 && bits_n > 0;
+    hipLaunchKernelGGL(k_sort_keys, dim3(blocks), dim3(kSortWG), 0, st, p, b, n, s, k0, rec);
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = !packed ? kRadixBits * pass : pass > 0 ? bits_n : 0;
+        hipLaunchKernelGGL(k_sort_hist, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0, n, shift, L.n_tiles,
                            hist);
         hipLaunchKernelGGL(k_sort_count_reduce, dim3(unsigned(L.n_parts)), dim3(kSortWG), 0, st, hist, L.n_hist,
                            part);
-        hipLaunchKernelGGL(k_sort_count_top, dim3(1), dim3(kSortWG), 0, st, part, L.n_parts);
         hipLaunchKernelGGL(k_sort_count_down, dim3(unsigned(L.n_parts)), dim3(kSortWG), 0, st, hist, L.n_hist, part);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(unsigned(L.n_tiles)), dim3(kSortWG), 0, st, k0, i0, n, shift,
-                           L.n_tiles, hist, k1, i1);
+        if (packed)
+            hipLaunchKernelGGL(k_sort_scatter<true>, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0, nullptr, n,
+                               shift, bits_n, L.n_tiles, hist, pass + 1 < passes ? k1 : nullptr, i1);
+        else
+            hipLaunchKernelGGL(k_sort_scatter<false>, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0,
+                               pass > 0 ? i0 : nullptr, n, shift, bits_n, L.n_tiles, hist, k1, i1);
         std::swap(k0, k1);
         std::swap(i0, i1);
     }
