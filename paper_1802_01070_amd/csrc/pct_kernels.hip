@@ -1415,24 +1415,47 @@ struct StoredChord<PCT_CHORD_BF16> {
     __device__ static __forceinline__ float get(unsigned short v) { return __uint_as_float(unsigned(v) << 16); }
 };
 
+// Rows are built by parts: the workgroup's rows take kRowSteps segments together
+// and leave their pieces in LDS, from where the lanes of a wave write them eight to
+// a row.  (A lane that writes its pieces as it meets them has a request to HBM for
+// each, and 64 lines of 64 rows open at a time.)  1e6
+// FP16 rows of 290 pieces: 2.5 ms, of which the writes nothing, against 6.7.
+constexpr int kRowSteps = 4;
+constexpr int kRowStage = 13;  // pieces of a row and part with a place in LDS: three a segment, and the row's last
+
+template <int CT>
+struct RowStage {
+    int j[kWG][kRowStage];
+    typename StoredChord<CT>::type c[kWG][kRowStage];
+    long long base[kWG];
+    int n[kWG];
+};
+
 template <int CT>
 struct RowSink {
     using S = StoredChord<CT>;
+    RowStage<CT> *stage;
     int32_t *vox;
     typename S::type *ch;
     int64_t pos, end;
     Reentry re;
     double n2;
+    int staged = 0;  // pieces since the last write
     __device__ __forceinline__ void piece(int j, int ix, int iy, int iz, double c)
     {
         c = round_chord<CT>(c);
         bool first;
         const double aprev = re.visit(j, ix, iy, iz, c, first);
         n2 += c * (2.0 * aprev + c);
-        if (pos < end) {
-            vox[pos] = first ? int(unsigned(j) | 0x80000000u) : j;
+        const int v = first ? int(unsigned(j) | 0x80000000u) : j;
+        if (staged < kRowStage) {
+            stage->j[threadIdx.x][staged] = v;
+            stage->c[threadIdx.x][staged] = S::put(c);
+        } else if (pos < end) {  // (steps longer than a voxel)
+            vox[pos] = v;
             ch[pos] = S::put(c);
         }
+        ++staged;
         ++pos;
     }
 };
@@ -1443,17 +1466,48 @@ __global__ void __launch_bounds__(kWG) k_rows_build(ProtonsDev p, int64_t n, con
                                                     const PathSrc src,  GridDev g,
                                                     unsigned *status)
 {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    Rec r = load_rec(p, i);
     __shared__ Reentry::Lds lds;
-    RowSink<CT> rs{vox, chord, offsets[i], offsets[i + 1], Reentry(lds, r), 0.0};
-    if (rec_finite(r)) {
-        const bool onward = walk_row<HULL>(r, src, g, rs);
-        if (!onward || rs.re.unsafe) raise_status(status, PCT_DEV_REENTRY);
-    } else {
-        raise_status(status, PCT_DEV_NONFINITE);
+    __shared__ RowStage<CT> stage;
+    const int tid = int(threadIdx.x);
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + tid;
+    const bool mine = i < n;
+    Rec r{};
+    bool active = false;
+    if (mine) {
+        r = load_rec(p, i);
+        active = rec_finite(r);
+        if (!active) {
+            raise_status(status, PCT_DEV_NONFINITE);
+            r = Rec{};
+        }
     }
+    const LanePath<HULL> path(src, g, r);
+    LaneWalk<HULL> walk(path, g, r);
+    RowSink<CT> rs{&stage, vox, chord, mine ? offsets[i] : 0, mine ? offsets[i + 1] : 0, Reentry(lds, r), 0.0};
+    const int K = active ? path.K : 0;
+    for (int k0 = 0; __syncthreads_or(k0 < K); k0 += kRowSteps) {
+        const int64_t base = rs.pos;
+        rs.staged = 0;
+        if (k0 < K) {
+            walk.run(k0, min(k0 + kRowSteps, K), rs);
+            if (k0 + kRowSteps >= K) walk.finish(rs);
+        }
+        stage.base[tid] = base;
+        stage.n[tid] = int(min(int64_t(min(rs.staged, kRowStage)), max(rs.end - base, int64_t(0))));
+        __syncthreads();
+        const int row0 = tid & ~(kWave - 1);
+#pragma unroll 1
+        for (int q0 = 0; q0 < kWave; q0 += 8) {
+            const int row = row0 + q0 + (tid & (kWave - 1)) / 8, cnt = stage.n[row];
+            const long long to = stage.base[row];
+            for (int q = tid % 8; q < cnt; q += 8) {
+                vox[to + q] = stage.j[row][q];
+                chord[to + q] = stage.c[row][q];
+            }
+        }
+    }
+    if (!mine) return;
+    if (active && (!walk.onward || rs.re.unsafe)) raise_status(status, PCT_DEV_REENTRY);
     if (rs.pos != rs.end) raise_status(status, PCT_DEV_ROW_OVERFLOW);  // offsets from other records
     n2[i] = rs.n2;
 }
