@@ -247,7 +247,7 @@ def pct_drop_iterate_rows(plan: Plan, rows: Rows, b: torch.Tensor, x: torch.Tens
 def pct_tv(plan: Plan, x: torch.Tensor, eps: float, with_grad: bool = True):
     code = _dtype_code(x)
     xp = _dev(x, "x", numel=plan.nvox)
-    val = torch.zeros(1, dtype=torch.float64, device=x.device)
+    val = torch.empty(1, dtype=torch.float64, device=x.device)
     grad = torch.empty_like(x) if with_grad else None
     st = lib().pct_tv(plan.handle, xp, code, float(eps), C.c_void_p(val.data_ptr()),
                       C.c_void_p(grad.data_ptr()) if with_grad else None, plan.ws_ptr, plan.ws_bytes,
@@ -261,7 +261,7 @@ def pct_tv_static(plan: Plan, x: torch.Tensor, eps: float, with_grad: bool = Tru
     library's own per-GPU scratch array holds the partial sums)."""
     code = _dtype_code(x)
     xp = _dev(x, "x", numel=plan.nvox)
-    val = torch.zeros(1, dtype=torch.float64, device=x.device)
+    val = torch.empty(1, dtype=torch.float64, device=x.device)
     grad = torch.empty_like(x) if with_grad else None
     st = lib().pct_tv_static(plan.handle, xp, code, float(eps), C.c_void_p(val.data_ptr()),
                              C.c_void_p(grad.data_ptr()) if with_grad else None, _stream(x.device))
