@@ -14,14 +14,17 @@
 
 namespace pct {
 
-// Path of one row in voxel units from the grid's corner.
+// Path of one row in voxel units; o: the grid's corner in them.
 template <bool HULL>
 struct LanePath {
     RowPath<HULL> row;
+    double o[3];
     int K;
     __device__ __forceinline__ LanePath(const PathSrc &src, const GridDev &g, const Rec &r)
         : row(src, g, r), K(row.K)
     {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) o[a] = g.lo[a] * g.inv_pitch[a];
     }
     __device__ __forceinline__ void place(int k, double w[3]) const
     {
@@ -37,7 +40,7 @@ struct LanePath<false> {
     const PathSrc &src;
     double t[4], v[4];       // t_in, th_in, t_out, th_out; the same of v in voxels
     double cx, sx, cy, sy;   // cos, sin in voxels a mm along x and y
-    double o[3];             // corner (voxels)
+    double o[3];
     int K;
     __device__ __forceinline__ LanePath(const PathSrc &src_, const GridDev &g, const Rec &r) : src(src_), K(src_.K)
     {
@@ -53,9 +56,9 @@ struct LanePath<false> {
     {
         const double *__restrict__ c = src.tab + k * kRowDoubles;
         const double tt = fma(c[0], t[0], fma(c[1], t[1], fma(c[2], t[2], c[3] * t[3])));
-        w[2] = fma(c[0], v[0], fma(c[1], v[1], fma(c[2], v[2], fma(c[3], v[3], -o[2]))));
-        w[0] = fma(c[4], cx, fma(-tt, sx, -o[0]));
-        w[1] = fma(c[4], sy, fma(tt, cy, -o[1]));
+        w[2] = fma(c[0], v[0], fma(c[1], v[1], fma(c[2], v[2], c[3] * v[3])));
+        w[0] = fma(c[4], cx, -tt * sx);
+        w[1] = fma(c[4], sy, tt * cy);
     }
 };
 
@@ -88,7 +91,7 @@ struct LaneWalk {
     }
     __device__ __forceinline__ double voxel(int a, double x) const
     {
-        return fmin(fmax(floor(x), -1.0), double(g.n[a]));
+        return fmin(fmax(floor(x - p.o[a]), -1.0), double(g.n[a]));
     }
     template <class Sink>
     __device__ __forceinline__ void leave(Sink &sink)
@@ -122,7 +125,7 @@ struct LaneWalk {
             if (k + 1 == p.K) {  // a path that ends on a plane has not crossed it
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    if (d[a] > 0.0 && w1[a] == f1[a]) f1[a] -= 1.0;
+                    if (d[a] > 0.0 && w1[a] == f1[a] + p.o[a]) f1[a] -= 1.0;
             }
             onward = onward && (dom ? d[1] : d[0]) * sgn > 0.0;
             const double len = fast_sqrt(len2);
@@ -132,7 +135,7 @@ struct LaneWalk {
                 e[a] = int(f1[a]) - i[a];
                 far |= unsigned(e[a] + 1) > 2u;
                 at[a] = 2.0;
-                if (e[a] != 0) at[a] = (fmax(f[a], f1[a]) - w[a]) * fast_rcp(d[a]);
+                if (e[a] != 0) at[a] = (fmax(f[a], f1[a]) + p.o[a] - w[a]) * fast_rcp(d[a]);
             }
             double last = 0.0;
             if (!__any(far)) {
@@ -151,7 +154,7 @@ struct LaneWalk {
             } else {
                 double inv[3];
                 auto next = [&](int a) {
-                    const double plane = double(i[a]) + (e[a] > 0 ? 1.0 : 0.0);
+                    const double plane = double(i[a]) + (e[a] > 0 ? 1.0 : 0.0) + p.o[a];
                     at[a] = e[a] == 0 ? 2.0 : fmin(fmax((plane - w[a]) * inv[a], last), 1.0);
                 };
 #pragma unroll

@@ -110,12 +110,16 @@ __device__ __forceinline__ double lane_before(double v, double first)
 // Dominant in-plane axis of a row (0: x, 1: y).
 __device__ __forceinline__ int dominant_axis(const Rec &r) { return fabs(r.cs) >= fabs(r.sn) ? 0 : 1; }
 
-// Index of the voxel that holds w mm from the grid's corner, clamped to one
-// voxel beyond the grid.  (A point within rounding of a plane may be put on
+// Index along axis a of the voxel that holds w (mm), clamped to one voxel beyond
+// the grid.  (A point within rounding of a plane may be put on
 // either side: its crossing then falls on the segment's end.)
-__device__ __forceinline__ int voxel_index(double w, double inv, int n)
+__device__ __forceinline__ int voxel_index(double w, const GridDev &g, int a)
 {
-    return int(fmin(fmax(floor(w * inv), -1.0), double(n)));
+    return int(fmin(fmax(floor((w - g.lo[a]) * g.inv_pitch[a]), -1.0), double(g.n[a])));
+}
+__device__ __forceinline__ double plane_at(int i, const GridDev &g, int a)
+{
+    return fma(double(i), g.pitch[a], g.lo[a]);
 }
 
 // What one wave needs of its row (the same in every lane).  With a hull the
@@ -154,7 +158,8 @@ struct RowPath {
         }
         return v;
     }
-    // vertex k, mm from the grid's corner
+    // vertex k (mm; from the grid's corner it would be twice as large, and as
+    // coarse)
     __device__ __forceinline__ void place(int k, const Vertex &c, double &x, double &y, double &z) const
     {
         double u, t, v;
@@ -180,9 +185,9 @@ struct RowPath {
             v = c.c[0] * r.v_in + c.c[1] * r.ph_in + c.c[2] * r.v_out + c.c[3] * r.ph_out;
             u = c.c[4];
         }
-        x = (u * r.cs - t * r.sn) - g.lo[0];
-        y = (u * r.sn + t * r.cs) - g.lo[1];
-        z = v - g.lo[2];
+        x = u * r.cs - t * r.sn;
+        y = u * r.sn + t * r.cs;
+        z = v;
     }
 };
 
@@ -235,7 +240,7 @@ __device__ __forceinline__ void put_many(const RecWindow &win, const GridDev &g,
     int at[3] = {i0[0], i0[1], i0[2]};
     double inv[3], f[3];  // fraction of the segment at the next plane of each axis
     auto next = [&](int a) {
-        const double plane = double(i1[a] > at[a] ? at[a] + 1 : at[a]) * g.pitch[a];
+        const double plane = plane_at(i1[a] > at[a] ? at[a] + 1 : at[a], g, a);
         f[a] = at[a] == i1[a] ? 2.0 : fmin(fmax((plane - w0[a]) * inv[a], 0.0), 1.0);
     };
 #pragma unroll
@@ -272,8 +277,7 @@ __device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWind
     double cx, cy, cz;  // start of the round's first segment
     p.place(0, p.fetch(0), cx, cy, cz);
     auto ahead = p.fetch(min(lane + 1, p.K));  // of the round to come
-    int jx = voxel_index(cx, g.inv_pitch[0], g.n[0]), jy = voxel_index(cy, g.inv_pitch[1], g.n[1]),
-        jz = voxel_index(cz, g.inv_pitch[2], g.n[2]);
+    int jx = voxel_index(cx, g, 0), jy = voxel_index(cy, g, 1), jz = voxel_index(cz, g, 2);
     int n = 1;  // records before this round
     onward = true;
     const double sgn = (dom ? p.r.sn : p.r.cs) > 0.0 ? 1.0 : -1.0;
@@ -285,12 +289,11 @@ __device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWind
         ahead = p.fetch(min(k0 + kWave + lane + 1, p.K));
         const double x0 = lane_before(x1, cx), y0 = lane_before(y1, cy), z0 = lane_before(z1, cz);
         const double dx = x1 - x0, dy = y1 - y0, dz = z1 - z0;
-        int ix1 = voxel_index(x1, g.inv_pitch[0], g.n[0]), iy1 = voxel_index(y1, g.inv_pitch[1], g.n[1]),
-            iz1 = voxel_index(z1, g.inv_pitch[2], g.n[2]);
+        int ix1 = voxel_index(x1, g, 0), iy1 = voxel_index(y1, g, 1), iz1 = voxel_index(z1, g, 2);
         if (k == p.K) {  // a path that ends on a plane has not crossed it
-            ix1 -= dx > 0.0 && x1 == double(ix1) * g.pitch[0] ? 1 : 0;
-            iy1 -= dy > 0.0 && y1 == double(iy1) * g.pitch[1] ? 1 : 0;
-            iz1 -= dz > 0.0 && z1 == double(iz1) * g.pitch[2] ? 1 : 0;
+            ix1 -= dx > 0.0 && x1 == plane_at(ix1, g, 0) ? 1 : 0;
+            iy1 -= dy > 0.0 && y1 == plane_at(iy1, g, 1) ? 1 : 0;
+            iz1 -= dz > 0.0 && z1 == plane_at(iz1, g, 2) ? 1 : 0;
         }
         const bool on = k0 + lane < p.K;
         const int ix0 = lane_before(ix1, jx), iy0 = lane_before(iy1, jy), iz0 = lane_before(iz1, jz);
@@ -312,12 +315,12 @@ __device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWind
             put_many(win, g, first, k0 + lane, len, w0, w1, i0, i1);
         } else {
             // fraction of the segment at each crossing (2: none) and their order
-            auto fraction = [](int e, int i0, double w0, double d, double pitch) {
-                const double plane = double(i0 + (e > 0 ? 1 : 0)) * pitch;
+            auto fraction = [&](int e, int i0, double w0, double d, int a) {
+                const double plane = plane_at(i0 + (e > 0 ? 1 : 0), g, a);
                 return e != 0 ? fmin(fmax((plane - w0) * fast_rcp(d), 0.0), 1.0) : 2.0;
             };
-            const double fx = fraction(ex, ix0, x0, dx, g.pitch[0]), fy = fraction(ey, iy0, y0, dy, g.pitch[1]),
-                         fz = fraction(ez, iz0, z0, dz, g.pitch[2]);
+            const double fx = fraction(ex, ix0, x0, dx, 0), fy = fraction(ey, iy0, y0, dy, 1),
+                         fz = fraction(ez, iz0, z0, dz, 2);
             const bool xy = fx <= fy, xz = fx <= fz, yz = fy <= fz;
             const int at = pack_xy(g, ix0, iy0), ey2 = pack_xy(g, 0, ey);
             if (ex != 0)
