@@ -26,8 +26,8 @@ struct SortLayout {
     size_t rec;         // n packed records of 10 floats (9 fields, then b)
     size_t total;
     int64_t n_tiles;    // tiles of kSortTile records
-    int64_t n_hist;     // digit counts, one per digit and tile
-    int64_t n_parts;    // partial sums of the count scan
+    int64_t n_hist;     // room for digit counts (one per digit and tile)
+    int64_t n_parts;    // room for partial sums of the count scan
 };
 
 constexpr int32_t kSortMaxAngles = 4096;

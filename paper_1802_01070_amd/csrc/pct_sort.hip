@@ -8,17 +8,18 @@
 // (ord: the FP32 bit pattern mapped so that unsigned order is numeric order,
 // with -0 taken as +0; a non-finite record gets a = n_angles and sorts last),
 // and the (key, position) pairs go through a least-significant-digit radix
-// sort with 9-bit digits, one pass per digit the key uses:
+// sort with 9-bit digits (8-bit ones for pairs that do not pack, and where the
+// workspace has no room for 512 counts a tile), one pass per digit the key uses:
 //
 //   k_sort_keys         one thread per record: the key, and a packed 40-byte copy
 //                       of the record (9 fields and b)
-//   k_sort_hist         one workgroup per tile of 4096 pairs: digit counts in
+//   k_sort_hist         one workgroup per tile of 4608 pairs: digit counts in
 //                       LDS, written digit-major (count of digit d in tile g at
 //                       d * n_tiles + g), so that one exclusive scan of the
 //                       counts gives every (digit, tile) its output offset
 //   k_sort_count_*      that scan: partial sums of 4096 counts, then the scan of
 //                       each segment from the sum of the partials before it
-//   k_sort_scatter      one workgroup per tile, a wave per 512 pairs in input
+//   k_sort_scatter      one workgroup per tile, a wave per 576 pairs in input
 //                       order: a lane's rank among the lanes of its wave with
 //                       the same digit comes from 9 ballots (one per digit
 //                       bit), the count of the wave's earlier pairs from LDS, so
@@ -45,6 +46,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <utility>
 
 #include "pct_sort.h"
@@ -54,15 +56,14 @@ namespace pct {
 namespace {
 
 constexpr int kSortWG = 256;
-constexpr int kRadixBits = 9;
-constexpr int kDigits = 1 << kRadixBits;
-constexpr int kRadixWG = 512;                                   // = kDigits: a thread per digit
+constexpr int kRadixWG = 512;
 constexpr int kRadixWaves = kRadixWG / 64;
-constexpr int kSortRounds = 8;
+constexpr int kSortRounds = 9;
 constexpr int64_t kSortTile = int64_t(kRadixWG) * kSortRounds;  // records per tile
+constexpr int64_t kCountTile = 2048;                            // the workspace has 256 counts for so many records
 constexpr int kScanPer = 16;
 constexpr int64_t kScanSeg = int64_t(kSortWG) * kScanPer;       // counts per scan workgroup
-static_assert(kRadixWG == kDigits && kSortRounds * 64 < 65536, "a thread per digit, 16-bit counts");
+static_assert(kRadixWG * kSortRounds < 65536, "16-bit counts and places in a tile");
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -125,9 +126,12 @@ __device__ inline int64_t tile_of_workgroup(int64_t n_tiles)
 }
 unsigned tile_grid(int64_t n_tiles) { return unsigned(8 * ((n_tiles + 7) / 8)); }
 
+template <int BITS>
 __global__ void __launch_bounds__(kRadixWG) k_sort_hist(const unsigned long long *key, int64_t n, int shift,
                                                         int64_t n_tiles, uint32_t *hist)
 {
+    constexpr int kDigits = 1 << BITS;
+    static_assert(kDigits <= kRadixWG);
     __shared__ uint32_t h[kDigits];
     const int64_t tile = tile_of_workgroup(n_tiles), tile0 = tile * kSortTile;
     if (tile >= n_tiles) return;
@@ -137,7 +141,7 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_hist(const unsigned long long
         const int64_t i = tile0 + int64_t(r) * kRadixWG + threadIdx.x;
         k[r] = i < n ? key[i] : 0ull;
     }
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < kDigits) h[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
@@ -145,7 +149,7 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_hist(const unsigned long long
         if (i < n) atomicAdd(&h[unsigned(k[r] >> shift) & unsigned(kDigits - 1)], 1u);
     }
     __syncthreads();
-    hist[int64_t(threadIdx.x) * n_tiles + tile] = h[threadIdx.x];
+    if (threadIdx.x < kDigits) hist[int64_t(threadIdx.x) * n_tiles + tile] = h[threadIdx.x];
 }
 
 // Exclusive prefix sum of v over a workgroup of WG threads in thread order; total
@@ -218,12 +222,13 @@ __global__ void __launch_bounds__(kSortWG) k_sort_count_down(uint32_t *hist, int
 // counts (23.3).  A 45-bit key takes five passes of 94 us; six of 8-bit digits,
 // each moving a key and a position and ranking its waves together round by round,
 // took 125 us each.
-template <bool PACKED>
+template <bool PACKED, int BITS>
 __global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long long *key_in, const uint32_t *idx_in,
                                                            int64_t n, int shift, int bits_n, int64_t n_tiles,
                                                            const uint32_t *off, unsigned long long *key_out,
                                                            uint32_t *idx_out)
 {
+    constexpr int kDigits = 1 << BITS;
     __shared__ uint32_t first[kDigits];                           // output slot of the tile's first pair of each digit
     __shared__ uint32_t local[kDigits];                           // tile-local start of each digit (pairs in digit order)
     __shared__ volatile unsigned short cnt[kRadixWaves][kDigits]; // pairs of each wave and digit
@@ -249,13 +254,16 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long l
     }
     // pairs of digit t in this tile: the next offset of the scanned counts
     // (digit-major) minus this one; the last entry ends at n
-    const int64_t e = int64_t(t) * n_tiles + tile;
-    const uint32_t o0 = off[e];
-    const uint32_t o1 = e + 1 < kDigits * n_tiles ? off[e + 1] : uint32_t(n);
-    for (int w = 0; w < kRadixWaves; ++w) cnt[w][t] = 0;
-    uint32_t tile_total;
-    first[t] = o0;
-    local[t] = wg_exclusive_scan<kRadixWG>(o1 - o0, lds, tile_total);
+    uint32_t mine = 0, tile_total;
+    if (t < kDigits) {
+        const int64_t e = int64_t(t) * n_tiles + tile;
+        const uint32_t o0 = off[e];
+        mine = (e + 1 < kDigits * n_tiles ? off[e + 1] : uint32_t(n)) - o0;
+        first[t] = o0;
+        for (int w = 0; w < kRadixWaves; ++w) cnt[w][t] = 0;
+    }
+    const uint32_t start = wg_exclusive_scan<kRadixWG>(mine, lds, tile_total);
+    if (t < kDigits) local[t] = start;
     const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
     for (int r = 0; r < kSortRounds; ++r) {
@@ -263,7 +271,7 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long l
         const unsigned d = unsigned(k[r] >> shift) & unsigned(kDigits - 1);
         unsigned long long same = __ballot(valid);
 #pragma unroll
-        for (int bit = 0; bit < kRadixBits; ++bit) {
+        for (int bit = 0; bit < BITS; ++bit) {
             const unsigned long long m = __ballot((d >> bit) & 1u);
             same &= ((d >> bit) & 1u) ? m : ~m;
         }
@@ -274,11 +282,13 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long l
         if (valid && lower == 0) cnt[wave][d] = static_cast<unsigned short>(seen + uint32_t(__popcll(same)));
     }
     __syncthreads();
-    uint32_t run = local[t];
-    for (int w = 0; w < kRadixWaves; ++w) {
-        const uint32_t c = cnt[w][t];
-        cnt[w][t] = static_cast<unsigned short>(run);
-        run += c;
+    if (t < kDigits) {
+        uint32_t run = start;
+        for (int w = 0; w < kRadixWaves; ++w) {
+            const uint32_t c = cnt[w][t];
+            cnt[w][t] = static_cast<unsigned short>(run);
+            run += c;
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -292,7 +302,7 @@ __global__ void __launch_bounds__(kRadixWG) k_sort_scatter(const unsigned long l
             sdigit[lp] = static_cast<unsigned short>(d);
             const unsigned long long pos = shift == 0 ? static_cast<unsigned long long>(ix[r])
                                                       : k[r] & ((1ull << bits_n) - 1ull);
-            skey[lp] = (rest >> kRadixBits) << bits_n | pos;
+            skey[lp] = (rest >> BITS) << bits_n | pos;
         } else {
             skey[lp] = k[r];
             sidx[lp] = ix[r];
@@ -349,7 +359,7 @@ SortLayout sort_layout(int64_t n)
 {
     SortLayout L{};
     L.n_tiles = (n + kSortTile - 1) / kSortTile;
-    L.n_hist = kDigits * L.n_tiles;
+    L.n_hist = 256 * ((n + kCountTile - 1) / kCountTile);
     L.n_parts = (L.n_hist + kScanSeg - 1) / kScanSeg;
     size_t o = 0;
     L.keys0 = o;
@@ -391,25 +401,37 @@ int launch_sort_scan(const SortDev &s, const ProtonsDev &p, int64_t n, const flo
         return b;
     };
     const int bits_n = bits(uint64_t(n - 1));
-    const int passes = (s.key_bits + kRadixBits - 1) / kRadixBits;
-    const bool packed = s.key_bits - kRadixBits + bits_n <= 64 && bits_n > 0;
+    auto sort = [&](auto packed_, auto bits_) {
+        constexpr bool kPacked = decltype(packed_)::value;
+        constexpr int kBits = decltype(bits_)::value;
+        const int64_t nh = (int64_t(1) << kBits) * L.n_tiles;
+        const unsigned parts = unsigned((nh + kScanSeg - 1) / kScanSeg), tiles = tile_grid(L.n_tiles);
+        const int passes = (s.key_bits + kBits - 1) / kBits;
+        for (int pass = 0; pass < passes; ++pass) {
+            const int shift = !kPacked ? kBits * pass : pass > 0 ? bits_n : 0;
+            hipLaunchKernelGGL(k_sort_hist<kBits>, dim3(tiles), dim3(kRadixWG), 0, st, k0, n, shift, L.n_tiles, hist);
+            hipLaunchKernelGGL(k_sort_count_reduce, dim3(parts), dim3(kSortWG), 0, st, hist, nh, part);
+            hipLaunchKernelGGL(k_sort_count_down, dim3(parts), dim3(kSortWG), 0, st, hist, nh, part);
+            hipLaunchKernelGGL((k_sort_scatter<kPacked, kBits>), dim3(tiles), dim3(kRadixWG), 0, st, k0,
+                               !kPacked && pass > 0 ? i0 : nullptr, n, shift, bits_n, L.n_tiles, hist,
+                               kPacked && pass + 1 == passes ? nullptr : k1, i1);
+            std::swap(k0, k1);
+            std::swap(i0, i1);
+        }
+    };
     hipLaunchKernelGGL(k_sort_keys, dim3(blocks), dim3(kSortWG), 0, st, p, b, n, s, k0, rec);
-    for (int pass = 0; pass < passes; ++pass) {
-        const int shift = !packed ? kRadixBits * pass : pass > 0 ? bits_n : 0;
-        hipLaunchKernelGGL(k_sort_hist, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0, n, shift, L.n_tiles,
-                           hist);
-        hipLaunchKernelGGL(k_sort_count_reduce, dim3(unsigned(L.n_parts)), dim3(kSortWG), 0, st, hist, L.n_hist,
-                           part);
-        hipLaunchKernelGGL(k_sort_count_down, dim3(unsigned(L.n_parts)), dim3(kSortWG), 0, st, hist, L.n_hist, part);
-        if (packed)
-            hipLaunchKernelGGL(k_sort_scatter<true>, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0, nullptr, n,
-                               shift, bits_n, L.n_tiles, hist, pass + 1 < passes ? k1 : nullptr, i1);
-        else
-            hipLaunchKernelGGL(k_sort_scatter<false>, dim3(tile_grid(L.n_tiles)), dim3(kRadixWG), 0, st, k0,
-                               pass > 0 ? i0 : nullptr, n, shift, bits_n, L.n_tiles, hist, k1, i1);
-        std::swap(k0, k1);
-        std::swap(i0, i1);
-    }
+    // one word a record where it holds what the first pass leaves of the key, and
+    // the position; 512 counts a tile where the workspace has them (all but a
+    // few sizes below 14336 records)
+    using Eight = std::integral_constant<int, 8>;
+    using Nine = std::integral_constant<int, 9>;
+    const bool wide = 512 * L.n_tiles <= L.n_hist;
+    if (bits_n == 0 || s.key_bits - (wide ? 9 : 8) + bits_n > 64)
+        sort(std::false_type{}, Eight{});
+    else if (wide)
+        sort(std::true_type{}, Nine{});
+    else
+        sort(std::true_type{}, Eight{});
     hipLaunchKernelGGL(k_sort_gather, dim3(blocks), dim3(kSortWG), 0, st, rec, n, i0, o, b_out, perm);
     return hipGetLastError();
 }
