@@ -59,7 +59,7 @@ def log(msg):
 # Sources each profiled kernel is built from: its counters stay valid while
 # these files are unchanged.
 KERNEL_SOURCES = {
-    "k_drop": ("pct_internal.h", "pct_path.hpp", "pct_kernels.hip"),
+    "k_drop": ("pct_internal.h", "pct_path.hpp", "pct_walk.hpp", "pct_kernels.hip"),
     "fbp": ("pct_internal.h", "pct_fbp.hip"),
 }
 
@@ -801,19 +801,14 @@ def main():
     ceiling = parallel_sweep_ceiling(api, plan, pr, x)
     # which block schedule pct_drop_iterate takes (the library's rules): FP32
     # with lanes > 1 and blocks of at most 8192 protons: the binned schedule
-    # (block kernel + slab commit); with --fused-commit, 64 lanes per proton
-    # and blocks of at most 4096 protons the traced-ahead atomic schedule, else
-    # the fused one; FP64 runs the block kernel and a separate commit
-    lanes = args.lanes or (64 if max(sc.grid.nx, sc.grid.ny) >= 160 else 32 if max(sc.grid.nx, sc.grid.ny) >= 64
-                           else 16)
+    # (block kernel + slab commit); with --fused-commit or larger blocks the
+    # fused one; FP64 runs the block kernel and a separate commit
+    lanes = args.lanes or 64
     f32 = vdtype == torch.float32
     if f32 and lanes > 1 and cfg.block <= 8192 and not (args.separate_commit or args.fused_commit):
-        kname, kdesc = "k_drop_bin", ("k_drop_bin (MLP trace + a.x + |a|^2 + rho of block t, packed D-weighted "
-                                      "contributions stored into per-(slab, row) bins; the slab commit "
-                                      "k_slab_commit sums them in LDS and commits the touched voxels)")
-    elif f32 and lanes == 64 and cfg.block <= 4096 and not args.separate_commit:
-        kname, kdesc = "k_drop_pipe", ("k_drop_pipe (trace of block t+1 into a row slot, DROP step of block t: "
-                                       "a.x + |a|^2 + rho + D-weighted scatter, commit of block t-1)")
+        kname, kdesc = "k_drop_bin", ("k_drop_bin (MLP trace + a.x + |a|^2 + rho of block t, chords stored into "
+                                      "per-(slab, row) bins; the slab commit k_slab_commit sums the D-weighted "
+                                      "contributions in LDS and commits the touched voxels)")
     elif f32 and not args.separate_commit:
         kname, kdesc = "k_drop_fused", ("k_drop_fused (MLP trace + a.x + |a|^2 + rho + D-weighted scatter of "
                                         "block t, commit of block t-1)")
