@@ -135,7 +135,11 @@ struct LaneWalk {
                 e[a] = int(f1[a]) - i[a];
                 far |= unsigned(e[a] + 1) > 2u;
                 at[a] = 2.0;
-                if (e[a] != 0) at[a] = (fmax(f[a], f1[a]) + p.o[a] - w[a]) * fast_rcp(d[a]);
+                // (a crossing lies in its segment, also where the path runs along the
+                // plane and its vertices' last bits cross it: there the quotient is
+                // of two rounding errors)
+                if (e[a] != 0)
+                    at[a] = fmin(fmax((fmax(f[a], f1[a]) + p.o[a] - w[a]) * fast_rcp(d[a]), 0.0), 1.0);
             }
             double last = 0.0;
             if (!__any(far)) {
