@@ -465,11 +465,11 @@ __device__ __forceinline__ int64_t row_of_workgroup(int w, int64_t lo, int64_t h
 // a_i.x and ||a_i||^2 of a row.  Chords enter a_i.x as CT values.
 template <typename CT, int CHORD, bool HULL, class XA>
 __device__ __forceinline__ void row_dot(const RowPath<HULL> &p, RecWindow &win, int dom, const XA &xa, bool &have,
-                                        bool &onward, double &dot, double &n2)
+                                        RowShape &shape, double &dot, double &n2)
 {
     double d = 0.0, s = 0.0;
     const int sy = p.g.n[0], sz = p.g.n[0] * p.g.n[1];
-    row_pieces<HULL, CHORD>(p, win, dom, have, onward, [&](const RowPiece &q) {
+    row_pieces<HULL, CHORD>(p, win, dom, have, shape, [&](const RowPiece &q) {
         if (!q.real) return;
         d = fma(double(CT(q.c)), xa(q.ix + sy * q.iy + sz * q.iz), d);
         s = fma(q.c, fma(2.0, q.before, q.c), s);
@@ -495,14 +495,15 @@ __device__ __forceinline__ void drop_row(const ProtonsDev &p, const float *__res
     const RowPath<HULL> path(src, g, r);
     const int dom = dominant_axis(r);
     RecWindow win(lds, src.nvmax, span);
-    bool have = false, onward = true;
+    bool have = false;
+    RowShape shape;
     double dot, n2;
-    row_dot<CT, CHORD, HULL>(path, win, dom, xa, have, onward, dot, n2);
-    if (!onward) raise_status(status, PCT_DEV_REENTRY);
+    row_dot<CT, CHORD, HULL>(path, win, dom, xa, have, shape, dot, n2);
+    if (!shape.onward || shape.cut) raise_status(status, PCT_DEV_REENTRY);
     if (!(n2 > 0.0)) return;
     const double rho = lambda * (bi - dot) / n2;
     const int sy = g.n[0], sz = g.n[0] * g.n[1];
-    row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+    row_pieces<HULL, CHORD>(path, win, dom, have, shape, [&](const RowPiece &q) {
         if (!q.real) return;
         const int j = q.ix + sy * q.iy + sz * q.iz;
         scatter_one<T>(acc, acc_lo, cnt, j, rho * double(CT(q.c)), q.first, status);
@@ -751,7 +752,8 @@ __global__ void __launch_bounds__(kWave) k_drop_bin(ProtonsDev p, const float *_
         const RowPath<HULL> path(src, g, r);
         const int dom = dominant_axis(r);
         RecWindow win(lds, src.nvmax, span);
-        bool have = false, onward = true;
+        bool have = false;
+        RowShape shape;
         const bool binned = dom == block_axis(p, lo);
         const unsigned cap = unsigned(bins.cap), slabs = unsigned(bins.nslab), own = unsigned(dom ? g.n[1] : g.n[0]);
         const int cb = it.packed ? g.n[2] : 1, cz = it.packed ? 1 : dom ? g.n[0] : g.n[1];
@@ -759,7 +761,7 @@ __global__ void __launch_bounds__(kWave) k_drop_bin(ProtonsDev p, const float *_
         double d = 0.0, s = 0.0;
         float cw = 0.f, xw = 0.f;  // chord and gather of the pass before, in flight
         bool spilled = !binned;
-        row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+        row_pieces<HULL, CHORD>(path, win, dom, have, shape, [&](const RowPiece &q) {
             const float cf = q.real ? float(q.c) : 0.f;
             d = fma(double(cw), double(xw), d);
             cw = cf;
@@ -771,7 +773,7 @@ __global__ void __launch_bounds__(kWave) k_drop_bin(ProtonsDev p, const float *_
                 spilled |= q.k >= kBinCap;
             }
             // a record that is no piece still takes its place among the entries
-            if (binned && onward && unsigned(q.k) < unsigned(kBinCap) && unsigned(q.slab) < own) {
+            if (binned && shape.onward && unsigned(q.k) < unsigned(kBinCap) && unsigned(q.slab) < own) {
                 const unsigned cell = unsigned((dom ? q.ix : q.iy) * cb + q.iz * cz);
                 const unsigned at = unsigned(q.slab) * cap + unsigned(row);
                 BinEntry *to = q.k == 0 ? bins.e0 + at : bins.ek + (unsigned(q.k - 1) * slabs * cap + at);
@@ -783,11 +785,11 @@ __global__ void __launch_bounds__(kWave) k_drop_bin(ProtonsDev p, const float *_
         d = fma(double(cw), double(xw), d);
         const double dot = wave_sum(d);
         n2 = wave_sum(s);
-        if (!onward && lane == 0) raise_status(status, PCT_DEV_REENTRY);
+        if ((!shape.onward || shape.cut) && lane == 0) raise_status(status, PCT_DEV_REENTRY);
         rho = lambda * (bi - dot) / n2;
-        const bool direct = !binned || !onward;
+        const bool direct = !binned || !shape.onward;
         if (n2 > 0.0 && (direct || __any(spilled))) {
-            row_pieces<HULL, CHORD>(path, win, dom, have, onward, [&](const RowPiece &q) {
+            row_pieces<HULL, CHORD>(path, win, dom, have, shape, [&](const RowPiece &q) {
                 if (q.real && (direct || q.k >= kBinCap))
                     atomicAdd(ovf + it.at(q.ix, q.iy, q.iz),
                               pack_contribution(rho * double(float(q.c)), q.first, status));

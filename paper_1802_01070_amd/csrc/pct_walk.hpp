@@ -266,11 +266,17 @@ __device__ __forceinline__ void put_many(const RecWindow &win, const GridDev &g,
     }
 }
 
-// The records of the window, the number of pieces of the row, and whether the
-// path moves on along the axis `dom` in every segment.  All lanes of the wave
-// call it; the caller waits for the LDS writes.
+// What the walk tells of a row besides its pieces (the same in every lane).
+struct RowShape {
+    bool onward = true;  // the path moves on along the dominant axis in every segment
+    bool turns = false;  // its voxel index goes both ways along some axis: without, no voxel comes back
+    bool cut = false;    // a voxel may have come back from before the window
+};
+
+// The records of the window, the number of pieces of the row, and its shape.  All
+// lanes of the wave call it; the caller waits for the LDS writes.
 template <bool HULL>
-__device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWindow &win, int dom, bool &onward)
+__device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWindow &win, int dom, RowShape &shape)
 {
     const GridDev &g = p.g;
     const int lane = int(threadIdx.x) & (kWave - 1);
@@ -278,8 +284,9 @@ __device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWind
     p.place(0, p.fetch(0), cx, cy, cz);
     auto ahead = p.fetch(min(lane + 1, p.K));  // of the round to come
     int jx = voxel_index(cx, g, 0), jy = voxel_index(cy, g, 1), jz = voxel_index(cz, g, 2);
+    const int sx = lane_value(jx, 0), sy = lane_value(jy, 0), sz = lane_value(jz, 0);
     int n = 1;  // records before this round
-    onward = true;
+    bool onward = true;
     const double sgn = (dom ? p.r.sn : p.r.cs) > 0.0 ? 1.0 : -1.0;
     if (lane == 0) win.put(0, 0, 0.0, pack_xy(g, jx, jy), jz);
     for (int k0 = 0; k0 < p.K; k0 += kWave) {
@@ -341,6 +348,9 @@ __device__ __forceinline__ int row_records(const RowPath<HULL> &p, const RecWind
         jy = lane_value(iy1, kWave - 1);
         jz = lane_value(iz1, kWave - 1);
     }
+    shape.onward = onward;
+    // a crossing is a step of one index: more of them than the ends are apart
+    shape.turns = n - 1 != abs(jx - sx) + abs(jy - sy) + abs(jz - sz);
     // the list's end
     __syncthreads();
     if (lane <= kLookAhead) win.put(n + lane, p.K - 1, win.len[p.K - 1], pack_xy(g, -2, -2), -2);
@@ -361,25 +371,32 @@ struct RowPiece {
 // Calls use(piece) for every record of the row, 64 at a time in path order (all
 // lanes of the wave take part; lanes beyond the list get a piece that is not
 // real and has k < 0).  `have`: the window holds the row already.
+//
+// A voxel can be met again inside its slab only, and not before two pieces on,
+// where the path moves on along the dominant axis: a piece looks back over its
+// slab.  A row of several windows keeps the slab it is in from one to the next;
+// where a slab does not fit a window, a piece of a path that turns somewhere and
+// would look back further raises shape.cut.  A path that turns back along that axis may meet any voxel again, and its pieces
+// look back over the window.
 template <bool HULL, int CHORD, class Use>
-__device__ __forceinline__ void row_pieces(const RowPath<HULL> &p, RecWindow &win, int dom, bool &have, bool &onward,
-                                           Use &&use)
+__device__ __forceinline__ void row_pieces(const RowPath<HULL> &p, RecWindow &win, int dom, bool &have,
+                                           RowShape &shape, Use &&use)
 {
     const GridDev &g = p.g;
     const int lane = int(threadIdx.x) & (kWave - 1);
     int run = 0, slab_before = INT_MIN;  // of the slab the round before ended in
     int n = 0;
-    for (int lo = 0; lo == 0 || lo < n; lo += win.span) {
-        if (!(have && lo == 0 && n == 0)) {
+    for (int lo = 0, from = 0; from == 0 || from < n;) {  // window, and the first piece that it hands over
+        if (!(have && from == 0)) {
             win.lo = lo;
             __syncthreads();
-            n = row_records<HULL>(p, win, dom, onward);
+            n = row_records<HULL>(p, win, dom, shape);
             __syncthreads();
             win.n = n;
         }
         n = win.n;
         const int hi = min(n, lo + win.span);
-        for (int g0 = lo; g0 < hi; g0 += kWave) {
+        for (int g0 = from; g0 < hi; g0 += kWave) {
             const int i = g0 + lane;
             const bool on = i < hi;
             const RowRec a = *win.at(on ? i : hi);
@@ -402,10 +419,10 @@ __device__ __forceinline__ void row_pieces(const RowPath<HULL> &p, RecWindow &wi
             q.k = !on ? -1 : below != 0ull ? lane - (kWave - 1 - __clzll(below)) : run + lane;
             q.first = true;
             q.before = 0.0;
-            // a voxel can be met again inside its slab only, and not before two
-            // pieces on; a path that turns back may meet any voxel again
-            const int back = onward ? min(q.k, kRecPad) : i - lo + min(lo, kRecPad);
-            if (q.real && back >= 2) {
+            if (shape.turns) {
+                const int want = shape.onward ? q.k : i, stored = i - lo + min(lo, kRecPad);
+                const int back = q.real ? min(want, stored) : 0;
+                if (lo > 0) shape.cut |= __any(q.real && want > stored);
                 for (int d = 2; d <= back; ++d) {
                     const RowRec *e = win.at(i - d);
                     if (e->xy != a.xy || e->z != a.z) continue;
@@ -420,6 +437,9 @@ __device__ __forceinline__ void row_pieces(const RowPath<HULL> &p, RecWindow &wi
             run = starts != 0ull ? kWave - (kWave - 1 - __clzll(starts)) : run + kWave;
             slab_before = lane_value(q.slab, kWave - 1);
         }
+        const int slab = (run + kWave - 1) & -kWave;
+        from = hi;
+        lo = hi - (!shape.onward ? 0 : slab < win.span ? slab : (win.span / 2) & -kWave);
     }
     have = n <= win.span;
 }
