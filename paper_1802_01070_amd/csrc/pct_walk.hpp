@@ -138,8 +138,13 @@ struct RowPath {
     {
         if constexpr (HULL) {
             if (!ps.miss) {
-                k_in = int(ceil((ps.uh_in - src.u_in) * src.inv_step));
-                k_out = int(ceil((src.u_out - ps.uh_out) * src.inv_step));
+                // (a length that is a whole number of steps up to rounding is cut
+                // into that many: one cut more would fall on the hull point)
+                auto steps = [&](double length) {
+                    return length > 0.0 ? max(1, int(ceil(length * src.inv_step - 0x1p-30))) : 0;
+                };
+                k_in = steps(ps.uh_in - src.u_in);
+                k_out = steps(src.u_out - ps.uh_out);
                 K = k_in + ps.kh + k_out;
             }
         }

@@ -24,7 +24,8 @@ def test_whole_steps_outside_the_hull_are_not_a_turn(step, radius, r):
     p["gantry"] = (np.arange(n) * (2.0 * np.pi / n)).astype(np.float32)
     b = np.linspace(0.8, 1.2, n).astype(np.float32) * np.float32(2.0 * radius)
     side = int(2.0 * r)
-    grid = synth.Grid(side, side, 3)
+    # (an origin that keeps the rays through the axis off the voxel planes)
+    grid = synth.Grid(side, side, 3, origin=(-r + 0.25, -r + 0.4, -1.5))
     mlp = synth.MLPModel(u_in=-r, u_out=r, step=step)
     oracle.set_hull(radius)
     try:
