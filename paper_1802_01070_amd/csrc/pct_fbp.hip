@@ -429,14 +429,7 @@ int launch_fbp_sinogram(const FbpDev &f, const ProtonsDev &p, int64_t n, const f
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) == hipSuccess;
         (void)hipGetLastError();
         if (priv) {
-            // the fewest flushes: no more workgroups than the chip holds at once (two
-            // a CU where two histograms fit its LDS) until chunks are full.  200 x 200
-            // x 32, 180 angles, the image of 1e6 and 3e6 records: 266 and 289 us (276 and
-            // 304 with a thousand chunks); whole rounds at 1e7 records: 372 against 355
-            int cus = 0;
-            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-            const int64_t held = int64_t(cus) * (2 * lds <= size_t(max_lds) ? 2 : 1);
-            const int64_t chunk = std::min<int64_t>(kFbpMaxChunk, std::max<int64_t>(1024, (n + held - 1) / held));
+            const int64_t chunk = std::min<int64_t>(kFbpMaxChunk, std::max<int64_t>(1024, (n + 1023) / 1024));
             hipLaunchKernelGGL(k_fbp_bin_lds, dim3(unsigned((n + chunk - 1) / chunk)), dim3(kFbpBinWG), lds, s, p, b, n,
                                chunk, f, sum, cnt);
         } else {
