@@ -60,7 +60,7 @@ struct Layout {
     size_t acc_stride;  // bytes between consecutive accumulators
     size_t cnt;      // nvox int32
     size_t x1;       // second copy of the iterate, nvox doubles
-    size_t partial;  // kMaxPartials doubles
+    size_t partial;  // kMaxPartials doubles (during DROP calls: the touched ranges of the last blocks)
     size_t lo;       // compensation word of the FP32 iterate, nvox floats
     size_t total;    // end of the fixed part; the bins follow
 };

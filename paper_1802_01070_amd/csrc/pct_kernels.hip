@@ -383,6 +383,69 @@ __device__ __forceinline__ void scatter_one(void *acc, long long *acc_lo, int32_
     }
 }
 
+// Touched range of a block, on large volumes (kRangeVoxels): least and
+// greatest voxel index its rows add to, for the block's commit.  A slot holds the
+// range in parts, each of a share of the workgroups and in a line of its own:
+// atomics on one line take 4 ns each (26 us for 3200 rows on one slot's words side
+// by side), and to look first whether a word has to move costs a round trip.
+constexpr int kRangeParts = 32, kRangeSlots = 4;
+struct alignas(256) RangePart {
+    int lo, hi;
+};
+static_assert(kRangeSlots * kRangeParts * sizeof(RangePart) <= kMaxPartials * sizeof(double), "in Layout::partial");
+
+struct TouchedRange {
+    int lo = INT_MAX, hi = -1;
+    __device__ __forceinline__ void touch(int j)
+    {
+        lo = min(lo, j);
+        hi = max(hi, j);
+    }
+    // All lanes of the wave call it.
+    __device__ __forceinline__ void publish(RangePart *slot)
+    {
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            lo = min(lo, __shfl_xor(lo, off, kWave));
+            hi = max(hi, __shfl_xor(hi, off, kWave));
+        }
+        if ((threadIdx.x & (kWave - 1)) != 0 || hi < 0) return;
+        RangePart *part = slot + blockIdx.x % kRangeParts;
+        atomicMin(&part->lo, lo);
+        atomicMax(&part->hi, hi);
+    }
+};
+__device__ __forceinline__ void clear_range(RangePart *slot)
+{
+    if (threadIdx.x >= kRangeParts) return;
+    slot[threadIdx.x].lo = INT_MAX;
+    slot[threadIdx.x].hi = -1;
+}
+// The whole range of a slot; all lanes of the wave call it.
+__device__ __forceinline__ void read_range(const RangePart *slot, int &lo, int &hi)
+{
+    lo = slot[threadIdx.x % kRangeParts].lo;
+    hi = slot[threadIdx.x % kRangeParts].hi;
+#pragma unroll
+    for (int off = kRangeParts / 2; off > 0; off >>= 1) {
+        lo = min(lo, __shfl_xor(lo, off, kWave));
+        hi = max(hi, __shfl_xor(hi, off, kWave));
+    }
+}
+// [j0, j1): both slots' ranges and what lies between.
+__device__ __forceinline__ void both_ranges(const RangePart *a, const RangePart *b, int &j0, int &j1)
+{
+    int lo, hi;
+    read_range(a, lo, hi);
+    read_range(b, j0, j1);
+    j0 = min(lo, j0);
+    j1 = max(hi, j1) + 1;
+}
+__global__ void __launch_bounds__(kWave) k_clear_ranges(RangePart *slots)
+{
+    for (int k = 0; k < kRangeSlots; ++k) clear_range(slots + k * kRangeParts);
+}
+
 // Scatter of one row: acc_j += rho a_ij and s_j += 1 once per row.  FP32 value
 // type: packed 64-bit accumulator; FP64: double accumulator (or the integer
 // pair) plus int count.
@@ -482,7 +545,7 @@ __device__ __forceinline__ void row_dot(const RowPath<HULL> &p, RecWindow &win, 
 template <typename T, int CHORD, bool HULL, class XA>
 __device__ __forceinline__ void drop_row(const ProtonsDev &p, const float *__restrict__ b, const XA &xa, void *acc,
                                          long long *acc_lo, int32_t *cnt, const PathSrc &src, const GridDev &g,
-                                         int64_t i, int span, double lambda, unsigned *status)
+                                         int64_t i, int span, double lambda, unsigned *status, RangePart *range)
 {
     using CT = typename std::conditional<sizeof(T) == 4, float, double>::type;
     extern __shared__ double lds[];
@@ -503,11 +566,14 @@ __device__ __forceinline__ void drop_row(const ProtonsDev &p, const float *__res
     if (!(n2 > 0.0)) return;
     const double rho = lambda * (bi - dot) / n2;
     const int sy = g.n[0], sz = g.n[0] * g.n[1];
+    TouchedRange touched;
     row_pieces<HULL, CHORD>(path, win, dom, have, shape, [&](const RowPiece &q) {
         if (!q.real) return;
         const int j = q.ix + sy * q.iy + sz * q.iz;
         scatter_one<T>(acc, acc_lo, cnt, j, rho * double(CT(q.c)), q.first, status);
+        if (range) touched.touch(j);
     });
+    if (range) touched.publish(range);
 }
 
 // Separate schedule: the block kernel (k_drop_commit follows).
@@ -516,12 +582,12 @@ __global__ void __launch_bounds__(kWave) k_drop_block(ProtonsDev p, const float 
                                                       const T *__restrict__ x, void *acc, int32_t *cnt,
                                                       const PathSrc src, GridDev g, int64_t lo, int64_t hi,
                                                       double lambda, unsigned *status, long long *acc_lo,
-                                                      const int *halt, int span)
+                                                      const int *halt, int span, RangePart *range)
 {
     if (gate_closed(halt)) return;
     const int64_t i = row_of_workgroup(int(blockIdx.x), lo, hi);
     if (i >= hi) return;
-    drop_row<T, CHORD, HULL>(p, b, PlainX<T>{x}, acc, acc_lo, cnt, src, g, i, span, lambda, status);
+    drop_row<T, CHORD, HULL>(p, b, PlainX<T>{x}, acc, acc_lo, cnt, src, g, i, span, lambda, status, range);
 }
 
 // ---------------------------------------------------------------------------
@@ -535,10 +601,9 @@ __global__ void __launch_bounds__(kWave) k_drop_block(ProtonsDev p, const float 
 //   value of block q-1, computed on the fly) and scatters into PK[q % 3].
 //   In the same launch, commit workgroups write X[(q+1) % 2] = base + update
 //   where block q-1 or q-2 touched a voxel (the only places where the two
-//   copies differ; a block touches voxels nearly all over the volume in
-//   angle-major scans, so the commit scans all of it: publishing the touched
-//   index range costs more, its atomics meet on two words) and clear
-//   PK[(q-2) % 3].  Nothing read in a launch is written in it, so no grid-wide
+//   copies differ), over the volume or, on a large one, over the two blocks'
+//   touched ranges (slots q-1 and q-2 of four; slot q+1 is cleared for the next
+//   block), and clear PK[(q-2) % 3].  Nothing read in a launch is written in it, so no grid-wide
 //   synchronisation is needed, and the commit's memory traffic overlaps the
 //   walk.  A flush kernel ends the sweep.
 // ---------------------------------------------------------------------------
@@ -563,12 +628,27 @@ struct LazyX {
     __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
 };
 
+// Range slots of a fused launch (nullptr: the commit goes over the volume).
+struct FusedRanges {
+    RangePart *cur;
+    const RangePart *prev, *old;
+    RangePart *reset;
+};
+
 __device__ __forceinline__ void commit_part(const float *__restrict__ base, float *__restrict__ next,
                                             const unsigned long long *__restrict__ pk_prev,
-                                            unsigned long long *__restrict__ pk_old, int nvox, int wg, int n_wg)
+                                            unsigned long long *__restrict__ pk_old, const FusedRanges &range,
+                                            int nvox, int wg, int n_wg)
 {
+    int j0 = 0, j1 = nvox;
+    if (range.cur) {
+        both_ranges(range.prev, range.old, j0, j1);
+        j0 &= ~3;
+        if (wg == 0) clear_range(range.reset);
+    }
     const int stride = 4 * n_wg * int(blockDim.x);
-    for (int j = 4 * (wg * int(blockDim.x) + int(threadIdx.x)); j < nvox; j += stride) {
+    for (unsigned ju = j0 + 4 * (wg * int(blockDim.x) + int(threadIdx.x)); ju < unsigned(j1); ju += stride) {
+        const int j = int(ju);
         const ulonglong2 p01 = *reinterpret_cast<const ulonglong2 *>(pk_prev + j);
         const ulonglong2 p23 = *reinterpret_cast<const ulonglong2 *>(pk_prev + j + 2);
         const ulonglong2 o01 = *reinterpret_cast<const ulonglong2 *>(pk_old + j);
@@ -593,17 +673,17 @@ __global__ void __launch_bounds__(kWave) k_drop_fused(ProtonsDev p, const float 
                                                       const float *__restrict__ base, float *__restrict__ next,
                                                       const unsigned long long *__restrict__ pk_prev,
                                                       unsigned long long *pk_cur, unsigned long long *pk_old,
-                                                      const PathSrc src, GridDev g, int64_t lo, int64_t hi,
-                                                      double lambda, unsigned *status, int nvox, int span)
+                                                      FusedRanges range, const PathSrc src, GridDev g, int64_t lo,
+                                                      int64_t hi, double lambda, unsigned *status, int nvox, int span)
 {
     if (int(blockIdx.x) < kCommitWG) {
-        commit_part(base, next, pk_prev, pk_old, nvox, int(blockIdx.x), kCommitWG);
+        commit_part(base, next, pk_prev, pk_old, range, nvox, int(blockIdx.x), kCommitWG);
         return;
     }
     const int64_t i = row_of_workgroup(int(blockIdx.x) - kCommitWG, lo, hi);
     if (i >= hi) return;
     drop_row<float, CHORD, HULL>(p, b, LazyX{base, pk_prev}, pk_cur, nullptr, nullptr, src, g, i, span, lambda,
-                                 status);
+                                 status, range.cur);
 }
 
 // Start of a fused sweep: X1 = x.
@@ -613,11 +693,16 @@ __global__ void __launch_bounds__(256) k_sweep_begin(const float *__restrict__ x
 }
 
 // End of a fused sweep of T blocks: x = X[T%2] + update of block T-1; clears
-// the accumulators of blocks T-1 and T-2.
+// the accumulators of blocks T-1 and T-2.  (Where neither touched a voxel, x holds
+// its value.)
 __global__ void __launch_bounds__(256) k_sweep_end(float *x, const float *src, unsigned long long *pk_last,
-                                                   unsigned long long *pk_prev, int nvox)
+                                                   unsigned long long *pk_prev, const RangePart *last,
+                                                   const RangePart *prev, int nvox)
 {
-    for (int j = int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += int(gridDim.x * blockDim.x)) {
+    int j0 = 0, j1 = nvox;
+    if (last) both_ranges(last, prev, j0, j1);
+    for (unsigned ju = j0 + blockIdx.x * blockDim.x + threadIdx.x; ju < unsigned(j1); ju += gridDim.x * blockDim.x) {
+        const int j = int(ju);
         const unsigned long long w = pk_last[j];
         x[j] = committed_value(src[j], w);
         if (w != 0ull) pk_last[j] = 0ull;
@@ -1072,17 +1157,26 @@ __global__ void __launch_bounds__(256) k_unpack_iterate(float *__restrict__ x, c
     }
 }
 
-// Commit of one block: a dense, coalesced scan of the volume; voxels with a
-// non-zero row count get x_j += acc_j / s_j and are reset.
+// Commit of one block: a dense, coalesced scan of the volume, or of the block's
+// touched range (and clears the slot of the next block); voxels with a non-zero
+// row count get x_j += acc_j / s_j and are reset.
 template <typename T>
-__device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt, int nvox, long long *acc_lo)
+__device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt, int nvox, long long *acc_lo,
+                                                 const RangePart *range, RangePart *range_next)
 {
-    const int stride = int(gridDim.x * blockDim.x);
+    int j0 = 0, j1 = nvox;
+    if (range) {
+        read_range(range, j0, j1);
+        ++j1;
+        if (blockIdx.x == 0) clear_range(range_next);
+    }
+    const unsigned stride = gridDim.x * blockDim.x, at = blockIdx.x * blockDim.x + threadIdx.x;
     if constexpr (sizeof(T) == 4) {
         // four 64-bit words per thread (the accumulator has 4 words of padding
         // past the last voxel; untouched words are zero)
         unsigned long long *pk = static_cast<unsigned long long *>(accv);
-        for (int j = 4 * int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += 4 * stride) {
+        for (unsigned ju = (j0 & ~3) + 4 * at; ju < unsigned(j1); ju += 4 * stride) {
+            const int j = int(ju);
             const ulonglong2 w01 = *reinterpret_cast<const ulonglong2 *>(pk + j);
             const ulonglong2 w23 = *reinterpret_cast<const ulonglong2 *>(pk + j + 2);
             const unsigned long long w[4] = {w01.x, w01.y, w23.x, w23.y};
@@ -1099,32 +1193,29 @@ __device__ __forceinline__ void drop_commit_body(T *x, void *accv, int32_t *cnt,
         }
         return;
     }
-    for (int j = int(blockIdx.x * blockDim.x + threadIdx.x); j < nvox; j += stride) {
-        {
-            const int c = cnt[j];
-            if (c != 0) {
-                if (acc_lo) {
-                    long long *hi = static_cast<long long *>(accv);
-                    x[j] = T(double(x[j]) + det_sum(hi[j], acc_lo[j]) / double(c));
-                    hi[j] = 0;
-                    acc_lo[j] = 0;
-                } else {
-                    double *acc = static_cast<double *>(accv);
-                    x[j] = T(double(x[j]) + acc[j] / double(c));
-                    acc[j] = 0.0;
-                }
-                cnt[j] = 0;
-            }
+    for (unsigned ju = j0 + at; ju < unsigned(j1); ju += stride) {
+        const int j = int(ju), c = cnt[j];
+        if (c == 0) continue;
+        if (acc_lo) {
+            long long *hi = static_cast<long long *>(accv);
+            x[j] = T(double(x[j]) + det_sum(hi[j], acc_lo[j]) / double(c));
+            hi[j] = 0;
+            acc_lo[j] = 0;
+        } else {
+            double *acc = static_cast<double *>(accv);
+            x[j] = T(double(x[j]) + acc[j] / double(c));
+            acc[j] = 0.0;
         }
+        cnt[j] = 0;
     }
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kWG) k_drop_commit(T *x, void *accv, int32_t *cnt, int nvox, long long *acc_lo,
-                                                     GateDev gt)
+                                                     const RangePart *range, RangePart *range_next, GateDev gt)
 {
     if (gate_closed(gt.halt)) return;
-    drop_commit_body<T>(x, accv, cnt, nvox, acc_lo);
+    drop_commit_body<T>(x, accv, cnt, nvox, acc_lo, range, range_next);
     gate_commit_end(gt);
 }
 
@@ -1531,11 +1622,11 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
                                                         const float *__restrict__ base, float *__restrict__ next,
                                                         const unsigned long long *__restrict__ pk_prev,
                                                         unsigned long long *pk_cur, unsigned long long *pk_old,
-                                                        int64_t lo, int64_t hi, double lambda,
+                                                        FusedRanges range, int64_t lo, int64_t hi, double lambda,
                                                         unsigned *status, int nvox)
 {
     if (int(blockIdx.x) < kCommitWG) {
-        commit_part(base, next, pk_prev, pk_old, nvox, int(blockIdx.x), kCommitWG);
+        commit_part(base, next, pk_prev, pk_old, range, nvox, int(blockIdx.x), kCommitWG);
         return;
     }
     using S = StoredChord<CT>;
@@ -1592,6 +1683,7 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
     }
     if (bad) raise_status(status, PCT_DEV_BAD_ROW);
     dot = group_sum<LPR>(dot);
+    TouchedRange touched;
     if (active && n2 > 0.0) {
         const double rho = lambda * (bi - dot) / n2;
 #pragma unroll
@@ -1599,6 +1691,7 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
             if (a + l + int64_t(k) * LPR < e) {
                 const int j = jr[k] & 0x7FFFFFFF;
                 atomicAdd(pk_cur + j, pack_contribution(rho * double(cr[k]), jr[k] < 0, status));
+                if (range.cur) touched.touch(j);
             }
         }
         for (int64_t q = a + l + int64_t(kRowRegs) * LPR; q < e; q += LPR) {
@@ -1606,8 +1699,10 @@ __global__ void __launch_bounds__(64) k_drop_rows_fused(RowsDev rows, const floa
             const int j = v & 0x7FFFFFFF;
             if (j >= nvox) continue;
             atomicAdd(pk_cur + j, pack_contribution(rho * double(S::get(chord[q])), v < 0, status));
+            if (range.cur) touched.touch(j);
         }
     }
+    if (range.cur) touched.publish(range.cur);
 }
 
 // First kernel of a stored-row block of the binned schedule, one wave per row:
@@ -2100,11 +2195,29 @@ void graph_release(pct_plan &pl)
     pl.cancel_stream = nullptr;
 }
 
+// Voxels from which a commit goes over its block's touched range, in the fused and
+// in the separate schedule.  Over the volume / over ranges, us a block step: FP16
+// rows by atomics, slab-ordered blocks of 400, on 256 x 256 x 64 20.5 / 17.2, x 128
+// 31.9 / 20.4, on 512^3 535 / 211, in acquisition order 24.3 / 25.4, 38.0 / 38.8 and
+// 560 / 550; FP64 rows traced, slab-ordered 18.9 / 20.8, x 128 22.5 / 21.4, x 256
+// 28.8 / 21.4, 512^3 179 / 61, in acquisition order 20.1 / 22.7, 23.0 / 25.9, 29.3 /
+// 31.6 and 183 / 186.
+constexpr int64_t kFusedRangeVoxels = int64_t(1) << 23, kRangeVoxels = int64_t(1) << 24;
+
+// Slot k of the touched ranges, nullptr below `from` voxels.
+static RangePart *range_slot(const pct_plan &pl, void *ws, int64_t from, int64_t k)
+{
+    if (pl.nvox < from) return nullptr;
+    const Layout L = layout_for(pl.nvox, pl.K, PCT_F32);
+    return reinterpret_cast<RangePart *>(wsb(ws) + L.partial) + (k % kRangeSlots) * kRangeParts;
+}
+
 // Buffers of the fused FP32 schedule: X[0] = x, X[1] in the workspace,
-// accumulators PK[0..2].
+// accumulators PK[0..2], range slots R[0..3] (nullptr: none).
 struct FusedBufs {
     float *X[2];
     unsigned long long *PK[3];
+    RangePart *R[kRangeSlots];
     int nv;
     unsigned copy_grid;
 };
@@ -2117,6 +2230,7 @@ static FusedBufs fused_bufs(const pct_plan &pl, void *ws, float *x)
     F.X[1] = reinterpret_cast<float *>(wsb(ws) + L.x1);
     for (int k = 0; k < 3; ++k)
         F.PK[k] = reinterpret_cast<unsigned long long *>(wsb(ws) + L.acc + size_t(k) * L.acc_stride);
+    for (int k = 0; k < kRangeSlots; ++k) F.R[k] = range_slot(pl, ws, kFusedRangeVoxels, k);
     F.nv = int(pl.nvox);
     F.copy_grid = unsigned(std::min<int64_t>(2048, (pl.nvox + 255) / 256));
     return F;
@@ -2128,11 +2242,13 @@ struct FusedStep {
     float *next;
     const unsigned long long *pk_prev;
     unsigned long long *pk_cur, *pk_old;
+    FusedRanges range;
 };
 
 static FusedStep fused_step(const FusedBufs &F, int64_t q)
 {
-    return FusedStep{F.X[q % 2], F.X[(q + 1) % 2], F.PK[(q + 2) % 3], F.PK[q % 3], F.PK[(q + 1) % 3]};
+    return FusedStep{F.X[q % 2],   F.X[(q + 1) % 2],  F.PK[(q + 2) % 3],
+                     F.PK[q % 3], F.PK[(q + 1) % 3], {F.R[q % 4], F.R[(q + 3) % 4], F.R[(q + 2) % 4], F.R[(q + 1) % 4]}};
 }
 
 // One fused sweep over blocks [b0, b1): copy, one launch per block (launch_q
@@ -2143,6 +2259,7 @@ static void enqueue_fused(pct_plan &pl, const FusedBufs &F, int64_t b0, int64_t 
                           hipStream_t s, bool record_events, int64_t every, LaunchQ launch_q)
 {
     hipLaunchKernelGGL(k_sweep_begin, dim3(F.copy_grid), dim3(256), 0, s, F.X[0], F.X[1], F.nv);
+    if (F.R[0]) hipLaunchKernelGGL(k_clear_ranges, dim3(1), dim3(kWave), 0, s, F.R[0]);
     int64_t q = 0;
     for (int64_t t = b0; t < b1; ++t, ++q) {
         const int64_t lo = t * block;
@@ -2158,7 +2275,7 @@ static void enqueue_fused(pct_plan &pl, const FusedBufs &F, int64_t b0, int64_t 
     if (q > 0) {
         const int64_t last = q - 1;
         hipLaunchKernelGGL(k_sweep_end, dim3(F.copy_grid), dim3(256), 0, s, F.X[0], F.X[q % 2], F.PK[last % 3],
-                           F.PK[(last + 2) % 3], F.nv);
+                           F.PK[(last + 2) % 3], F.R[last % 4], F.R[(last + 3) % 4], F.nv);
     }
 }
 
@@ -2371,7 +2488,6 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
     const PathSrc src = path_src(pl, wsb(ws) + L.table);
     const size_t rec_lds = record_bytes(src.nvmax, span);
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
-    int *hdr = reinterpret_cast<int *>(wsb(ws) + L.hdr);
     void *acc = wsb(ws) + L.acc;
     int32_t *cnt = reinterpret_cast<int32_t *>(wsb(ws) + L.cnt);
     GridDev g = grid_dev(pl.grid);
@@ -2382,12 +2498,17 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
     const bool det = sizeof(T) == 8 && (o.flags & PCT_DROP_DETERMINISTIC) != 0;
     long long *acc_lo = det ? reinterpret_cast<long long *>(wsb(ws) + L.acc + L.acc_stride) : nullptr;
 
-    // Separate schedule: block kernel + commit per block.
+    // Separate schedule: block kernel + commit per block.  (The one-lane kernel
+    // leaves no ranges: its rows take far longer than the volume.)
+    const bool ranges = lanes > 1 && pl.nvox >= kRangeVoxels;
     auto enqueue_sweep = [&](hipStream_t s, bool record_events) {
         int64_t seq = 0;
+        if (ranges) hipLaunchKernelGGL(k_clear_ranges, dim3(1), dim3(kWave), 0, s, range_slot(pl, ws, kRangeVoxels, 0));
         for (int64_t t = o.block_begin; t < o.block_end; ++t, ++seq) {
             int64_t lo = t * o.block;
             int64_t hi = std::min<int64_t>(n, lo + o.block);
+            RangePart *range = ranges ? range_slot(pl, ws, kRangeVoxels, seq) : nullptr;
+            RangePart *range_next = ranges ? range_slot(pl, ws, kRangeVoxels, seq + 1) : nullptr;
             const bool sample = record_events && (seq % every == 0) && pl.prof_used[0] < kProfSamples;
             if (sample) (void)hipEventRecord(prof_event(pl, 0, 2 * pl.prof_used[0]), s);
             if (lanes == 1)
@@ -2395,14 +2516,14 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
                                    cnt, src, g, lo, hi, o.lambda, status, acc_lo, gate.halt);
             else
                 hipLaunchKernelGGL((k_drop_block<T, CHORD, HULL>), dim3(row_grid(hi - lo)), dim3(kWave), rec_lds, s, p,
-                               b, x, acc, cnt, src, g, lo, hi, o.lambda, status, acc_lo, gate.halt, span);
+                               b, x, acc, cnt, src, g, lo, hi, o.lambda, status, acc_lo, gate.halt, span, range);
             if (sample) {
                 (void)hipEventRecord(prof_event(pl, 0, 2 * pl.prof_used[0] + 1), s);
                 pl.prof_used[0]++;
                 (void)hipEventRecord(prof_event(pl, 1, 2 * pl.prof_used[1]), s);
             }
             hipLaunchKernelGGL(k_drop_commit<T>, dim3(commit_grid), dim3(kWG), 0, s, x, acc, cnt, int(pl.nvox),
-                               acc_lo, gate);
+                               acc_lo, range, range_next, gate);
             if (sample) {
                 (void)hipEventRecord(prof_event(pl, 1, 2 * pl.prof_used[1] + 1), s);
                 pl.prof_used[1]++;
@@ -2440,7 +2561,8 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
                               [&](hipStream_t s, int64_t, int64_t lo, int64_t hi, const FusedStep &f) {
                                   hipLaunchKernelGGL((k_drop_fused<CHORD, HULL>),
                                                      dim3(kCommitWG + row_grid(hi - lo)), dim3(kWave), rec_lds, s,
-                                                     p, b, f.base, f.next, f.pk_prev, f.pk_cur, f.pk_old, src, g, lo, hi, o.lambda, status, F.nv, span);
+                                                     p, b, f.base, f.next, f.pk_prev, f.pk_cur, f.pk_old, f.range, src, g, lo, hi,
+                                                     o.lambda, status, F.nv, span);
                               });
                 return;
             }
@@ -2617,8 +2739,7 @@ static void launch_rows_fused(int lanes, hipStream_t s, const RowsDev &rows, con
     case LPR: {                                                                                                  \
         const unsigned grid = unsigned(kCommitWG + (n + (64 / LPR) - 1) / (64 / LPR));                        \
         hipLaunchKernelGGL((k_drop_rows_fused<CT, LPR>), dim3(grid), dim3(64), 0, s, rows, b, f.base, f.next,     \
-                           f.pk_prev, f.pk_cur, f.pk_old, lo, hi, lambda,                                          \
-                           status, nvox);                                                                        \
+                           f.pk_prev, f.pk_cur, f.pk_old, f.range, lo, hi, lambda, status, nvox);                \
         break;                                                                                                   \
     }
         PCT_LAUNCH_ROWS(16)
