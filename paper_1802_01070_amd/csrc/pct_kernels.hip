@@ -2750,6 +2750,25 @@ static void launch_rows_fused(int lanes, hipStream_t s, const RowsDev &rows, con
     }
 }
 
+// Whether a call's stored rows go by bins, the same sums as by atomics, so the same
+// x.  Not where paths at 45 degrees have more pieces than k_rows_bin holds (the
+// others go by overflow words, piece by piece, and its commit then reads the
+// volume), and not where blocks are small for the volume, whose commit goes over
+// all windows where that of the fused schedule goes over the block's range.  By
+// bins / by atomics, us a block step: 3200 rows of 290 pieces on 200 x 200 x 32
+// 29.4 / 33.2, of 650 on 512 x 512 x 16 87 / 69 and of 1030 on 800 x 800 x 16
+// 204 / 160; slab-ordered blocks of 400 rows on 256 x 256 x 64 19.2 / 20.6, x 128
+// 26.6 / 20.4, x 256 40.1 / 28.5; in acquisition order
+// 19.8 / 24.3, 26.6 / 39.0 and 39.4 / 86.2.
+static bool rows_by_bins(const pct_plan &pl, int64_t block)
+{
+    const double depth = pl.mlp.u_out - pl.mlp.u_in;
+    const double pieces = std::min(M_SQRT2 * depth / std::min(pl.grid.pitch[0], pl.grid.pitch[1]),
+                                   double(pl.grid.nx) + double(pl.grid.ny)) +
+                          std::min(0.03 * depth / pl.grid.pitch[2], double(pl.grid.nz));
+    return pieces <= kBinRegs * kWave && block >= pl.nvox / 16384;
+}
+
 int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *x, const pct_drop_opts &o, void *ws,
                      size_t ws_bytes, void *stream)
 {
@@ -2766,10 +2785,8 @@ int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     const RowsDev rd{reinterpret_cast<const long long *>(rows.offsets), rows.vox, rows.chord, rows.n2};
     const int64_t n = rows.n;
-    // by bins unless the call names its lanes per row: the same sums, so the same x
-    // (a 3200-row block of the 200 x 200 x 32 scan: 29.4 us against 33.2)
-    BinnedCall B;
-    if (o.lanes == 0) B = binned_call(pl, x, ws, ws_bytes, o.block, nblk * o.n_iter, false);
+    BinnedCall B;  // unless the call names its lanes per row
+    if (o.lanes == 0 && rows_by_bins(pl, o.block)) B = binned_call(pl, x, ws, ws_bytes, o.block, nblk * o.n_iter, false);
     int *axis = reinterpret_cast<int *>(wsb(ws) + L.hdr) + kHdrAxis;
     const GridDev g = grid_dev(pl.grid);
     auto bin = [&](auto chord, hipStream_t s, int64_t lo, int64_t hi, const BinsDev &bins, int par, hipEvent_t e0,
