@@ -285,13 +285,27 @@ __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first
             if (k0 + B::kSteps >= K) walk.finish(s);
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < B::kSlots; q += kWG) {
-            const int k = keys[q / B::kLine];
-            if (k < 0) continue;
-            const T v = vals[q];
-            if (v != T(0)) atomicAdd(gout + (k * B::kLine + q % B::kLine), v);
-            vals[q] = T(0);
-            if (q % B::kLine == 0) keys[q / B::kLine] = -1;
+        // (four keys and sums read before any is used: one after the other, a call of
+        // few workgroups waits for LDS 32 times a part; eight of them take more
+        // registers than four waves a SIMD have)
+        constexpr int kFlush = 4;
+        static_assert(B::kSlots % (kFlush * kWG) == 0);
+        for (int q0 = threadIdx.x; q0 < B::kSlots; q0 += kFlush * kWG) {
+            int key[kFlush];
+            T sum[kFlush];
+#pragma unroll
+            for (int u = 0; u < kFlush; ++u) {
+                key[u] = keys[(q0 + u * kWG) / B::kLine];
+                sum[u] = vals[q0 + u * kWG];
+            }
+#pragma unroll
+            for (int u = 0; u < kFlush; ++u) {
+                const int q = q0 + u * kWG;
+                if (key[u] < 0) continue;
+                if (sum[u] != T(0)) atomicAdd(gout + (key[u] * B::kLine + q % B::kLine), sum[u]);
+                vals[q] = T(0);
+                if (q % B::kLine == 0) keys[q / B::kLine] = -1;
+            }
         }
     }
 }
