@@ -86,7 +86,7 @@ __global__ void k_gate_begin(GateDev gt)
 template <bool HULL, class Sink>
 __device__ __forceinline__ bool walk_row(const Rec &r, const PathSrc &src, const GridDev &g, Sink &sink)
 {
-    const LanePath<HULL> path(src, g, r);
+    const RowPath<HULL> path(src, g, r);
     LaneWalk<HULL> walk(path, g, r);
     walk.run(0, path.K, sink);
     walk.finish(sink);
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first
             }
         }
     }
-    const LanePath<HULL> path(src, g, r);
+    const RowPath<HULL> path(src, g, r);
     LaneWalk<HULL> walk(path, g, r);
     HashScatterSink<T> s{(LdsPtr<int>)keys, (LdsPtr<T>)vals, (HbmPtr<T>)gout, ri, false};
     const int K = active ? path.K : 0;
@@ -1588,7 +1588,7 @@ __global__ void __launch_bounds__(kWG) k_rows_build(ProtonsDev p, int64_t n, con
             r = Rec{};
         }
     }
-    const LanePath<HULL> path(src, g, r);
+    const RowPath<HULL> path(src, g, r);
     LaneWalk<HULL> walk(path, g, r);
     RowSink<CT> rs{&stage, vox, chord, mine ? offsets[i] : 0, mine ? offsets[i + 1] : 0, Reentry(lds, r), 0.0};
     const int K = active ? path.K : 0;

@@ -14,62 +14,14 @@
 
 namespace pct {
 
-// Path of one row in voxel units; o: the grid's corner in them.
-template <bool HULL>
-struct LanePath {
-    RowPath<HULL> row;
-    double o[3];
-    int K;
-    __device__ __forceinline__ LanePath(const PathSrc &src, const GridDev &g, const Rec &r)
-        : row(src, g, r), K(row.K)
-    {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) o[a] = g.lo[a] * g.inv_pitch[a];
-    }
-    __device__ __forceinline__ void place(int k, double w[3]) const
-    {
-        row.place(k, row.fetch(k), w[0], w[1], w[2]);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) w[a] *= row.g.inv_pitch[a];
-    }
-};
-
-// The shared table's path: the record and the turn to the lab scaled once.
-template <>
-struct LanePath<false> {
-    const PathSrc &src;
-    double t[4], v[4];       // t_in, th_in, t_out, th_out; the same of v in voxels
-    double cx, sx, cy, sy;   // cos, sin in voxels a mm along x and y
-    double o[3];
-    int K;
-    __device__ __forceinline__ LanePath(const PathSrc &src_, const GridDev &g, const Rec &r) : src(src_), K(src_.K)
-    {
-        t[0] = r.t_in, t[1] = r.th_in, t[2] = r.t_out, t[3] = r.th_out;
-        v[0] = r.v_in * g.inv_pitch[2], v[1] = r.ph_in * g.inv_pitch[2];
-        v[2] = r.v_out * g.inv_pitch[2], v[3] = r.ph_out * g.inv_pitch[2];
-        cx = r.cs * g.inv_pitch[0], sx = r.sn * g.inv_pitch[0];
-        cy = r.cs * g.inv_pitch[1], sy = r.sn * g.inv_pitch[1];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) o[a] = g.lo[a] * g.inv_pitch[a];
-    }
-    __device__ __forceinline__ void place(int k, double w[3]) const
-    {
-        const double *__restrict__ c = src.tab + k * kRowDoubles;
-        const double tt = fma(c[0], t[0], fma(c[1], t[1], fma(c[2], t[2], c[3] * t[3])));
-        w[2] = fma(c[0], v[0], fma(c[1], v[1], fma(c[2], v[2], c[3] * v[3])));
-        w[0] = fma(c[4], cx, -tt * sx);
-        w[1] = fma(c[4], sy, tt * cy);
-    }
-};
-
 // The walk.  run() takes the segments [k0, k1) and hands every finished piece
 // that lies in the grid to sink.piece(j, ix, iy, iz, chord), consecutive parts
 // in a voxel as one; finish() hands over the last.
 template <bool HULL>
 struct LaneWalk {
-    const LanePath<HULL> &p;
+    const RowPath<HULL> &p;
     const GridDev &g;
-    double w[3];    // the path's position (voxels)
+    double w[3];    // the path's position (mm)
     double f[3];    // and its voxel, from -1 to n
     int i[3];
     unsigned j;     // linear index of it (wraps outside the grid)
@@ -78,10 +30,10 @@ struct LaneWalk {
     int dom;
     double sgn;
 
-    __device__ __forceinline__ LaneWalk(const LanePath<HULL> &path, const GridDev &grid, const Rec &r)
+    __device__ __forceinline__ LaneWalk(const RowPath<HULL> &path, const GridDev &grid, const Rec &r)
         : p(path), g(grid), c(0.0), onward(true), dom(dominant_axis(r)), sgn((dom ? r.sn : r.cs) > 0.0 ? 1.0 : -1.0)
     {
-        p.place(0, w);
+        place(0, w);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             f[a] = voxel(a, w[a]);
@@ -89,10 +41,12 @@ struct LaneWalk {
         }
         j = unsigned(i[0]) + unsigned(g.n[0]) * (unsigned(i[1]) + unsigned(g.n[1]) * unsigned(i[2]));
     }
+    __device__ __forceinline__ void place(int k, double x[3]) const { p.place(k, p.fetch(k), x[0], x[1], x[2]); }
     __device__ __forceinline__ double voxel(int a, double x) const
     {
-        return fmin(fmax(floor(x - p.o[a]), -1.0), double(g.n[a]));
+        return fmin(fmax(floor((x - g.lo[a]) * g.inv_pitch[a]), -1.0), double(g.n[a]));
     }
+    __device__ __forceinline__ double plane(int a, double x) const { return fma(x, g.pitch[a], g.lo[a]); }
     template <class Sink>
     __device__ __forceinline__ void leave(Sink &sink)
     {
@@ -112,20 +66,19 @@ struct LaneWalk {
         const unsigned stride[3] = {1u, unsigned(g.n[0]), unsigned(g.n[0]) * unsigned(g.n[1])};
         for (int k = k0; k < k1; ++k) {
             double w1[3], f1[3], d[3], at[3];
-            p.place(k + 1, w1);
+            place(k + 1, w1);
             double len2 = 0.0;
             bool far = false;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 d[a] = w1[a] - w[a];
                 f1[a] = voxel(a, w1[a]);
-                const double mm = d[a] * g.pitch[a];
-                len2 = fma(mm, mm, len2);
+                len2 = fma(d[a], d[a], len2);
             }
             if (k + 1 == p.K) {  // a path that ends on a plane has not crossed it
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    if (d[a] > 0.0 && w1[a] == f1[a] + p.o[a]) f1[a] -= 1.0;
+                    if (d[a] > 0.0 && w1[a] == plane(a, f1[a])) f1[a] -= 1.0;
             }
             onward = onward && (dom ? d[1] : d[0]) * sgn > 0.0;
             const double len = fast_sqrt(len2);
@@ -139,7 +92,7 @@ struct LaneWalk {
                 // plane and its vertices' last bits cross it: there the quotient is
                 // of two rounding errors)
                 if (e[a] != 0)
-                    at[a] = fmin(fmax((fmax(f[a], f1[a]) + p.o[a] - w[a]) * fast_rcp(d[a]), 0.0), 1.0);
+                    at[a] = fmin(fmax((plane(a, fmax(f[a], f1[a])) - w[a]) * fast_rcp(d[a]), 0.0), 1.0);
             }
             double last = 0.0;
             if (!__any(far)) {
@@ -158,8 +111,8 @@ struct LaneWalk {
             } else {
                 double inv[3];
                 auto next = [&](int a) {
-                    const double plane = double(i[a]) + (e[a] > 0 ? 1.0 : 0.0) + p.o[a];
-                    at[a] = e[a] == 0 ? 2.0 : fmin(fmax((plane - w[a]) * inv[a], last), 1.0);
+                    const double to = plane(a, double(i[a]) + (e[a] > 0 ? 1.0 : 0.0));
+                    at[a] = e[a] == 0 ? 2.0 : fmin(fmax((to - w[a]) * inv[a], last), 1.0);
                 };
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
