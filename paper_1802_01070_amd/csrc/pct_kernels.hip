@@ -198,9 +198,9 @@ __global__ void __launch_bounds__(kWG) k_forward(ProtonsDev p, int64_t first, in
 // and an angle-sorted scan's consecutive rows cross nearly the same voxels, so
 // the workgroup sums its pieces in an LDS table.  Its key is a line of eight
 // consecutive voxels (open addressing, a few probes): the table then reaches HBM
-// line by line, eight lanes to one request.  The rows advance together, kSteps
+// line by line, eight lanes to one request.  The rows advance together, `steps`
 // segments at a time, and the table is emptied after each such part: the voxels
-// of a part fit it, where those of whole rows (22 000 of the head scan's 256 rows)
+// of a part of eight fit it, where those of whole rows (22 000 of the head scan's 256 rows)
 // would not.  A piece that finds no slot goes straight to HBM, and so do the later
 // pieces of its lane in that part (a scan in acquisition order).
 // 2e6 rows of 220 segments on the 256 x 256 x 64 grid, FP32 / FP64: sorted 5.3 /
@@ -214,7 +214,6 @@ struct BpTable {
     static constexpr int kKeys = 1 << kBits;
     static constexpr int kSlots = kKeys * kLine;
     static constexpr int kProbes = 4;
-    static constexpr int kSteps = 8;
 };
 
 template <typename T>
@@ -249,8 +248,8 @@ struct HashScatterSink {
 
 template <typename T, bool HULL>
 __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first, int64_t n,
-                                                     const T *__restrict__ rv, T *gout, const PathSrc src, GridDev g,
-                                                     unsigned *status)
+                                                     const T *__restrict__ rv, T *gout, int steps, const PathSrc src,
+                                                     GridDev g, unsigned *status)
 {
     using B = BpTable<T>;
     __shared__ int keys[B::kKeys];
@@ -278,11 +277,11 @@ __global__ void __launch_bounds__(kWG) k_backproject(ProtonsDev p, int64_t first
     LaneWalk<HULL> walk(path, g, r);
     HashScatterSink<T> s{(LdsPtr<int>)keys, (LdsPtr<T>)vals, (HbmPtr<T>)gout, ri, false};
     const int K = active ? path.K : 0;
-    for (int k0 = 0; __syncthreads_or(k0 < K); k0 += B::kSteps) {
+    for (int k0 = 0; __syncthreads_or(k0 < K); k0 += steps) {
         s.full = false;
         if (k0 < K) {
-            walk.run(k0, min(k0 + B::kSteps, K), s);
-            if (k0 + B::kSteps >= K) walk.finish(s);
+            walk.run(k0, min(k0 + steps, K), s);
+            if (k0 + steps >= K) walk.finish(s);
         }
         __syncthreads();
         // (four keys and sums read before any is used: one after the other, a call of
@@ -2089,17 +2088,22 @@ int launch_backproject(const pct_plan &pl, const ProtonsDev &p, int64_t n, const
     const PathSrc src = path_src(pl, wsb(ws) + L.table);
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     GridDev g = grid_dev(pl.grid);
+    // parts of 32 segments for calls of few workgroups, which wait for every part's
+    // barriers and never for HBM's atomics: 1e4 rows, FP32 / FP64, sorted on 256 x 256
+    // x 64 418 / 419 us by parts of 8, 402 / 385 of 32, in acquisition order on 200 x
+    // 200 x 32 555 / 499 and 390 / 341
+    const int steps = n <= 16384 ? 32 : 8;
     auto go = [&](auto hull) {
         constexpr bool H = decltype(hull)::value;
         launch_pieces(n, [&](int64_t first, int64_t cnt) {
             if (dtype == PCT_F64)
                 hipLaunchKernelGGL((k_backproject<double, H>), dim3(grid_for(cnt)), dim3(kWG), 0, s, p, first,
-                                   first + cnt, static_cast<const double *>(r), static_cast<double *>(gout), src,
-                                   g, status);
+                                   first + cnt, static_cast<const double *>(r), static_cast<double *>(gout),
+                                   steps, src, g, status);
             else
                 hipLaunchKernelGGL((k_backproject<float, H>), dim3(grid_for(cnt)), dim3(kWG), 0, s, p, first,
-                                   first + cnt, static_cast<const float *>(r), static_cast<float *>(gout), src, g,
-                                   status);
+                                   first + cnt, static_cast<const float *>(r), static_cast<float *>(gout),
+                                   steps, src, g, status);
         });
     };
     if (src.hull)
