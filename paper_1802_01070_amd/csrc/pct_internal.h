@@ -1,6 +1,8 @@
 // Internal declarations shared by the host entry points and the HIP kernels.
 #pragma once
 
+#include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
@@ -78,6 +80,30 @@ inline size_t bin_bytes(int64_t records, int nslab)
 {
     const size_t nrow = size_t(nslab) * size_t(bin_rows(records));
     return (nrow * kBinCap * 8 + size_t(bin_rows(records)) * 12 + 255) & ~size_t(255);
+}
+
+// LDS of the wave kernels' rows (pct_walk.hpp): the length of every segment, and a
+// window of `span` records and their segments with a few on either side.
+constexpr int kWave = 64;
+constexpr int kRecPad = 16;       // records before a window kept for looking back
+constexpr int kLookAhead = 2;     // records after a window
+constexpr int kRecBytes = 18;     // a record and its segment
+constexpr int kMaxRowSegments = 2400;
+constexpr size_t kRowLds = 65536;  // what a workgroup may have without asking for more
+inline size_t record_bytes(int segments, int span)
+{
+    return size_t((segments + 1) & ~1) * sizeof(double) + size_t(span + kRecPad + 1 + kLookAhead) * kRecBytes;
+}
+// Records of a row's window: enough for a path across the grid at 45 degrees,
+// with room for what it does outside and for its slope along z, as far as kRowLds
+// goes (3520 records beside 220 segments); a row with more takes several windows.
+inline int record_span(const pct_grid &g, double depth, int segments)
+{
+    const double lateral = std::min(1.5 * depth / std::min(g.pitch[0], g.pitch[1]), double(g.nx) + double(g.ny));
+    const double along_z = std::min(0.25 * depth / g.pitch[2], double(g.nz));
+    const double want = std::ceil((lateral + along_z + 24.0) / kWave);
+    const int most = int((kRowLds - record_bytes(segments, 0)) / (kRecBytes * kWave));
+    return kWave * int(std::min(std::max(want, 1.0), double(most)));
 }
 
 // header words (int32 index): status word, the two overflow flags of the

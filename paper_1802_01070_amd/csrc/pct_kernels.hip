@@ -2186,19 +2186,6 @@ static int slab_window_words()
 // row_of_workgroup).
 static inline unsigned row_grid(int64_t n) { return unsigned(8 * ((n + 7) / 8)); }
 
-// Records of a row's window: enough for a path across the grid at 45 degrees,
-// with room for what it does outside and for its slope along z, in at most 64
-// KB of LDS (a row with more takes several windows).
-static int record_span(const pct_plan &pl)
-{
-    const double depth = pl.mlp.u_out - pl.mlp.u_in;
-    const double lateral = std::min({1.5 * depth / std::min(pl.grid.pitch[0], pl.grid.pitch[1]),
-                                     double(pl.grid.nx) + double(pl.grid.ny)});
-    const double along_z = std::min(0.25 * depth / pl.grid.pitch[2], double(pl.grid.nz));
-    const double want = std::ceil((lateral + along_z + 24.0) / kWave);
-    return kWave * int(std::min(std::max(want, 1.0), 60.0));
-}
-
 // Block steps of a call from which the iterate is packed (see IterateDev).
 constexpr int64_t kPackBlocks = 8;
 
@@ -2499,11 +2486,11 @@ static int drop_loop(pct_plan &pl, const ProtonsDev &p, int64_t n, const float *
     // one lane per row on request, and where the wave kernels' records do not
     // hold the row; else a wave per row
     const int lanes = o.lanes == 1 || grid_dev(pl.grid).xy_shift == 0 || pl.K > kMaxRowSegments ? 1 : kWave;
-    const int span = record_span(pl);
     const int64_t nblk = o.block_end - o.block_begin;
     const int64_t every = std::max<int64_t>(1, (nblk + kProfSamples - 1) / kProfSamples);
     Layout L = layout_for(pl.nvox, pl.K, o.dtype);
     const PathSrc src = path_src(pl, wsb(ws) + L.table);
+    const int span = record_span(pl.grid, pl.mlp.u_out - pl.mlp.u_in, std::min(src.nvmax, kMaxRowSegments + 3));
     const size_t rec_lds = record_bytes(src.nvmax, span);
     unsigned *status = reinterpret_cast<unsigned *>(wsb(ws) + L.hdr) + kHdrStatus;
     void *acc = wsb(ws) + L.acc;

@@ -22,10 +22,6 @@
 
 namespace pct {
 
-constexpr int kWave = 64;
-constexpr int kRecPad = 16;       // records before a window kept for looking back
-constexpr int kLookAhead = 2;     // records after a window
-
 // A crossing: its distance from the start of its segment (mm), and the voxel
 // after it (ix + iy 2^xy_shift, iz; indices run from -1 to n, one past the grid
 // each way).
@@ -33,7 +29,7 @@ struct RowRec {
     double s;
     int xy, z;
 };
-constexpr int kMaxRowSegments = 2400;  // segments of a row whose lengths fit LDS beside its records
+static_assert(sizeof(RowRec) + sizeof(unsigned short) == kRecBytes, "record_bytes reckons with it");
 
 // The two fields of a packed in-plane index.
 __device__ __forceinline__ int pack_xy(const GridDev &g, int ix, int iy) { return ix + iy * (1 << g.xy_shift); }
@@ -231,11 +227,6 @@ struct RecWindow {
         return c;
     }
 };
-inline size_t record_bytes(int segments, int span)
-{
-    return size_t((segments + 1) & ~1) * sizeof(double) +
-           size_t(span + kRecPad + 1 + kLookAhead) * (sizeof(RowRec) + sizeof(unsigned short));
-}
 
 // Crossings of one segment that passes more than one plane of an axis: one
 // after the other.
