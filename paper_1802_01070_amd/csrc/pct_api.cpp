@@ -93,7 +93,8 @@ PathSrc path_src(const pct_plan &pl, const void *table_dev)
     return p;
 }
 
-// tracker segment, hull-to-hull MLP (at most K segments), tracker segment
+// With a hull the path has three parts, each of a whole number of steps from its
+// start and a shorter rest: at most K + 2 segments, K + 3 vertices.
 int path_vertices_max(const pct_plan &pl) { return pl.K + 1 + (pl.hull ? 2 : 0); }
 
 // ---------------------------------------------------------------------------

@@ -131,15 +131,11 @@ __global__ void __launch_bounds__(kWG) k_trace(ProtonsDev p, int64_t first, int6
 // ---------------------------------------------------------------------------
 // forward projection
 // ---------------------------------------------------------------------------
-// Value of the iterate at voxel j seen by a block.  load() issues the read,
-// value() consumes it.
+// Value of the iterate at voxel j seen by a block.
 template <typename T>
 struct PlainX {
-    using Raw = T;
     const T *__restrict__ x;
-    __device__ __forceinline__ Raw load(int j) const { return x[j]; }
-    __device__ __forceinline__ static double value(Raw v) { return double(v); }
-    __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
+    __device__ __forceinline__ double operator()(int j) const { return double(x[j]); }
 };
 
 // The value read for a piece is used when the next piece comes, so the reads
@@ -630,15 +626,9 @@ __device__ __forceinline__ float committed_value(float base, unsigned long long 
 }
 
 struct LazyX {
-    struct Raw {
-        float base;
-        unsigned long long pk;
-    };
     const float *__restrict__ base;
     const unsigned long long *__restrict__ pk;
-    __device__ __forceinline__ Raw load(int j) const { return Raw{base[j], pk[j]}; }
-    __device__ __forceinline__ static double value(const Raw &v) { return double(committed_value(v.base, v.pk)); }
-    __device__ __forceinline__ double operator()(int j) const { return value(load(j)); }
+    __device__ __forceinline__ double operator()(int j) const { return double(committed_value(base[j], pk[j])); }
 };
 
 // Range slots of a fused launch (nullptr: the commit goes over the volume).
@@ -2680,12 +2670,12 @@ int launch_rows_count(const pct_plan &pl, const ProtonsDev &p, int64_t n, int64_
     long long *off = reinterpret_cast<long long *>(offsets);
     hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(64), 0, s, off, int64_t(1));
     if (n > 0) {
-if (src.hull)
-                    hipLaunchKernelGGL(k_row_lengths<true>, dim3(grid_for(n)), dim3(kWG), 0, s, p, n, off + 1, src,
-                           grid_dev(pl.grid), status);
+        if (src.hull)
+            hipLaunchKernelGGL(k_row_lengths<true>, dim3(grid_for(n)), dim3(kWG), 0, s, p, n, off + 1, src,
+                               grid_dev(pl.grid), status);
         else
-                    hipLaunchKernelGGL(k_row_lengths<false>, dim3(grid_for(n)), dim3(kWG), 0, s, p, n, off + 1, src,
-                           grid_dev(pl.grid), status);
+            hipLaunchKernelGGL(k_row_lengths<false>, dim3(grid_for(n)), dim3(kWG), 0, s, p, n, off + 1, src,
+                               grid_dev(pl.grid), status);
         const int64_t G = std::max<int64_t>(1, std::min<int64_t>(kMaxPartials, (n + kSelWG - 1) / kSelWG));
         int64_t chunk = (n + G - 1) / G;
         chunk = std::max<int64_t>(kSelWG, (chunk + kSelWG - 1) / kSelWG * kSelWG);

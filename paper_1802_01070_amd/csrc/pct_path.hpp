@@ -133,9 +133,8 @@ __device__ __forceinline__ bool hull_cross(const PathSrc &m, const Rec &r, doubl
 }
 
 struct PathState {
-    int nv;         // vertices
-    int pre, kh;    // leading tracker vertex (0/1), MLP segments inside the hull
-    bool miss;      // the tracks do not reach the hull: one straight segment
+    int kh;         // MLP segments inside the hull
+    bool miss;      // the tracks do not reach the hull: one straight path
     double uh_in, uh_out, t0, v0, t1, v1;
 };
 
@@ -151,14 +150,10 @@ __device__ __forceinline__ PathState hull_prepare(const Rec &r, const PathSrc &m
     ps.uh_out = fmin(fmax(u2, m.u_in), m.u_out);
     if (!hit || !(ps.uh_out > ps.uh_in)) {
         ps.miss = true;
-        ps.nv = 2;
         return ps;
     }
     const double D = ps.uh_out - ps.uh_in;
     ps.kh = max(1, int(ceil(D / m.step)));
-    ps.pre = ps.uh_in > m.u_in ? 1 : 0;
-    const int post = ps.uh_out < m.u_out ? 1 : 0;
-    ps.nv = ps.pre + ps.kh + 1 + post;
     ps.t0 = r.t_in + r.th_in * (ps.uh_in - m.u_in);
     ps.v0 = r.v_in + r.ph_in * (ps.uh_in - m.u_in);
     ps.t1 = r.t_out + r.th_out * (ps.uh_out - m.u_out);
@@ -169,33 +164,17 @@ __device__ __forceinline__ PathState hull_prepare(const Rec &r, const PathSrc &m
 template <bool HULL>
 __device__ __forceinline__ PathState path_prepare(const Rec &r, const PathSrc &m)
 {
-    if constexpr (HULL) {
+    if constexpr (HULL)
         return hull_prepare(r, m);
-    } else {
-        PathState ps{};
-        ps.nv = m.K + 1;
-        return ps;
-    }
+    else
+        return PathState{};
 }
 
-// Vertex k of a hull path in the beam frame.
-__device__ __forceinline__ void hull_point(const Rec &r, const PathSrc &m, const PathState &ps, int k, double &u,
+// Vertex j (0 <= j <= kh) of the part of a path inside the hull, in the beam frame.
+__device__ __forceinline__ void hull_point(const Rec &r, const PathSrc &m, const PathState &ps, int j, double &u,
                                            double &t, double &v)
 {
-    const int j = k - ps.pre;
-    if (ps.miss) {
-        u = k == 0 ? m.u_in : m.u_out;
-        t = k == 0 ? r.t_in : r.t_out;
-        v = k == 0 ? r.v_in : r.v_out;
-    } else if (j < 0) {
-        u = m.u_in;
-        t = r.t_in;
-        v = r.v_in;
-    } else if (j > ps.kh) {
-        u = m.u_out;
-        t = r.t_out;
-        v = r.v_out;
-    } else if (j == 0) {
+    if (j == 0) {
         u = ps.uh_in;
         t = ps.t0;
         v = ps.v0;

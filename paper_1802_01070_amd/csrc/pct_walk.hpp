@@ -179,7 +179,7 @@ struct RowPath {
                 t = r.t_out - r.th_out * (src.u_out - u);
                 v = r.v_out - r.ph_out * (src.u_out - u);
             } else {
-                hull_point(r, src, ps, k - k_in + ps.pre, u, t, v);
+                hull_point(r, src, ps, k - k_in, u, t, v);
             }
         } else {
             t = c.c[0] * r.t_in + c.c[1] * r.th_in + c.c[2] * r.t_out + c.c[3] * r.th_out;
