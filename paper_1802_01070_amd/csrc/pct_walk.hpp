@@ -416,9 +416,12 @@ __device__ __forceinline__ void row_pieces(const RowPath<HULL> &p, RecWindow &wi
             q.first = true;
             q.before = 0.0;
             if (shape.turns) {
-                const int want = shape.onward ? q.k : i, stored = i - lo + min(lo, kRecPad);
-                const int back = q.real ? min(want, stored) : 0;
-                if (lo > 0) shape.cut |= __any(q.real && want > stored);
+                int back = !q.real ? 0 : shape.onward ? q.k : i;
+                if (lo > 0) {
+                    const int stored = i - lo + min(lo, kRecPad);
+                    shape.cut |= __any(back > stored);
+                    back = min(back, stored);
+                }
                 for (int d = 2; d <= back; ++d) {
                     const RowRec *e = win.at(i - d);
                     if (e->xy != a.xy || e->z != a.z) continue;
