@@ -199,10 +199,11 @@ __global__ void __launch_bounds__(kWG) k_forward(ProtonsDev p, int64_t first, in
 // of a part of eight fit it, where those of whole rows (22 000 of the head scan's 256 rows)
 // would not.  A piece that finds no slot goes straight to HBM, and so do the later
 // pieces of its lane in that part (a scan in acquisition order).
-// 2e6 rows of 220 segments on the 256 x 256 x 64 grid, FP32 / FP64: sorted 5.3 /
-// 4.8 ms (18.0 / 18.0 with a table keyed by voxel for the whole row; 12.4 / 11.0
-// with that key in parts; lines of 4: 6.2, of 16: 6.3; 5.1 without the flush);
-// acquisition order 17.5 / 18.0 ms (26.0 / 23.1; parts of 16 segments 20.5).
+// 2e6 rows of 220 segments on the 256 x 256 x 64 grid, FP32 / FP64: sorted 5.04 /
+// 4.72 ms (5.3 / 4.8 with the slots emptied one by one, and then 6.2 with lines of
+// 4, 6.3 of 16; 18.0 / 18.0 with a table keyed by voxel for the whole row; 12.4 /
+// 11.0 with that key in parts); acquisition order 17.5 / 18.0 ms (26.0 / 23.1;
+// parts of 16 segments 20.5).
 template <typename T>
 struct BpTable {
     static constexpr int kLine = 8;       // consecutive voxels of a key
@@ -813,7 +814,7 @@ __device__ __forceinline__ unsigned udiv_exact(unsigned j, unsigned d, double in
 // Bound by VALU issue: about 1600 instructions a row (records 270 per round of 64
 // segments, pieces 80 per round of 64 records, 250 to read the record and form
 // its frame), 17 us at 6400 rows, the rest latency at four waves a SIMD.  One
-// wave per row: 36.0 us for a 6400-row block of the 256 x 256 x 64 scan and 19.6
+// wave per row: 35.2 us for a 6400-row block of the 256 x 256 x 64 scan and 18.9
 // us for 3200 rows on 200 x 200 x 32, against 61.2 and 33.4 us with each lane
 // walking a run of slabs of its own (3700 instructions a row, the lanes' segments
 // clipped and set up one by one) and 45 us with the same lanes carrying their
