@@ -410,8 +410,7 @@ int pct_rows_build(const pct_plan *plan, const pct_protons *p, int32_t chord_typ
 /* Block-iterative DROP over stored rows: as pct_drop_iterate, with the rows
  * read instead of traced.  FP32 x only (PCT_ERR_UNSUPPORTED otherwise);
  * opts->chord must equal rows->chord_type; opts->lanes: 0 (by slab bins where
- * the workspace holds a block's, rows are not longer than 512 pieces and blocks
- * not small for the volume, else 64), or 16, 32 or 64 lanes per row with
+ * the workspace holds a block's and they take less time than atomics, else 64), or 16, 32 or 64 lanes per row with
  * atomics, the same x bit for bit with 64; PCT_DROP_SEPARATE_COMMIT and PCT_DROP_CANCELLABLE are not
  * supported (PCT_ERR_UNSUPPORTED). */
 int pct_drop_iterate_rows(const pct_plan *plan, const pct_rows *rows, const float *b, void *x,

@@ -2193,12 +2193,13 @@ void graph_release(pct_plan &pl)
 
 // Voxels from which a commit goes over its block's touched range, in the fused and
 // in the separate schedule.  Over the volume / over ranges, us a block step: FP16
-// rows by atomics, slab-ordered blocks of 400, on 256 x 256 x 64 20.5 / 17.2, x 128
-// 31.9 / 20.4, on 512^3 535 / 211, in acquisition order 24.3 / 25.4, 38.0 / 38.8 and
-// 560 / 550; FP64 rows traced, slab-ordered 18.9 / 20.8, x 128 22.5 / 21.4, x 256
-// 28.8 / 21.4, 512^3 179 / 61, in acquisition order 20.1 / 22.7, 23.0 / 25.9, 29.3 /
-// 31.6 and 183 / 186.
-constexpr int64_t kFusedRangeVoxels = int64_t(1) << 23, kRangeVoxels = int64_t(1) << 24;
+// rows by atomics, slab-ordered blocks of 250 on 256 x 256 x 64 19.4 / 13.8, of 400 x
+// 128 31.9 / 20.4, on 512^3 535 / 211, blocks of one angle over all slices, 250 x 64
+// 22.4 / 23.1, 3200 x 64 58.2 / 59.9, x 96 72.6 / 74.1; FP64 rows traced, slab-
+// ordered 400 on 256 x 256 x 64 18.9 / 20.8, x 128 22.5 / 21.4, x 256 28.8 / 21.4,
+// 512^3 179 / 61, in acquisition order 20.1 / 22.7, 23.0 / 25.9, 29.3 / 31.6 and 183 /
+// 186.
+constexpr int64_t kFusedRangeVoxels = int64_t(1) << 22, kRangeVoxels = int64_t(1) << 24;
 
 // Slot k of the touched ranges, nullptr below `from` voxels.
 static RangePart *range_slot(const pct_plan &pl, void *ws, int64_t from, int64_t k)
@@ -2749,20 +2750,30 @@ static void launch_rows_fused(int lanes, hipStream_t s, const RowsDev &rows, con
 // Whether a call's stored rows go by bins, the same sums as by atomics, so the same
 // x.  Not where paths at 45 degrees have more pieces than k_rows_bin holds (the
 // others go by overflow words, piece by piece, and its commit then reads the
-// volume), and not where blocks are small for the volume, whose commit goes over
-// all windows where that of the fused schedule goes over the block's range.  By
-// bins / by atomics, us a block step: 3200 rows of 290 pieces on 200 x 200 x 32
-// 29.4 / 33.2, of 650 on 512 x 512 x 16 87 / 69 and of 1030 on 800 x 800 x 16
-// 204 / 160; slab-ordered blocks of 400 rows on 256 x 256 x 64 19.2 / 20.6, x 128
-// 26.6 / 20.4, x 256 40.1 / 28.5; in acquisition order
-// 19.8 / 24.3, 26.6 / 39.0 and 39.4 / 86.2.
+// volume: rows of 650 pieces on 512 x 512 x 16 87 us a step of 3200 by bins, 69 by
+// atomics, of 1030 on 800 x 800 x 16 204 and 160), and not where blocks are small
+// for the volume, whose commit goes over all windows where that of the fused
+// schedule goes over the block's range (slab-ordered blocks of 400 on 256 x 256 x 96
+// 24.7 and 16.6 us, of 1000 x 256 44.0 and 33.8; blocks over all slices pay for that,
+// 25.4 and 31.9, 43.6 and 101, which the call cannot tell).  Else whichever takes less: by bins
+// two launches and work by the row, by atomics one launch and work by the piece and
+// the voxel.  The costs are fitted (us a step, to about a tenth) to grids of 48 to
+// 256 voxels across and 4 to 64 slices, blocks of 250 to 8000 rows of one angle; by
+// bins / by atomics: 3200 rows on 200 x 200 x 32 27.9 / 31.8, 1600 22.4 / 17.1, 700
+// 17.4 / 11.9; 8000 on 128 x 128 x 32 33.6 / 37.7, 3200 22.8 / 19.6; 8000 on 64 x 64
+// x 64 29.1 / 20.9; 700 on 256 x 256 x 64 21.4 / 27.2.
 static bool rows_by_bins(const pct_plan &pl, int64_t block)
 {
-    const double depth = pl.mlp.u_out - pl.mlp.u_in;
-    const double pieces = std::min(M_SQRT2 * depth / std::min(pl.grid.pitch[0], pl.grid.pitch[1]),
-                                   double(pl.grid.nx) + double(pl.grid.ny)) +
-                          std::min(0.03 * depth / pl.grid.pitch[2], double(pl.grid.nz));
-    return pieces <= kBinRegs * kWave && block >= pl.nvox / 16384;
+    const pct_grid &g = pl.grid;
+    const double depth = pl.mlp.u_out - pl.mlp.u_in, pitch = std::min(g.pitch[0], g.pitch[1]);
+    const double most = std::min(M_SQRT2 * depth / pitch, double(g.nx) + double(g.ny)) +
+                        std::min(0.03 * depth / g.pitch[2], double(g.nz));
+    if (most > kBinRegs * kWave || block < pl.nvox / 12288) return false;
+    const double pieces = 1.1 * std::min(depth, std::max(g.nx * g.pitch[0], g.ny * g.pitch[1])) / pitch;
+    const double krows = 1e-3 * double(block), mvox = 1e-6 * double(pl.nvox);
+    const double by_bins = 10.0 + 0.02 * std::max(g.nx, g.ny) + krows * (1.5 + 0.012 * pieces) + mvox;
+    const double by_atomics = 4.0 + 0.034 * krows * pieces + 3.3 * mvox;
+    return by_bins < by_atomics;
 }
 
 int launch_drop_rows(pct_plan &pl, const pct_rows &rows, const float *b, float *x, const pct_drop_opts &o, void *ws,

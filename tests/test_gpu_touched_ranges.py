@@ -1,5 +1,5 @@
 """Commits over a block's touched range, on either side of the volumes from which
-the fused (2^23 voxels) and the separate schedule (2^24) take it: blocks that
+the fused (2^22 voxels) and the separate schedule (2^24) take it: blocks that
 touch a few slices each, in rising and falling order, one block that touches
 nothing, a last block that is not full, an odd and an even number of blocks a
 sweep, and recorded sweeps replayed.
@@ -40,7 +40,7 @@ def scan(nz, blocks, block, n):
     return grid, mlp, p, b
 
 
-@pytest.mark.parametrize("nz", [127, 128, 255, 256])
+@pytest.mark.parametrize("nz", [63, 64, 255, 256])
 @pytest.mark.parametrize("blocks,n_iter", [(4, 2), (5, 1), (5, 4)])
 def test_schedules_agree(nz, blocks, n_iter):
     block = 24
